@@ -487,15 +487,20 @@ gipc_status gipc_pairs_check(gipc_ctx* ctx, const gipc_mesh* mesh, const gipc_pa
     if ((st = bind_batch(ctx, params, pm)) != GIPC_OK) return st;
     hipStream_t s = S(stream);
     const double* xr = mesh->x_rest ? mesh->x_rest : mesh->x;
-    CK(ensure(ctx->chk, sizeof(int64_t) * 6), "alloc check counters");
-    const int64_t init[6] = {0, 0, 0, 0, 0, INT64_MAX};
+    int64_t init[kCheckCopies][kCheckStride] = {}, hc[kCheckCopies][kCheckStride];
+    for (auto& c : init) c[5] = INT64_MAX;
+    CK(ensure(ctx->chk, sizeof(init)), "alloc check counters");
     CK(hipMemcpyAsync(ctx->chk.p, init, sizeof(init), hipMemcpyHostToDevice, s), "clear check counters");
     CK(launch_stage_check(pairs->tuples, pairs->P, mesh->V, mesh->x, xr, pm, as<uint8_t>(ctx->cand_ft),
                           as<int4>(ctx->cand_vid), as<int64_t>(ctx->chk), s),
        "check");
-    int64_t h[6];
-    CK(hipMemcpyAsync(h, ctx->chk.p, sizeof(h), hipMemcpyDeviceToHost, s), "copy check counters");
+    CK(hipMemcpyAsync(hc, ctx->chk.p, sizeof(hc), hipMemcpyDeviceToHost, s), "copy check counters");
     CK(hipStreamSynchronize(s), "stream synchronize");
+    int64_t h[6] = {0, 0, 0, 0, 0, INT64_MAX};
+    for (const auto& c : hc) {
+        for (int i = 0; i < 5; ++i) h[i] += c[i];
+        h[5] = std::min(h[5], c[5]);
+    }
     if (h[4] > 0) return fail(ctx, GIPC_ERR_INDEX, "%lld malformed tuple(s)", (long long)h[4]);
     gipc_check c{h[0], h[1], h[2], h[3], (h[0] + h[2] > 0) ? h[5] : -1};
     if (out) *out = c;

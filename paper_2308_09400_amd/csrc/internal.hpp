@@ -210,8 +210,10 @@ hipError_t launch_stage_classify(const int32_t* tuples, int64_t P, int32_t V, co
 hipError_t launch_stage_scatter(const uint8_t* ft, const int4* vid, int64_t P, const int64_t* boff, int4* st_vid,
                                 int32_t* st_src, hipStream_t s);
 // the build's classification (ft_b, vid_b) against the one at x; counters
-// (device int64 [6], zeroed, [5] = INT64_MAX): entered, left, changed,
-// degenerate, malformed, first changed tuple
+// (device int64 [kCheckCopies][kCheckStride], each copy's first six zeroed,
+// [5] = INT64_MAX): entered, left, changed, degenerate, malformed, first
+// changed tuple; the result is the sum (the smallest [5]) over the copies
+constexpr int kCheckCopies = 64, kCheckStride = 16;
 hipError_t launch_stage_check(const int32_t* tuples, int64_t P, int32_t V, const double* x, const double* xr,
                               const DevParams& pm, const uint8_t* ft_b, const int4* vid_b, int64_t* counters,
                               hipStream_t s);

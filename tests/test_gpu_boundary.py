@@ -267,3 +267,37 @@ def test_pairs_check_reports_stale_builds(gp):
         gp.pairs_check(gpu3["ctx"], gpu3["X"], T[:1].contiguous(), prm, x_rest=gpu3["XR"])
     assert ei.value.status == gp.ERR_STATE
     gpu3["ctx"].close()
+
+
+@pytest.mark.parametrize("P", [1, 63, 64, 255, 256, 257, 64 * 256 + 3, 70001])
+def test_pairs_check_counts_every_tuple(gp, P):
+    """Lists that end inside a wavefront, a workgroup and a round over the
+    copies of the counters: every third point comes within dhat, every third
+    leaves, and the counts and the first entered tuple are exact."""
+    rng = np.random.default_rng(P)
+    z0, z1 = np.full(P, 0.5), np.full(P, 0.5)
+    enter = np.arange(P) % 3 == 1
+    leave = np.arange(P) % 3 == 2
+    z0[enter], z1[leave] = 2.0, 3.0
+    tri = np.array([[0, 0, 0], [1, 0, 0], [0, 1, 0]], float)
+    xy = rng.uniform(0.1, 0.4, (P, 2))
+    dev = torch.device("cuda")
+
+    def positions(z):
+        return torch.tensor(np.concatenate([tri, np.concatenate([xy, z[:, None] * DH], 1)]), device=dev)
+
+    T = torch.tensor(np.stack([-(np.arange(3, P + 3) + 1), np.zeros(P), np.ones(P), np.full(P, 2)], 1),
+                     dtype=torch.int32, device=dev)
+    keep = np.flatnonzero(~enter)[:2000]  # the build's limit of pairs per vertex
+    sel = np.zeros(P, bool)
+    sel[keep] = True
+    z0[~sel & ~enter], z1[~sel & ~enter] = 2.0, 2.0  # the others stay inactive
+    leave &= sel
+    ctx, prm = gp.Context(), gp.params(dhat=DH)
+    gp.pairs_build(ctx, positions(z0), T, prm)
+    stale, c = gp.pairs_check(ctx, positions(z1), T, prm)
+    n = int(enter.sum())
+    first = int(np.flatnonzero(enter)[0]) if n else -1
+    assert stale == (n > 0)
+    assert c == {"n_entered": n, "n_left": int(leave.sum()), "n_changed": 0, "n_degenerate": 0, "first": first}
+    ctx.close()
