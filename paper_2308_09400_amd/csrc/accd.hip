@@ -15,27 +15,75 @@
 // returned) or the time passes tc (tc is returned).  Distances are the
 // constrained minimum of the tuple's primitives (Eq. 4 / Eq. 5), evaluated
 // at each trial point from x, not accumulated.
+#include <algorithm>
+
 #include "internal.hpp"
 
 namespace gipc {
 namespace {
 
+// 1 / v for v > 0 to about 2^-45: v_rcp_f64 and one Newton step.  Used for
+// the parameter of a closest point on a segment only: the distance is
+// stationary there, so this error enters it squared, below its rounding.
+__device__ __forceinline__ double rcp_near(double v) {
+    const double r = __builtin_amdgcn_rcp(v);
+    return fma(r, fma(-v, r, 1.0), r);
+}
+
+// squared distance of the point a + ap to the segment from a along ab, il2 =
+// 1 / |ab|^2 (0 for one shorter than 1e-150: its first end point then)
+__device__ __forceinline__ double seg_dist2_near(d3 ap, d3 ab, double il2) {
+    const double t = dot(ap, ab) * il2;
+    const d3 w = ap - fmin(fmax(t, 0.0), 1.0) * ab;
+    return dot(w, w);
+}
+__device__ __forceinline__ double inv_len2(double l2) { return l2 > 1e-300 ? rcp_near(l2) : 0.0; }
+
+// the constrained minimum of Eq. 4 / Eq. 5 over the sub-problems of
+// classify_pt and classify_ee, without the sub-problem it is attained at: the
+// interior tests compare numerators, and a distance has one full division
+// (six or seven there)
+__device__ __forceinline__ double near_pt2(d3 p, d3 t0, d3 t1, d3 t2) {
+    const d3 e1 = t1 - t0, e2 = t2 - t0, e3 = t2 - t1, r = p - t0, r1 = p - t1;
+    const d3 n = cross(e1, e2);
+    const double nn = dot(n, n), a11 = dot(e1, e1), a22 = dot(e2, e2), a12 = dot(e1, e2);
+    const double b1 = dot(e1, r), b2 = dot(e2, r);
+    const double u = a22 * b1 - a12 * b2, v = a11 * b2 - a12 * b1, h = dot(r, n);
+    double best = INFINITY;
+    if (nn > kInteriorTol * a11 * a22 && u >= 0.0 && v >= 0.0 && u + v <= nn) best = h * h / nn;
+    best = fmin(best, seg_dist2_near(r, e1, inv_len2(a11)));
+    best = fmin(best, seg_dist2_near(r1, e3, inv_len2(dot(e3, e3))));
+    return fmin(best, seg_dist2_near(r, e2, inv_len2(a22)));
+}
+
+__device__ __forceinline__ double near_ee2(d3 a0, d3 a1, d3 b0, d3 b1) {
+    const d3 a = a1 - a0, b = b1 - b0, r = a0 - b0;
+    const d3 n = cross(a, b);
+    const double cc = dot(n, n), aa = dot(a, a), bb = dot(b, b);
+    const double ab = dot(a, b), ar = dot(a, r), br = dot(b, r);
+    const double u = ab * br - bb * ar, v = aa * br - ab * ar, h = dot(r, n);
+    double best = INFINITY;
+    if (cc > kInteriorTol * aa * bb && u >= 0.0 && u <= cc && v >= 0.0 && v <= cc) best = h * h / cc;
+    const double ia = inv_len2(aa), ib = inv_len2(bb);
+    best = fmin(best, seg_dist2_near(r, b, ib));
+    best = fmin(best, seg_dist2_near(a1 - b0, b, ib));
+    best = fmin(best, seg_dist2_near(b0 - a0, a, ia));
+    return fmin(best, seg_dist2_near(b1 - a0, a, ia));
+}
+
 // constrained squared distance of a decoded tuple whose four slots are the
 // local positions L[0..11] (slot k at L[3k])
 __device__ __forceinline__ double local_dist2(int kind, const double* L) {
-    DevParams pm{};  // no mollifier decision: only the distance is wanted
-    double d2 = 0.0;
-    bool degen;
-    if (kind == 0) (void)classify_ee(L, nullptr, 0, 1, 2, 3, pm, d2, degen);
-    else if (kind == 1) (void)classify_pt(L, 0, 1, 2, 3, d2, degen);
-    else if (kind == 2) (void)classify_pe(L, 0, 1, 2, d2, degen);
-    else if (kind == 3) {
-        const d3 w = ld3(L, 0) - ld3(L, 1);
-        d2 = dot(w, w);
-    } else {
-        (void)classify_par(L, nullptr, 0, 1, 2, 3, kind == 4, pm, d2, degen);
-    }
-    return d2;
+    const d3 p0 = ld3(L, 0), p1 = ld3(L, 1), p2 = ld3(L, 2), p3 = ld3(L, 3);
+    if (kind == 0) return near_ee2(p0, p1, p2, p3);
+    if (kind == 1) return near_pt2(p0, p1, p2, p3);
+    // point against a segment (kinds 2 and 4) or a point (3 and 5)
+    const bool par = kind >= 4;
+    const d3 a = par ? p2 : p1, b = par ? p3 : p2;
+    const d3 w = p0 - a;
+    if (kind == 3 || kind == 5) return dot(w, w);
+    const d3 e = b - a;
+    return seg_dist2_near(w, e, inv_len2(dot(e, e)));
 }
 
 // counters: [0] malformed tuples, [1] first malformed index, [2] tuples
@@ -55,66 +103,88 @@ __global__ void k_accd_reset(unsigned long long* c, double tc) {
 }
 
 // Every lane keeps one tuple's search state and takes the next tuple from a
-// queue as soon as its search ends (a wavefront takes kAccdChunk queue
+// queue when its search has ended (a wavefront takes a chunk of queue
 // entries at a time with one atomic), so a wavefront does not wait on its
-// slowest lane: on the ten-sheet candidates the searches take 1 to 766
-// trial steps, and one lane per tuple took 18.1 ms against 3.2 ms here.
-// The grid is a fixed number of workgroups that run until the queue is
-// empty; every search ends within max_iter steps, so every wavefront does.
-constexpr int kAccdChunk = 256;
-constexpr int kAccdGrid = 2048;  // workgroups: more than the chip holds at once
+// slowest lane: the searches take 1 to several hundred trial steps, and with
+// one lane per tuple the ten-sheet candidates took five times as long.  A
+// round of the loop forms one distance per lane, the initial one of a new
+// tuple or that of a trial point, through the same code; lanes are refilled
+// kAccdRefill at a time, since a round with a refill pays for its loads
+// whatever their number.  A first sub-step past tc ends the search without
+// its distance, which the answer does not depend on (two in five searches).
+// The displacements stay in LDS, 24 registers fewer and so a fourth
+// wavefront per SIMD.  Bound by vector issue (three quarters of the slots).
+// The 50.6M candidates of ten 256 x 256 sheets, each falling or jittering by
+// about dhat: 1.82 ms; with the initial distance apart from the trials, lanes
+// refilled one at a time, a division in every segment test and three atomics
+// on one line per wavefront and 256 tuples it was 3.97 ms, and 826k
+// candidates of three 101 x 101 sheets 378 against 68 us (there the atomics,
+// 20 ns apart, were nearly all of it).
+// The grid is at most the workgroups the chip holds at once; each wavefront
+// starts with a chunk of its own and takes further ones from the queue until
+// it is empty; every search ends within max_iter steps, so every wavefront
+// does.
+constexpr int kAccdRefill = 32;
+constexpr int kAccdGrid = 1024;
 
-__global__ void __launch_bounds__(kBlock) k_accd_queue(const int4* __restrict__ tuples, int64_t P, int32_t V,
+__global__ void __launch_bounds__(kBlock, 4) k_accd_queue(const int4* __restrict__ tuples, int64_t P, int32_t V,
                                                        const double* __restrict__ X, const double* __restrict__ D,
-                                                       double s, double tc, int32_t max_iter,
+                                                       double s, double tc, int32_t max_iter, int32_t chunk,
                                                        double* __restrict__ toi_out,
                                                        unsigned long long* __restrict__ c) {
     const int lane = threadIdx.x & 63;
     const unsigned long long below = lane == 0 ? 0ull : (~0ull >> (64 - lane));
-    int64_t cb = 0, ce = 0;   // the wavefront's current chunk [cb, ce)
+    // the wavefront's current chunk [cb, ce); the first ones need no atomic
+    int64_t cb = ((int64_t)blockIdx.x * (kBlock / 64) + (threadIdx.x >> 6)) * chunk;
+    int64_t ce = cb + chunk < P ? cb + chunk : P;
+    const int64_t queue0 = (int64_t)gridDim.x * (kBlock / 64) * chunk;
     bool exhausted = false;
-    bool act = false;
+    bool act = false, fresh = false;  // fresh: the lane's tuple has no distance yet
     int64_t p = 0;
     int kind = 0, it = 0, itmax = 0;
-    double x0[12], dp[12];
-    double lp = 0.0, g = 0.0, t = 0.0, tl = 0.0, tmin = tc;
+    __shared__ double sdp[kBlock / 64][12][64];
+    double(*dl)[64] = sdp[threadIdx.x >> 6];  // the lanes' displacements
+    double x0[12];
+    double lp = 0.0, ilp = 0.0, g = 0.0, t = 0.0, tl = 0.0, tmin = tc;
     while (true) {
-        unsigned long long idle = __ballot(!act);
-        while (idle != 0ull && !exhausted) {
+        const unsigned long long idle = __ballot(!act);
+        if (!exhausted && __popcll(idle) >= kAccdRefill) {
             if (cb >= ce) {
-                unsigned long long b = 0ull;
-                if (lane == 0) b = atomicAdd(&c[6], (unsigned long long)kAccdChunk);
-                cb = (int64_t)__shfl(b, 0, 64);
-                ce = cb + kAccdChunk < P ? cb + kAccdChunk : P;
-                if (cb >= P) {
-                    exhausted = true;
-                    break;
+                cb = P;
+                if (queue0 < P) {
+                    unsigned long long b = 0ull;
+                    if (lane == 0) b = atomicAdd(&c[6], (unsigned long long)chunk);
+                    cb = queue0 + (int64_t)__shfl(b, 0, 64);
                 }
+                ce = cb + chunk < P ? cb + chunk : P;
+                exhausted = cb >= P;
             }
-            const int64_t take = (int64_t)__popcll(idle) < ce - cb ? (int64_t)__popcll(idle) : ce - cb;
+            const int64_t left = ce > cb ? ce - cb : 0;
+            const int64_t take = (int64_t)__popcll(idle) < left ? (int64_t)__popcll(idle) : left;
             const int64_t rank = __popcll(idle & below);
-            const bool got = !act && rank < take;
-            if (got) p = cb + rank;
-            cb += take;
-            if (got) {
+            if (!act && rank < take) {
+                p = cb + rank;
                 int v[4], nv;
                 kind = decode_tuple(tuples[p], V, v, nv);
-                double res = tc;
-                bool done = true;
                 if (kind < 0) {
                     atomicAdd(&c[0], 1ull);
                     atomicMin(&c[1], (unsigned long long)p);
-                    res = 0.0;
+                    if (toi_out) toi_out[p] = 0.0;
+                    tmin = fmin(tmin, 0.0);
                 } else {
+                    act = fresh = true;
+                    double dp[12];
 #pragma unroll
                     for (int k = 0; k < 4; ++k) {
                         const bool use = k < nv;
                         const int vk = use ? v[k] : 0;
-#pragma unroll
-                        for (int d = 0; d < 3; ++d) {
-                            x0[3 * k + d] = use ? X[3ll * vk + d] : 0.0;
-                            dp[3 * k + d] = use ? D[3ll * vk + d] : 0.0;
-                        }
+                        const d3 xv = ld3(X, vk), dv = ld3(D, vk);
+                        x0[3 * k] = use ? xv.x : 0.0;
+                        x0[3 * k + 1] = use ? xv.y : 0.0;
+                        x0[3 * k + 2] = use ? xv.z : 0.0;
+                        dp[3 * k] = use ? dv.x : 0.0;
+                        dp[3 * k + 1] = use ? dv.y : 0.0;
+                        dp[3 * k + 2] = use ? dv.z : 0.0;
                     }
                     int nf = 1, sb = 1, ns = 1;
                     switch (kind) {
@@ -125,6 +195,7 @@ __global__ void __launch_bounds__(kBlock) k_accd_queue(const int4* __restrict__ 
                         case 4: sb = 2; ns = 2; break;
                         default: sb = 2; break;
                     }
+                    const double im = nf + ns == 4 ? 0.25 : (nf + ns == 3 ? 1.0 / 3.0 : 0.5);
                     double m[3] = {0.0, 0.0, 0.0};
 #pragma unroll
                     for (int k = 0; k < 4; ++k) {
@@ -133,85 +204,121 @@ __global__ void __launch_bounds__(kBlock) k_accd_queue(const int4* __restrict__ 
                         for (int d = 0; d < 3; ++d) m[d] += in ? dp[3 * k + d] : 0.0;
                     }
 #pragma unroll
-                    for (int d = 0; d < 3; ++d) m[d] /= (double)(nf + ns);
+                    for (int d = 0; d < 3; ++d) m[d] *= im;
 #pragma unroll
                     for (int k = 0; k < 4; ++k)
 #pragma unroll
                         for (int d = 0; d < 3; ++d) dp[3 * k + d] -= m[d];
-                    double l1 = 0.0, l2 = 0.0;
+#pragma unroll
+                    for (int j = 0; j < 12; ++j) dl[j][lane] = dp[j];
+                    double l1 = 0.0, l2 = 0.0;  // squared, the root taken of the largest
 #pragma unroll
                     for (int k = 0; k < 4; ++k) {
-                        const double n = sqrt(dp[3 * k] * dp[3 * k] + dp[3 * k + 1] * dp[3 * k + 1] +
-                                              dp[3 * k + 2] * dp[3 * k + 2]);
-                        if (k < nf) l1 = fmax(l1, n);
-                        else if (k >= sb && k < sb + ns) l2 = fmax(l2, n);
+                        const double n2 = dp[3 * k] * dp[3 * k] + dp[3 * k + 1] * dp[3 * k + 1] +
+                                          dp[3 * k + 2] * dp[3 * k + 2];
+                        if (k < nf) l1 = fmax(l1, n2);
+                        else if (k >= sb && k < sb + ns) l2 = fmax(l2, n2);
                     }
-                    lp = l1 + l2;
-                    const double dd0 = local_dist2(kind, x0);
-                    if (!(dd0 > 0.0) || !(dd0 < INFINITY)) {
-                        atomicAdd(&c[3], 1ull);
-                        res = 0.0;
-                    } else if (lp > 0.0) {
-                        const double d0 = sqrt(dd0);
-                        g = s * d0;
-                        t = 0.0;
-                        tl = (1.0 - s) * d0 / lp;
-                        it = 0;
-                        done = false;
-                    }
-                }
-                if (done) {
-                    if (toi_out) toi_out[p] = res;
-                    tmin = fmin(tmin, res);
-                } else {
-                    act = true;
+                    lp = sqrt(l1) + sqrt(l2);
+                    ilp = 1.0 / lp;
                 }
             }
-            idle = __ballot(!act);
+            cb += take;
         }
-        if (__ballot(act) == 0ull) break;  // the queue is empty and every search has ended
+        if (__ballot(act) == 0ull) {
+            if (exhausted) break;  // the queue is empty and every search has ended
+            continue;
+        }
         if (act) {
-            ++it;
-            double xt[12];
             const double tt = t + tl;
+            const double ts = fresh ? 0.0 : tt;
+            double xt[12];
 #pragma unroll
-            for (int j = 0; j < 12; ++j) xt[j] = x0[j] + tt * dp[j];
-            const double dd = sqrt(local_dist2(kind, xt));
+            for (int j = 0; j < 12; ++j) xt[j] = fma(ts, dl[j][lane], x0[j]);
+            if (fresh && !(lp < INFINITY)) {  // 0 * infinity: a displacement that is not finite
+#pragma unroll
+                for (int j = 0; j < 12; ++j) xt[j] = x0[j];
+            }
+            const double dd2 = local_dist2(kind, xt);
             bool fin = false;
             double res = 0.0;
-            if (t > 0.0 && dd < g) {
-                res = t;
-                fin = true;
-            } else {
-                t = t + tl;
-                if (t > tc) {
+            if (fresh) {
+                fresh = false;
+                if (!(dd2 > 0.0) || !(dd2 < INFINITY)) {
+                    atomicAdd(&c[3], 1ull);
+                    fin = true;
+                } else if (lp > 0.0) {
+                    const double d0 = sqrt(dd2);
+                    g = s * d0;
+                    t = 0.0;
+                    tl = (1.0 - s) * d0 * ilp;
+                    it = 0;
+                    if (tl > tc) {
+                        res = tc;
+                        fin = true;
+                        itmax = max(itmax, 1);
+                    }
+                } else {
                     res = tc;
                     fin = true;
+                }
+            } else {
+                ++it;
+                const double dd = sqrt(dd2);
+                if (t > 0.0 && dd < g) {
+                    res = t;
+                    fin = true;
                 } else {
-                    tl = 0.9 * dd / lp;
-                    if (it >= max_iter) {
-                        atomicAdd(&c[2], 1ull);
-                        res = t;
+                    t = tt;
+                    if (t > tc) {
+                        res = tc;
                         fin = true;
+                    } else {
+                        tl = 0.9 * dd * ilp;
+                        if (it >= max_iter) {
+                            atomicAdd(&c[2], 1ull);
+                            res = t;
+                            fin = true;
+                        } else if (t + tl > tc && 0.1 * dd > (1.0 + 1e-9) * g) {
+                            // the next trial lies past tc, and its distance,
+                            // at least dd - lp tl = 0.1 dd, not below g
+                            ++it;
+                            res = tc;
+                            fin = true;
+                        }
                     }
                 }
+                if (fin) itmax = max(itmax, it);
             }
             if (fin) {
                 if (toi_out) toi_out[p] = res;
                 tmin = fmin(tmin, res);
-                itmax = max(itmax, it);
                 act = false;
             }
         }
     }
+    // the workgroup's smallest time and most steps; memory only if they change it
+    __shared__ double wmin[kBlock / 64];
+    __shared__ int wmax[kBlock / 64];
 #pragma unroll
     for (int o = 32; o > 0; o >>= 1) {
         tmin = fmin(tmin, __shfl_xor(tmin, o, 64));
         itmax = max(itmax, __shfl_xor(itmax, o, 64));
     }
     if (lane == 0) {
-        atomicMin(&c[4], (unsigned long long)__double_as_longlong(tmin));
-        atomicMax(&c[5], (unsigned long long)itmax);
+        wmin[threadIdx.x >> 6] = tmin;
+        wmax[threadIdx.x >> 6] = itmax;
+    }
+    __syncthreads();
+    if (threadIdx.x == 0) {
+        for (int w = 1; w < kBlock / 64; ++w) {
+            tmin = fmin(tmin, wmin[w]);
+            itmax = max(itmax, wmax[w]);
+        }
+        const unsigned long long tb = (unsigned long long)__double_as_longlong(tmin);
+        if (tb < __hip_atomic_load(&c[4], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT)) atomicMin(&c[4], tb);
+        if ((unsigned long long)itmax > __hip_atomic_load(&c[5], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT))
+            atomicMax(&c[5], (unsigned long long)itmax);
     }
 }
 
@@ -223,8 +330,14 @@ hipError_t launch_accd(const int32_t* tuples, int64_t P, int32_t V, const double
     if (P > 0) {
         int64_t nb = (P + kBlock - 1) / kBlock;
         if (nb > kAccdGrid) nb = kAccdGrid;
+        // a quarter of a wavefront's share at once, at most 2048 tuples, so
+        // that few of the queue's atomics (one line: 20 ns apart) are needed;
+        // shares of up to 256 tuples are dealt out whole, without any
+        const int64_t waves = nb * (kBlock / 64), share = (P + waves - 1) / waves;
+        int64_t chunk = (share + 63) / 64 * 64;
+        if (chunk > 256) chunk = std::min<int64_t>(2048, std::max<int64_t>(64, share / 4 / 64 * 64));
         k_accd_queue<<<(unsigned)nb, kBlock, 0, st>>>(reinterpret_cast<const int4*>(tuples), P, V, x, disp, s, tc,
-                                                      max_iter, toi, counters);
+                                                      max_iter, (int32_t)chunk, toi, counters);
     }
     return hipGetLastError();
 }

@@ -74,6 +74,17 @@ __device__ __forceinline__ int vslot(const int4& v, int j) {
 // tuple: a pattern not above, an id outside [0, V) or a repeated id.
 __device__ __forceinline__ int decode_tuple(const int4 t, int32_t V, int v[4], int& nv) {
     int kind = -1;
+    if ((t.z | t.w) >= 0 && (t.x & t.y) >= 0) {
+        // the two kinds a broad phase gives, without the branches of the rest
+        v[0] = t.x >= 0 ? t.x : ~t.x;
+        v[1] = t.y >= 0 ? t.y : ~t.y;
+        v[2] = t.z;
+        v[3] = t.w;
+        nv = 4;
+        const bool ok = max(max(v[0], v[1]), max(v[2], v[3])) < V && v[0] != v[1] && v[0] != v[2] && v[0] != v[3] &&
+                        v[1] != v[2] && v[1] != v[3] && v[2] != v[3];
+        return ok ? (t.x >= 0 ? 0 : 1) : -1;
+    }
     v[0] = v[1] = v[2] = v[3] = -1;
     nv = 0;
     if (t.x >= 0) {

@@ -13,6 +13,9 @@
 * the ten-sheet candidate list (51M tuples) moved toward contact: sampled
   tuples against the oracle, the step against the smallest sampled time
   and the whole-list minimum;
+* lists of 1 to a few thousand tuples (below, at and above a refill, a
+  wavefront and a chunk of the queue), one malformed among them too: every
+  time, the largest number of trial steps and the error;
 * without the per-tuple output the same step;
 * malformed tuples and bad arguments are errors.
 """
@@ -231,3 +234,22 @@ def test_ten_sheets_sampled(gp, ctx):
     assert info["n_capped"] == 0 and capped == 0
     _, info2 = gp.accd(ctx, x, _dev(disp), tup, s=S, tc=1.0, per_tuple=False)
     assert info2["step"] == info["step"] and info2["max_steps"] == info["max_steps"]
+
+
+@pytest.mark.parametrize("P", [1, 31, 32, 33, 63, 64, 65, 257, 2500])
+@pytest.mark.parametrize("tc", [1.0, 0.05])
+def test_queue_sizes(gp, ctx, P, tc):
+    s = scenes.two_sheets(n=6, dhat=0.15, kappa=10.0, seed=5, offset=0.5, jitter=0.3)
+    rng = np.random.default_rng(P)
+    d = rng.normal(size=s.x.shape) * 0.05
+    d[:, 2] -= 0.1 * (np.arange(s.V) >= s.V // 2)
+    t = s.tuples[rng.integers(0, s.P, P)]
+    _, st = scenes.decode_tuples(t)
+    ref = [oracle.accd(t[k], s.x[st[k][st[k] >= 0]], d[st[k][st[k] >= 0]], s=S, tc=tc) for k in range(P)]
+    toi, info = _run(gp, ctx, s.x, d, t, tc=tc)
+    _check(toi, np.array([r[0] for r in ref]))
+    assert info["step"] == toi.min() and info["max_steps"] == max(r[1] for r in ref)
+    t[P // 2] = [0, 0, 1, 2]
+    with pytest.raises(gp.GipcError) as ei:
+        _run(gp, ctx, s.x, d, t, tc=tc)
+    assert ei.value.status == gp.ERR_INDEX
