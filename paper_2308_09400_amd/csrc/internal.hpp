@@ -134,6 +134,7 @@ struct PcgScalars {  // device-resident scalars of the PCG loop
     int iters, done, breakdown, maxit;
     int delta;  // stopping test: 0 r.r <= rtol2 b.b, 1 r.z <= rtol2 r0.z0
     int conv;   // the stopping test held
+    double rzb[2];  // r.z by the parity of the iteration that reads it
 };
 
 }  // namespace gipc

@@ -38,10 +38,14 @@
 // PCG (Saad Alg. 9.1 with the inverse 3x3 diagonal blocks as
 // preconditioner, the paper's simple block preconditioner of Sec. 7.2):
 // every scalar (alpha, beta, residual norms, the stopping test) lives in
-// device memory, so an iteration is six kernel launches without host
+// device memory, so an iteration is a few kernel launches without host
 // round trips (product, p.q partials, alpha, update with the r.z and r.r
-// partials, beta, p update); the host polls the "done" flag every 16
-// iterations (once when rtol = 0).  The p.q partials are a pass of their
+// partials, beta, p update: six, four up to 65536 rows and two up to 4096,
+// see kMergeParts); the host polls the "done" flag every 16
+// iterations (once when rtol = 0).  Every other iteration walks the matrix
+// backwards, so that it starts with the blocks read last, some of which the
+// 256 MB cache still holds: 6.84 against 6.94 ms for 20 iterations on ten
+// 256 x 256 sheets (1.25 GB of blocks).  The p.q partials are a pass of their
 // own over p and q: formed in the product's epilogue (a block reduction
 // at the end of every product workgroup) they cost 355 against 327 us per
 // FP64 iteration on the ten-sheet matrix, and 254 against 223 us in FP32.
@@ -98,14 +102,15 @@ __global__ void __launch_bounds__(kEntBlock) k_spmv_ent(int64_t nnzb, const int3
                                                         const unsigned long long* __restrict__ hm,
                                                         const int32_t* __restrict__ wrow,
                                                         const double* __restrict__ x, double* __restrict__ y,
-                                                        const PcgScalars* __restrict__ sc) {
+                                                        const PcgScalars* __restrict__ sc, int rev) {
     if (sc && sc->done) return;
+    const unsigned wg = rev ? gridDim.x - 1 - blockIdx.x : blockIdx.x;
     __shared__ double sf[kEntWaves][3], sl[kEntWaves][3], stail[3];
     __shared__ unsigned long long sm[kEntWaves], smn[kEntWaves];
     __shared__ int32_t srow[kEntWaves];
     const int64_t W = (nnzb + 63) >> 6;
     const int wi = threadIdx.x >> 6, l = threadIdx.x & 63;
-    const int64_t w = (int64_t)__builtin_amdgcn_readfirstlane((int)(blockIdx.x * kEntWaves + wi));
+    const int64_t w = (int64_t)__builtin_amdgcn_readfirstlane((int)(wg * kEntWaves + wi));
     if (w < W) {
         const int64_t s = (w << 6) + l;
         const bool ok = s < nnzb;
@@ -279,30 +284,43 @@ __device__ __forceinline__ double sum_parts(const double* __restrict__ part, int
     return block_sum_n<kRed>(s, lds);
 }
 
-// inverse of each row's diagonal block (cofactors, FP64); identity if singular
+// inverse of each row's diagonal block (cofactors, FP64); identity if
+// singular.  kBjLanes lanes per row look for the diagonal together: one lane
+// walking its row's columns waited for a dozen dependent loads (ten 256 x 256
+// sheets: 218 against 160 us now).
+constexpr int kBjLanes = 8;
 template <typename T>
 __global__ void __launch_bounds__(kBlock) k_bj_inverse(int32_t V, const int32_t* __restrict__ rp,
                                                        const int32_t* __restrict__ ci, const T* __restrict__ val,
                                                        int64_t nnzb, double* __restrict__ minv) {
-    const int64_t r = (int64_t)blockIdx.x * kBlock + threadIdx.x;
-    if (r >= V) return;
-    double A[9] = {0, 0, 0, 0, 0, 0, 0, 0, 0};
-    for (int32_t s = rp[r]; s < rp[r + 1]; ++s)
+    const int64_t r = ((int64_t)blockIdx.x * kBlock + threadIdx.x) / kBjLanes;
+    const int lg = threadIdx.x % kBjLanes;
+    if (r >= V) return;  // the whole lane group
+    const int32_t e = rp[r + 1];
+    int32_t at = INT32_MAX;
+    for (int32_t s = rp[r] + lg; s < e; s += kBjLanes)
         if (ci[s] == r) {
-            for (int c = 0; c < 9; ++c) A[c] = (double)val[c * nnzb + s];
+            at = s;
             break;
         }
+#pragma unroll
+    for (int o = kBjLanes / 2; o > 0; o >>= 1) at = min(at, __shfl_xor(at, o, kBjLanes));
+    double A[9] = {0, 0, 0, 0, 0, 0, 0, 0, 0};
+    if (at != INT32_MAX)
+#pragma unroll
+        for (int c = 0; c < 9; ++c) A[c] = (double)val[c * nnzb + at];
     double c00 = A[4] * A[8] - A[5] * A[7], c01 = A[5] * A[6] - A[3] * A[8], c02 = A[3] * A[7] - A[4] * A[6];
     double det = A[0] * c00 + A[1] * c01 + A[2] * c02;
-    double* M = minv + 9 * r;
-    if (!(fabs(det) > 0.0) || !isfinite(det)) {
-        for (int c = 0; c < 9; ++c) M[c] = (c % 4 == 0) ? 1.0 : 0.0;
-        return;
+    double M[9] = {1, 0, 0, 0, 1, 0, 0, 0, 1};
+    if (fabs(det) > 0.0 && isfinite(det)) {
+        double id = 1.0 / det;
+        M[0] = c00 * id; M[1] = (A[2] * A[7] - A[1] * A[8]) * id; M[2] = (A[1] * A[5] - A[2] * A[4]) * id;
+        M[3] = c01 * id; M[4] = (A[0] * A[8] - A[2] * A[6]) * id; M[5] = (A[2] * A[3] - A[0] * A[5]) * id;
+        M[6] = c02 * id; M[7] = (A[1] * A[6] - A[0] * A[7]) * id; M[8] = (A[0] * A[4] - A[1] * A[3]) * id;
     }
-    double id = 1.0 / det;
-    M[0] = c00 * id; M[1] = (A[2] * A[7] - A[1] * A[8]) * id; M[2] = (A[1] * A[5] - A[2] * A[4]) * id;
-    M[3] = c01 * id; M[4] = (A[0] * A[8] - A[2] * A[6]) * id; M[5] = (A[2] * A[3] - A[0] * A[5]) * id;
-    M[6] = c02 * id; M[7] = (A[1] * A[6] - A[0] * A[7]) * id; M[8] = (A[0] * A[4] - A[1] * A[3]) * id;
+#pragma unroll
+    for (int c = 0; c < 9; ++c)
+        if (lg == c % kBjLanes) minv[9 * r + c] = M[c];
 }
 
 __device__ __forceinline__ d3 apply3(const double* M, d3 v) {
@@ -426,7 +444,7 @@ __global__ void __launch_bounds__(kRed) k_pcg_beta(int first, const double* __re
     const double BB = first ? sum_parts(part + 2 * nb, nb, lds) : 0.0;
     if (threadIdx.x != 0) return;
     if (first) {
-        sc->rz = RZ; sc->rr = RR; sc->bb = BB; sc->rtol2 = rtol2; sc->rz0 = RZ;
+        sc->rz = RZ; sc->rzb[0] = RZ; sc->rr = RR; sc->bb = BB; sc->rtol2 = rtol2; sc->rz0 = RZ;
         sc->pq = 0; sc->alpha = 0; sc->beta = 0;
         sc->iters = 0; sc->breakdown = 0; sc->maxit = maxit; sc->delta = delta;
         sc->conv = delta ? (RZ <= rtol2 * RZ) : (RR <= rtol2 * BB);
@@ -456,6 +474,166 @@ __global__ void __launch_bounds__(kBlock) k_pupdate(int64_t n, const double* __r
     }
 }
 
+// The same iteration with fewer launches, for systems whose kernels are
+// shorter than the gaps between them.  Up to kMergeParts workgroups of rows,
+// every workgroup of the update forms alpha, and every one of the p update
+// beta, from the partials itself (a few KB from L2): two launches fewer.  Up
+// to kVecRows rows one workgroup does everything between two products: four
+// launches fewer, about 4.5 us each where launches are what a solve waits
+// for.  A whole Newton step of two 16 x 16 sheets (512 rows, 16 iterations)
+// 1.22 -> 0.93 ms, of three 101 x 101 sheets (30603 rows, 16 iterations) with
+// 0.31 ms of it from elsewhere 1.88 -> 1.46 ms.  One workgroup walks 4096 rows
+// in about the time of the three launches it saves; above 65536 rows the
+// partials that every workgroup would read again outweigh a launch.
+constexpr int kMergeParts = 256;
+constexpr int kVecThreads = 1024;
+constexpr int kVecRows = 4096;
+
+// sum of part[0..n), in every thread of the workgroup (fixed order)
+__device__ __forceinline__ double wg_total(const double* __restrict__ part, int64_t n, double* lds) {
+    double a = 0.0;
+    for (int64_t i = threadIdx.x; i < n; i += kBlock) a += part[i];
+    a = block_sum(a, lds);
+    if (threadIdx.x == 0) lds[0] = a;
+    __syncthreads();
+    a = lds[0];
+    __syncthreads();
+    return a;
+}
+
+// alpha, x += alpha p, r -= alpha q, z = M^-1 r, partials (r.z, r.r).  The
+// scalars that other workgroups read are not written here, save done at a
+// breakdown, which they all find by themselves.
+__global__ void __launch_bounds__(kBlock) k_pcg_alpha_update(int32_t V, double* __restrict__ x, double* __restrict__ r,
+                                                             double* __restrict__ z, const double* __restrict__ p,
+                                                             const double* __restrict__ q,
+                                                             const double* __restrict__ minv,
+                                                             const double* __restrict__ pqpart, int64_t npq,
+                                                             double* __restrict__ part, PcgScalars* sc, int cur) {
+    if (sc->done) return;
+    __shared__ double lds[kBlock / 64];
+    const double pq = wg_total(pqpart, npq, lds);
+    if (!(pq > 0.0)) {
+        if (blockIdx.x == 0 && threadIdx.x == 0) {
+            sc->pq = pq;
+            sc->breakdown = 1;
+            sc->done = 1;
+        }
+        return;
+    }
+    const double al = sc->rzb[cur] / pq;
+    const int64_t i = (int64_t)blockIdx.x * kBlock + threadIdx.x;
+    double rz = 0, rr = 0;
+    if (i < V) {
+        stv(x, i, ldv(x, i) + al * ldv(p, i));
+        const d3 rv = ldv(r, i) - al * ldv(q, i);
+        const d3 zv = apply3(minv + 9 * i, rv);
+        stv(r, i, rv);
+        stv(z, i, zv);
+        rz = dot(rv, zv);
+        rr = dot(rv, rv);
+    }
+    rz = block_sum(rz, lds);
+    rr = block_sum(rr, lds);
+    if (threadIdx.x == 0) {
+        part[blockIdx.x] = rz;
+        part[gridDim.x + blockIdx.x] = rr;
+    }
+}
+
+// the end of an iteration: r.z, r.r and the stopping test (one thread)
+__device__ __forceinline__ void pcg_step(PcgScalars* sc, double RZ, double RR, double beta, int cur) {
+    sc->beta = beta;
+    sc->rz = RZ;
+    sc->rzb[cur ^ 1] = RZ;
+    sc->rr = RR;
+    sc->iters += 1;
+    sc->conv = sc->delta ? (RZ <= sc->rtol2 * sc->rz0) : (RR <= sc->rtol2 * sc->bb);
+    sc->done = sc->conv || sc->iters >= sc->maxit;
+}
+
+// beta, p = z + beta p and its FP32 copy; nb: workgroups of the update.  A
+// workgroup that finds done already set by the first one leaves its part of p
+// as it is: nothing reads p after that.
+__global__ void __launch_bounds__(kBlock) k_pcg_beta_pupdate(int64_t n, const double* __restrict__ z,
+                                                             double* __restrict__ p, float* __restrict__ p32,
+                                                             const double* __restrict__ part, int64_t nb,
+                                                             PcgScalars* sc, int cur) {
+    if (sc->done) return;
+    __shared__ double lds[kBlock / 64];
+    const double RZ = wg_total(part, nb, lds), RR = wg_total(part + nb, nb, lds);
+    const double be = RZ / sc->rzb[cur];
+    const int64_t i = (int64_t)blockIdx.x * kBlock + threadIdx.x;
+    if (i < n) {
+        const double v = z[i] + be * p[i];
+        p[i] = v;
+        if (p32) p32[i] = (float)v;
+    }
+    if (blockIdx.x == 0 && threadIdx.x == 0) pcg_step(sc, RZ, RR, be, cur);
+}
+
+// everything between two products in one workgroup (V <= kVecRows); z stays
+// in registers
+__global__ void __launch_bounds__(kVecThreads) k_pcg_vec(int32_t V, double* __restrict__ x, double* __restrict__ r,
+                                                         double* __restrict__ p, const double* __restrict__ q,
+                                                         const double* __restrict__ minv, float* __restrict__ p32,
+                                                         PcgScalars* sc, int cur) {
+    if (sc->done) return;
+    __shared__ double lds[kVecThreads / 64], tot[3];
+    constexpr int M = kVecRows / kVecThreads;
+    double d = 0.0;
+    for (int64_t i = threadIdx.x; i < V; i += kVecThreads) d += dot(ldv(p, i), ldv(q, i));
+    d = block_sum_n<kVecThreads>(d, lds);
+    if (threadIdx.x == 0) tot[0] = d;
+    __syncthreads();
+    const double pq = tot[0];
+    if (!(pq > 0.0)) {
+        if (threadIdx.x == 0) {
+            sc->pq = pq;
+            sc->breakdown = 1;
+            sc->done = 1;
+        }
+        return;
+    }
+    const double old = sc->rzb[cur], al = old / pq;
+    d3 zv[M];
+    double rz = 0, rr = 0;
+#pragma unroll
+    for (int m = 0; m < M; ++m) {
+        const int64_t i = threadIdx.x + m * kVecThreads;
+        if (i < V) {
+            stv(x, i, ldv(x, i) + al * ldv(p, i));
+            const d3 rv = ldv(r, i) - al * ldv(q, i);
+            zv[m] = apply3(minv + 9 * i, rv);
+            stv(r, i, rv);
+            rz += dot(rv, zv[m]);
+            rr += dot(rv, rv);
+        }
+    }
+    rz = block_sum_n<kVecThreads>(rz, lds);
+    rr = block_sum_n<kVecThreads>(rr, lds);
+    if (threadIdx.x == 0) {
+        tot[1] = rz;
+        tot[2] = rr;
+    }
+    __syncthreads();
+    const double be = tot[1] / old;
+#pragma unroll
+    for (int m = 0; m < M; ++m) {
+        const int64_t i = threadIdx.x + m * kVecThreads;
+        if (i < V) {
+            const d3 pv = zv[m] + be * ldv(p, i);
+            stv(p, i, pv);
+            if (p32) {
+                p32[3 * i] = (float)pv.x;
+                p32[3 * i + 1] = (float)pv.y;
+                p32[3 * i + 2] = (float)pv.z;
+            }
+        }
+    }
+    if (threadIdx.x == 0) pcg_step(sc, tot[1], tot[2], be, cur);
+}
+
 }  // namespace
 
 // the entry-parallel product needs FP64 blocks and the pattern's row-start map
@@ -471,7 +649,7 @@ hipError_t launch_spmv(const gipc_bsr& A, const void* x, void* y, hipStream_t s)
         k_spmv_ent<<<(unsigned)spmv_ent_blocks(A.nnzb), kEntBlock, 0, s>>>(
             A.nnzb, A.row_ptr, A.col_idx, static_cast<const double*>(A.val),
             reinterpret_cast<const unsigned long long*>(A.wave_head), A.wave_row, static_cast<const double*>(x),
-            static_cast<double*>(y), nullptr);
+            static_cast<double*>(y), nullptr, 0);
         return hipGetLastError();
     }
     const int64_t threads = (int64_t)A.nbrows * kG;
@@ -604,6 +782,7 @@ static hipError_t pcg_exec(const gipc_bsr& A, const double* b, double* x, double
     const bool ent = !mf && spmv_by_entry(A);       // entry-parallel FP64 product
     const int64_t nbs = mf ? mf_num_parts(V) : nbv;  // p.q partials
     const unsigned nbrow = (unsigned)(((int64_t)V * kG + kBlock - 1) / kBlock);  // kG lanes per row
+    const unsigned nbj = (unsigned)(((int64_t)V * kBjLanes + kBlock - 1) / kBlock);
     hipError_t e;
 #define GIPC_TRY(x)                            \
     do {                                       \
@@ -616,19 +795,23 @@ static hipError_t pcg_exec(const gipc_bsr& A, const double* b, double* x, double
     PcgScalars* sc = w.sc;
     const unsigned nbn = (unsigned)((n3 + kBlock - 1) / kBlock);
 
+    // partials of p.q apart from those of r.z and r.r (over b.b, which is read once)
+    double* pqpart = part + 2 * pcg_num_parts(A, mf);
+    const bool tiny = V <= kVecRows, merged = nbv <= kMergeParts;
+
     k_pcg_reset<<<1, 64, 0, s>>>(sc);
     // r = b - A x0 (for FP32 matrices through an FP32 copy of x0)
     if (mf) {
         GIPC_TRY(launch_mf_diag_inverse(*mf, minv, s));
         GIPC_TRY(launch_mf_apply(*mf, x, q, nullptr, nullptr, s));
     } else if (f32) {
-        k_bj_inverse<float><<<(unsigned)nbv, kBlock, 0, s>>>(V, A.row_ptr, A.col_idx,
+        k_bj_inverse<float><<<nbj, kBlock, 0, s>>>(V, A.row_ptr, A.col_idx,
                                                              static_cast<const float*>(A.val), A.nnzb, minv);
         k_pupdate<<<nbn, kBlock, 0, s>>>(n3, nullptr, x, p32, sc, 1);  // FP32 copy of x0 in p32
         k_pcg_spmv<float><<<nbrow, kBlock, 0, s>>>(V, A.row_ptr, A.col_idx, static_cast<const float*>(A.val),
                                                    A.nnzb, p32, q, sc);
     } else {
-        k_bj_inverse<double><<<(unsigned)nbv, kBlock, 0, s>>>(V, A.row_ptr, A.col_idx,
+        k_bj_inverse<double><<<nbj, kBlock, 0, s>>>(V, A.row_ptr, A.col_idx,
                                                               static_cast<const double*>(A.val), A.nnzb, minv);
         GIPC_TRY(launch_spmv(A, x, q, s));
     }
@@ -648,7 +831,7 @@ static hipError_t pcg_exec(const gipc_bsr& A, const double* b, double* x, double
         int32_t m = maxit - launched < chunk ? maxit - launched : chunk;
         for (int32_t it = 0; it < m; ++it) {
             if (mf) {
-                GIPC_TRY(launch_mf_apply(*mf, p, q, part, sc, s));
+                GIPC_TRY(launch_mf_apply(*mf, p, q, pqpart, sc, s));
             } else {
                 if (f32)
                     k_pcg_spmv<float><<<nbrow, kBlock, 0, s>>>(V, A.row_ptr, A.col_idx,
@@ -656,16 +839,25 @@ static hipError_t pcg_exec(const gipc_bsr& A, const double* b, double* x, double
                 else if (ent)
                     k_spmv_ent<<<(unsigned)spmv_ent_blocks(A.nnzb), kEntBlock, 0, s>>>(
                         A.nnzb, A.row_ptr, A.col_idx, static_cast<const double*>(A.val),
-                        reinterpret_cast<const unsigned long long*>(A.wave_head), A.wave_row, p, q, sc);
+                        reinterpret_cast<const unsigned long long*>(A.wave_head), A.wave_row, p, q, sc,
+                        (launched + it) & 1);
                 else
                     k_pcg_spmv<double><<<nbrow, kBlock, 0, s>>>(V, A.row_ptr, A.col_idx,
                                                                 static_cast<const double*>(A.val), A.nnzb, p, q, sc);
-                k_pcg_pq<<<(unsigned)nbv, kBlock, 0, s>>>(V, p, q, part, sc);
+                if (!tiny) k_pcg_pq<<<(unsigned)nbv, kBlock, 0, s>>>(V, p, q, pqpart, sc);
             }
-            k_pcg_alpha<<<1, kRed, 0, s>>>(part, nbs, sc);
-            k_pcg_update<<<(unsigned)nbv, kBlock, 0, s>>>(0, V, b, x, r, z, p, q, minv, part, sc);
-            k_pcg_beta<<<1, kRed, 0, s>>>(0, part, nbv, sc, 0.0, 0, 0);
-            k_pupdate<<<nbn, kBlock, 0, s>>>(n3, z, p, p32, sc, 0);
+            const int cur = (launched + it) & 1;
+            if (tiny) {
+                k_pcg_vec<<<1, kVecThreads, 0, s>>>(V, x, r, p, q, minv, p32, sc, cur);
+            } else if (merged) {
+                k_pcg_alpha_update<<<(unsigned)nbv, kBlock, 0, s>>>(V, x, r, z, p, q, minv, pqpart, nbs, part, sc, cur);
+                k_pcg_beta_pupdate<<<nbn, kBlock, 0, s>>>(n3, z, p, p32, part, nbv, sc, cur);
+            } else {
+                k_pcg_alpha<<<1, kRed, 0, s>>>(pqpart, nbs, sc);
+                k_pcg_update<<<(unsigned)nbv, kBlock, 0, s>>>(0, V, b, x, r, z, p, q, minv, part, sc);
+                k_pcg_beta<<<1, kRed, 0, s>>>(0, part, nbv, sc, 0.0, 0, 0);
+                k_pupdate<<<nbn, kBlock, 0, s>>>(n3, z, p, p32, sc, 0);
+            }
         }
         GIPC_TRY(hipGetLastError());
         launched += m;
