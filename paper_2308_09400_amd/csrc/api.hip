@@ -247,7 +247,7 @@ namespace {
 // every device buffer the context holds
 std::vector<DevBuf*> ctx_buffers(gipc_ctx* ctx) {
     return {&ctx->cand_ft, &ctx->cand_vid, &ctx->bcount, &ctx->boff, &ctx->counters, &ctx->st_vid,
-                      &ctx->st_src, &ctx->mult, &ctx->mkeys, &ctx->mrep_of, &ctx->mcount,
+                      &ctx->st_src, &ctx->mult, &ctx->mkeys, &ctx->mslots, &ctx->mrep_of, &ctx->mcount,
                       &ctx->mbcount, &ctx->mpos, &ctx->st_vid2, &ctx->st_src2, &ctx->deg, &ctx->kcount, &ctx->fill, &ctx->inc_ptr, &ctx->kptr,
                       &ctx->contrib, &ctx->kcol, &ctx->kbeg, &ctx->ncols, &ctx->row_ptr, &ctx->col_idx, &ctx->cptr,
                       &ctx->slot_row, &ctx->diag_slot, &ctx->whead, &ctx->wrow, &ctx->maxbuf, &ctx->bigrows, &ctx->tslot, &ctx->incr, &ctx->order,
@@ -386,16 +386,18 @@ gipc_status gipc_pairs_build(gipc_ctx* ctx, const gipc_mesh* mesh, const gipc_pa
     const size_t Vs = (size_t)(V > 0 ? V : 1);
     CK(ensure(ctx->deg, sizeof(int32_t) * Vs), "alloc pattern");
     CK(ensure(ctx->kcount, sizeof(int32_t) * Vs), "alloc pattern");
-    CK(ensure(ctx->fill, sizeof(int32_t) * Vs), "alloc pattern");
+    CK(ensure(ctx->fill, sizeof(uint64_t) * Vs), "alloc pattern");
+    CK(ensure(ctx->st_vid2, sizeof(int4) * (size_t)(Ps > 0 ? Ps : 1)), "alloc pattern");  // places (free here)
     CK(ensure(ctx->inc_ptr, sizeof(int64_t) * (Vs + 1)), "alloc pattern");
     CK(ensure(ctx->kptr, sizeof(int64_t) * (Vs + 1)), "alloc pattern");
     CK(ensure(ctx->ncols, sizeof(int32_t) * Vs), "alloc pattern");
     CK(ensure(ctx->row_ptr, sizeof(int32_t) * (Vs + 1)), "alloc pattern");
     CK(ensure(ctx->diag_slot, sizeof(int32_t) * Vs), "alloc pattern");
-    CK(zero_i32(as<int32_t>(ctx->deg), as<int32_t>(ctx->kcount), as<int32_t>(ctx->fill), (int64_t)Vs, s),
-       "clear pattern");
-    CK(launch_sym_count(as<int4>(ctx->st_vid), tr, as<int32_t>(ctx->deg), as<int32_t>(ctx->kcount), s), "count");
-    CK(reduce_max_i32(as<int32_t>(ctx->deg), V, reinterpret_cast<int32_t*>(cnt + C_MAXDEG), s), "max degree");
+    CK(zero_i32(as<int32_t>(ctx->fill), nullptr, nullptr, 2 * (int64_t)Vs, s), "clear pattern");
+    CK(launch_sym_count(as<int4>(ctx->st_vid), tr, V, as<unsigned long long>(ctx->fill), as<int4>(ctx->st_vid2),
+                        as<int32_t>(ctx->deg), as<int32_t>(ctx->kcount), reinterpret_cast<int32_t*>(cnt + C_MAXDEG),
+                        s),
+       "count");
     CK((exclusive_scan<int32_t, int64_t>(as<int32_t>(ctx->deg), V, as<int64_t>(ctx->inc_ptr), ctx, s, cnt + C_INC)),
        "incidence scan");
     CK((exclusive_scan<int32_t, int64_t>(as<int32_t>(ctx->kcount), V, as<int64_t>(ctx->kptr), ctx, s, cnt + C_K)),
@@ -410,7 +412,7 @@ gipc_status gipc_pairs_build(gipc_ctx* ctx, const gipc_mesh* mesh, const gipc_pa
     CK(ensure(ctx->contrib, sizeof(uint32_t) * (size_t)K), "alloc contributions");
     CK(ensure(ctx->kcol, sizeof(int32_t) * (size_t)K), "alloc contributions");
     CK(ensure(ctx->kbeg, sizeof(int32_t) * (size_t)K), "alloc contributions");
-    CK(launch_sym_scatter(as<int4>(ctx->st_vid), tr, as<int64_t>(ctx->inc_ptr), as<int32_t>(ctx->fill),
+    CK(launch_sym_scatter(as<int4>(ctx->st_vid), tr, as<int64_t>(ctx->inc_ptr), as<int4>(ctx->st_vid2),
                           as<int4>(ctx->incr), s),
        "incidence scatter");
     CK(ensure(ctx->bigrows, sizeof(int32_t) * Vs), "alloc pattern");

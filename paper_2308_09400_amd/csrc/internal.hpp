@@ -60,6 +60,62 @@ __device__ __forceinline__ int vslot(const int4& v, int j) {
     return j == 0 ? v.x : (j == 1 ? v.y : (j == 2 ? v.z : v.w));
 }
 
+// Groups of equal keys among the lanes of a wavefront, wherever they sit: a
+// group's leader is its lowest lane, rank numbers its lanes from 0 (in no
+// particular order), count is its size.  One atomic per group then replaces
+// one per lane.  Each round the open lanes meet in an LDS table of 128 slots
+// at the hash of their key, where the lowest lane wins; lanes with the
+// winner's key are done, the others meet again under another hash.  With some
+// 25 distinct keys in a wavefront that is about two rounds of 25
+// instructions, where one round per distinct key took 25 rounds of 15.
+// tab: 128 words of LDS of this wavefront alone.
+__device__ __forceinline__ void wave_lds_fence() {
+    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+    __builtin_amdgcn_wave_barrier();
+    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+}
+
+constexpr int kGroupSlots = 128;
+
+struct WaveGroup {
+    int leader, rank, count;  // leader -1 for lanes not in
+};
+
+template <int N>
+__device__ __forceinline__ WaveGroup wave_group(const int (&key)[N], bool in, uint32_t* tab) {
+    const int lane = threadIdx.x & 63;
+    WaveGroup g{-1, 0, 0};
+    uint32_t h = 0u;
+#pragma unroll
+    for (int n = 0; n < N; ++n) h = (h ^ (uint32_t)key[n]) * 0x9e3779b1u;
+    h ^= h >> 15;
+    bool open = in;
+    while (__ballot(open) != 0ull) {
+        tab[lane] = ~0u;
+        tab[lane + 64] = ~0u;
+        wave_lds_fence();
+        if (open) atomicMin(&tab[h % kGroupSlots], (uint32_t)lane);
+        wave_lds_fence();
+        const int w = open ? (int)tab[h % kGroupSlots] : lane;
+        bool same = open;
+#pragma unroll
+        for (int n = 0; n < N; ++n) same = __shfl(key[n], w, 64) == key[n] && same;
+        if (same) {
+            g.leader = w;
+            open = false;
+        }
+        h = (h >> 7) * 0x85ebca6bu + 1u;
+        wave_lds_fence();
+    }
+    tab[lane] = 0u;
+    wave_lds_fence();
+    if (in) g.rank = (int)atomicAdd(&tab[g.leader], 1u);
+    wave_lds_fence();
+    if (in) g.count = (int)tab[g.leader];
+    wave_lds_fence();
+    return g;
+}
+
 // One tuple in the paper's sign encoding (Sec. 7.2, "Data structures"),
 // negative ids as -(i+1), decoded with ~i:
 //   [a0, a1, b0, b1]            edge-edge (a1 negative: close to parallel)
@@ -151,7 +207,7 @@ struct gipc_ctx {
     gipc::DevBuf st_vid, st_src, mult;
     bool merged = false;
     // merge scratch
-    gipc::DevBuf mkeys, mrep_of, mcount, mbcount, mpos, st_vid2, st_src2;
+    gipc::DevBuf mkeys, mslots, mrep_of, mcount, mbcount, mpos, st_vid2, st_src2;
     gipc::TypeRanges ranges{};
     int64_t Ps = 0;
     int32_t V = 0;
@@ -212,7 +268,6 @@ hipError_t exclusive_scan(const TIn* in, int64_t n, TOut* out, gipc_ctx* ctx, hi
                           int64_t* total_dev = nullptr);
 // zeroes a[0..n), and b and c when not null, in one launch
 hipError_t zero_i32(int32_t* a, int32_t* b, int32_t* c, int64_t n, hipStream_t s);
-hipError_t reduce_max_i32(const int32_t* in, int64_t n, int32_t* out_dev, hipStream_t s);
 
 // ---- stage.hip
 hipError_t launch_vertex_scene(const int32_t* vert_off, int32_t S, int32_t V, int32_t* vscene, hipStream_t s);
@@ -245,10 +300,14 @@ hipError_t build_row_order(gipc_ctx* ctx, const double* x, int32_t V, const int3
                            hipStream_t s);
 
 // ---- symbolic.hip
-hipError_t launch_sym_count(const int4* st_vid, TypeRanges tr, int32_t* deg, int32_t* kcount, hipStream_t s);
+// pairs touching each vertex (deg), their block contributions to its row
+// (kcount) and the largest deg (max_deg, zero on entry); both: scratch, zero
+// on entry; rank: each staged pair's place among its vertices' pairs, by slot
+hipError_t launch_sym_count(const int4* st_vid, TypeRanges tr, int32_t V, unsigned long long* both, int4* rank,
+                            int32_t* deg, int32_t* kcount, int32_t* max_deg, hipStream_t s);
 // incr: one record per incidence: k << 2 | i, then the vertices of the pair's other
 // slots in slot order (-1 past the stencil)
-hipError_t launch_sym_scatter(const int4* st_vid, TypeRanges tr, const int64_t* inc_ptr, int32_t* fill,
+hipError_t launch_sym_scatter(const int4* st_vid, TypeRanges tr, const int64_t* inc_ptr, const int4* rank,
                               int4* incr, hipStream_t s);
 // big: int32 [V] scratch for the rows sorted by whole workgroups, nbig: a
 // device counter that must be zero on entry

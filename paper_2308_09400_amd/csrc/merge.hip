@@ -14,6 +14,10 @@
 // constraints.  Counts are integer atomics and the compaction keeps the
 // staged order, so the result is deterministic.
 //
+// One lane per group of equal keys in a wavefront goes to the table.  The
+// insert keeps the slot it found for every pair and counts the group there,
+// so the second pass only reads: the slot, and the representative's key.
+//
 // Layout: one 8-byte word per slot holding a 36-bit fingerprint above the
 // 28-bit representative (staged indices are below 2^28), so a slot is
 // claimed and its representative lowered with 64-bit atomics on one word
@@ -63,155 +67,151 @@ __device__ __forceinline__ uint64_t home(const Key& k, unsigned long long f, dou
 // slower); both passes walk the same sequence, so they agree.
 constexpr int kMaxProbe = 4096;
 
-// Lanes of a wavefront carrying the same key (same kind) form a group; its
-// leader is its lowest lane, which holds the group's smallest staged index.
-// Only leaders touch the table.  The loop runs once per distinct key of the
-// wavefront (the mask of pending lanes is the same in every lane).
-struct Group {
-    int leader;                  // lane of this lane's leader (-1 if not in)
-    unsigned long long members;  // lanes of this lane's group
-};
-
-__device__ __forceinline__ Group wave_group(const Key& key, bool pp, bool in) {
-    Group g{-1, 0ull};
-    unsigned long long pending = __ballot(in);
-    while (pending) {
-        const int l = __ffsll((long long)pending) - 1;
-        const int ka = __shfl(key.a, l, 64), kb = __shfl(key.b, l, 64), kc = __shfl(key.c, l, 64);
-        const int kp = __shfl((int)pp, l, 64);
-        const bool same = in && key.a == ka && key.b == kb && key.c == kc && (int)pp == kp;
-        const unsigned long long grp = __ballot(same);
-        if (same) {
-            g.leader = l;
-            g.members = grp;
-        }
-        pending &= ~grp;
-    }
-    return g;
-}
-
-// pairs [k0, k1) are PE then PP from pp0 on
+// pairs [k0, k1) are PE then PP from pp0 on.  slot[k - k0] = the key's slot,
+// or ~leader where the probe bound was reached (the group then stands for
+// itself); own[slot] = the pairs of the group that claimed it, cnt[slot] those
+// of the others, lone those of a group without a slot, at its leader.  An
+// atomic costs some 16 cycles of an L2 channel, a load one: a slot is read
+// first, and only claiming it, lowering its representative (rare: pairs come
+// in order) and counting into another group's slot are atomics.
 __global__ void __launch_bounds__(kBlock) k_merge_insert(const int4* __restrict__ st_vid, int64_t k0, int64_t k1,
                                                          int64_t pp0, unsigned long long* __restrict__ table,
-                                                         double scale, uint64_t mask) {
+                                                         int32_t* __restrict__ cnt, int32_t* __restrict__ own,
+                                                         double scale, uint64_t mask, int32_t* __restrict__ slot,
+                                                         int32_t* __restrict__ lone) {
+    __shared__ uint32_t tab[kBlock / 64][kGroupSlots];
     const int64_t k = k0 + (int64_t)blockIdx.x * kBlock + threadIdx.x;
     const bool in = k < k1;
     const bool pp = k >= pp0;
     const Key key = in ? canon(pp, st_vid[k]) : Key{-1, -1, -1};
-    // only the leader of each group of equal keys in the wavefront inserts
-    const Group grp = wave_group(key, pp, in);
-    if (!in || grp.leader != (int)(threadIdx.x & 63)) return;
-    const unsigned long long f = fingerprint(key);
-    const unsigned long long word = f | (unsigned long long)k;
-    uint64_t h = home(key, f, scale, mask);
-    for (int t = 0; t < kMaxProbe; ++t) {
-        const unsigned long long prev = atomicCAS(&table[h], 0ull, word);
-        if (prev == 0ull) return;
-        if ((prev & ~kRepMask) == f) {
-            if (word < prev) atomicMin(&table[h], word);
-            return;
-        }
-        h = (h + 1) & mask;
-    }
-}
-
-__global__ void __launch_bounds__(kBlock) k_merge_resolve(const int4* __restrict__ st_vid, int64_t k0, int64_t k1,
-                                                          int64_t pp0, const unsigned long long* __restrict__ table,
-                                                          double scale, uint64_t mask, int32_t* __restrict__ rep_of,
-                                                          int32_t* __restrict__ mult) {
-    const int64_t k = k0 + (int64_t)blockIdx.x * kBlock + threadIdx.x;
-    const bool in = k < k1;
-    const bool pp = k >= pp0;
-    const Key me = in ? canon(pp, st_vid[k]) : Key{-1, -1, -1};
-    const Group grp = wave_group(me, pp, in);
+    // the kinds cannot meet: a PP key has c = -1
+    const int kk[3] = {key.a, key.b, key.c};
+    const WaveGroup grp = wave_group<3>(kk, in, tab[threadIdx.x >> 6]);
     const int lane = threadIdx.x & 63;
-    // the leader finds the representative of the group's key; a group whose
-    // key is in no slot (probe bound) takes its leader
-    int32_t my = (int32_t)k;
+    int32_t found = ~(int32_t)k;
     if (in && grp.leader == lane) {
-        const unsigned long long f = fingerprint(me);
-        uint64_t h = home(me, f, scale, mask);
+        const unsigned long long f = fingerprint(key);
+        const unsigned long long word = f | (unsigned long long)k;
+        uint64_t h = home(key, f, scale, mask);
         for (int t = 0; t < kMaxProbe; ++t) {
-            const unsigned long long w = table[h];
-            if ((w & ~kRepMask) == f) {
-                const int32_t r = (int32_t)(w & kRepMask);
-                if (r != (int32_t)k) {  // another pair is the representative: compare full keys
-                    const bool rpp = r >= pp0;
-                    const Key o = canon(rpp, st_vid[r]);
-                    if (rpp == pp && o.a == me.a && o.b == me.b && o.c == me.c) my = r;
+            unsigned long long prev = __hip_atomic_load(&table[h], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+            if (prev == 0ull) {
+                prev = atomicCAS(&table[h], 0ull, word);
+                if (prev == 0ull) {
+                    own[h] = grp.count;
+                    found = (int32_t)h;
+                    break;
                 }
+            }
+            if ((prev & ~kRepMask) == f) {
+                if (word < prev) atomicMin(&table[h], word);
+                atomicAdd(&cnt[h], grp.count);
+                found = (int32_t)h;
                 break;
             }
-            if (w == 0ull) break;  // not inserted (probe bound reached on insert)
             h = (h + 1) & mask;
         }
+        if (found < 0) lone[k - k0] = grp.count;
     }
-    const int32_t rep = __shfl(my, grp.leader < 0 ? lane : grp.leader, 64);
-    if (!in) return;
-    rep_of[k - k0] = rep;
-    if (grp.leader == lane) atomicAdd(&mult[rep - k0], __popcll(grp.members));
+    found = __shfl(found, grp.leader < 0 ? lane : grp.leader, 64);
+    if (in) slot[k - k0] = found;
 }
 
-// the pairs the compaction keeps: those outside [k0, k1), and inside it
-// the representatives
-__device__ __forceinline__ bool survives(int64_t k, int64_t Ps, int64_t k0, int64_t k1,
-                                         const int32_t* __restrict__ rep_of) {
-    return k < Ps && (k < k0 || k >= k1 || rep_of[k - k0] == (int32_t)k);
-}
-
-// survivors per workgroup of kBlock staged pairs
-__global__ void __launch_bounds__(kBlock) k_merge_count(int64_t Ps, int64_t k0, int64_t k1,
-                                                        const int32_t* __restrict__ rep_of,
-                                                        int32_t* __restrict__ bcnt) {
-    __shared__ int32_t cnt[kBlock / 64];
+// Staged pairs outside [k0, k1) survive with multiplicity 1.  Inside it,
+// state[k - k0] (over slot) = 0 for a pair that merges into its key's
+// representative, its multiplicity for one that stands for itself, and ~slot
+// for a representative, whose multiplicity is own + cnt of the slot.  A pair whose
+// key is not the representative's (a fingerprint collision) takes itself out
+// of that count.  Survivors are counted per workgroup of kBlock pairs.
+__global__ void __launch_bounds__(kBlock) k_merge_resolve(const int4* __restrict__ st_vid, int64_t Ps, int64_t k0,
+                                                          int64_t k1, int64_t pp0,
+                                                          const unsigned long long* __restrict__ table,
+                                                          int32_t* __restrict__ cnt, int32_t* __restrict__ state,
+                                                          const int32_t* __restrict__ lone,
+                                                          int32_t* __restrict__ bcnt) {
+    __shared__ int32_t wcnt[kBlock / 64];
     const int64_t k = (int64_t)blockIdx.x * kBlock + threadIdx.x;
-    const unsigned long long m = __ballot(survives(k, Ps, k0, k1, rep_of));
-    if ((threadIdx.x & 63) == 0) cnt[threadIdx.x >> 6] = __popcll(m);
+    bool keep = k < Ps;
+    if (k >= k0 && k < k1) {
+        const int32_t s = state[k - k0];
+        int32_t m = 0;
+        if (s >= 0) {
+            const int32_t r = (int32_t)(table[s] & kRepMask);
+            if (r == (int32_t)k) {
+                m = ~s;
+            } else {
+                const bool pp = k >= pp0, rpp = r >= pp0;
+                const Key me = canon(pp, st_vid[k]), o = canon(rpp, st_vid[r]);
+                if (!(rpp == pp && o.a == me.a && o.b == me.b && o.c == me.c)) {
+                    atomicAdd(&cnt[s], -1);
+                    m = 1;
+                }
+            }
+        } else if (~s == (int32_t)k) {
+            m = lone[k - k0];
+        }
+        state[k - k0] = m;
+        keep = m != 0;
+    }
+    const unsigned long long b = __ballot(keep);
+    if ((threadIdx.x & 63) == 0) wcnt[threadIdx.x >> 6] = __popcll(b);
     __syncthreads();
     if (threadIdx.x == 0) {
         int32_t c = 0;
-        for (int w = 0; w < kBlock / 64; ++w) c += cnt[w];
+        for (int w = 0; w < kBlock / 64; ++w) c += wcnt[w];
         bcnt[blockIdx.x] = c;
     }
+}
+
+// the pairs the compaction keeps
+__device__ __forceinline__ bool survives(int64_t k, int64_t Ps, int64_t k0, int64_t k1,
+                                         const int32_t* __restrict__ state) {
+    return k < Ps && (k < k0 || k >= k1 || state[k - k0] != 0);
 }
 
 // stable compaction: a survivor's position is its workgroup's offset plus
 // the survivors before it in the workgroup
 __global__ void __launch_bounds__(kBlock) k_merge_scatter(int64_t Ps, int64_t k0, int64_t k1,
-                                                          const int32_t* __restrict__ rep_of,
+                                                          const int32_t* __restrict__ state,
+                                                          const int32_t* __restrict__ cnt_in,
+                                                          const int32_t* __restrict__ own,
                                                           const int64_t* __restrict__ boff,
                                                           const int4* __restrict__ st_vid,
                                                           const int32_t* __restrict__ st_src,
-                                                          const int32_t* __restrict__ mult_in,
                                                           int4* __restrict__ vid_out, int32_t* __restrict__ src_out,
                                                           int32_t* __restrict__ mult_out) {
     __shared__ int32_t cnt[kBlock / 64];
     const int64_t k = (int64_t)blockIdx.x * kBlock + threadIdx.x;
     const int wid = threadIdx.x >> 6;
-    const bool f = survives(k, Ps, k0, k1, rep_of);
+    const bool f = survives(k, Ps, k0, k1, state);
     const unsigned long long m = __ballot(f);
     if ((threadIdx.x & 63) == 0) cnt[wid] = __popcll(m);
     __syncthreads();
     if (!f) return;
     int64_t n = boff[blockIdx.x];
-    for (int w = 0; w < wid; ++w) n += cnt[w];
+    for (int v = 0; v < wid; ++v) n += cnt[v];
     n += __popcll(m & __lanemask_lt());
     vid_out[n] = st_vid[k];
     src_out[n] = st_src[k];
-    mult_out[n] = (k >= k0 && k < k1) ? mult_in[k - k0] : 1;
+    int32_t w = 1;
+    if (k >= k0 && k < k1) {
+        w = state[k - k0];
+        if (w < 0) w = own[~w] + cnt_in[~w];
+    }
+    mult_out[n] = w;
 }
 
 // merged type offsets, one workgroup per t = 0..8: out[t] = the survivors
 // before tr.off[t]
 __global__ void __launch_bounds__(kBlock) k_merge_offsets(int64_t Ps, int64_t k0, int64_t k1,
-                                                          const int32_t* __restrict__ rep_of,
+                                                          const int32_t* __restrict__ state,
                                                           const int64_t* __restrict__ boff, TypeRanges tr,
                                                           int64_t* __restrict__ out) {
     __shared__ int32_t cnt[kBlock / 64];
     const int64_t o = tr.off[blockIdx.x];
     const int64_t b = o / kBlock;
     const int64_t k = b * kBlock + threadIdx.x;
-    const unsigned long long m = __ballot(k < o && survives(k, Ps, k0, k1, rep_of));
+    const unsigned long long m = __ballot(k < o && survives(k, Ps, k0, k1, state));
     if ((threadIdx.x & 63) == 0) cnt[threadIdx.x >> 6] = __popcll(m);
     __syncthreads();
     if (threadIdx.x == 0) {
@@ -247,31 +247,32 @@ hipError_t merge_duplicates(gipc_ctx* ctx, int32_t V, hipStream_t s, int64_t* ne
     TRY(ensure(ctx->st_vid2, sizeof(int4) * (size_t)(Ps > 0 ? Ps : 1)));
     TRY(ensure(ctx->st_src2, sizeof(int32_t) * (size_t)(Ps > 0 ? Ps : 1)));
     TRY(ensure(ctx->mult, sizeof(int32_t) * (size_t)(Ps > 0 ? Ps : 1)));
+    TRY(ensure(ctx->mslots, sizeof(int32_t) * 2 * H));
+    int32_t *state = as<int32_t>(ctx->mrep_of), *count = as<int32_t>(ctx->mslots), *lone = as<int32_t>(ctx->mcount);
+    int32_t* own = count + H;
+    const unsigned long long* table = as<unsigned long long>(ctx->mkeys);
     if (n > 0) {
-        TRY(hipMemsetAsync(ctx->mkeys.p, 0, sizeof(unsigned long long) * H, s));
-        TRY(hipMemsetAsync(ctx->mcount.p, 0, sizeof(int32_t) * n, s));
+        TRY(zero_i32(as<int32_t>(ctx->mkeys), nullptr, nullptr, 2 * (int64_t)H, s));
+        TRY(zero_i32(count, nullptr, nullptr, (int64_t)H, s));
         k_merge_insert<<<grid(n), kBlock, 0, s>>>(as<int4>(ctx->st_vid), k0, k1, pp0,
-                                                  as<unsigned long long>(ctx->mkeys), scale, H - 1);
-        TRY(hipGetLastError());
-        k_merge_resolve<<<grid(n), kBlock, 0, s>>>(as<int4>(ctx->st_vid), k0, k1, pp0,
-                                                   as<unsigned long long>(ctx->mkeys), scale, H - 1,
-                                                   as<int32_t>(ctx->mrep_of), as<int32_t>(ctx->mcount));
+                                                  as<unsigned long long>(ctx->mkeys), count, own, scale, H - 1,
+                                                  state, lone);
         TRY(hipGetLastError());
     }
-    const int32_t* rep = as<int32_t>(ctx->mrep_of);
     if (Ps > 0) {
-        k_merge_count<<<(unsigned)nbk, kBlock, 0, s>>>(Ps, k0, k1, rep, as<int32_t>(ctx->mbcount));
+        k_merge_resolve<<<(unsigned)nbk, kBlock, 0, s>>>(as<int4>(ctx->st_vid), Ps, k0, k1, pp0, table, count, state,
+                                                         lone, as<int32_t>(ctx->mbcount));
         TRY(hipGetLastError());
     }
     TRY((exclusive_scan<int32_t, int64_t>(as<int32_t>(ctx->mbcount), nbk, as<int64_t>(ctx->mpos), ctx, s)));
     if (Ps > 0) {
-        k_merge_scatter<<<(unsigned)nbk, kBlock, 0, s>>>(Ps, k0, k1, rep, as<int64_t>(ctx->mpos),
+        k_merge_scatter<<<(unsigned)nbk, kBlock, 0, s>>>(Ps, k0, k1, state, count, own, as<int64_t>(ctx->mpos),
                                                          as<int4>(ctx->st_vid), as<int32_t>(ctx->st_src),
-                                                         as<int32_t>(ctx->mcount), as<int4>(ctx->st_vid2),
-                                                         as<int32_t>(ctx->st_src2), as<int32_t>(ctx->mult));
+                                                         as<int4>(ctx->st_vid2), as<int32_t>(ctx->st_src2),
+                                                         as<int32_t>(ctx->mult));
         TRY(hipGetLastError());
     }
-    k_merge_offsets<<<9, kBlock, 0, s>>>(Ps, k0, k1, rep, as<int64_t>(ctx->mpos), tr, new_off_dev);
+    k_merge_offsets<<<9, kBlock, 0, s>>>(Ps, k0, k1, state, as<int64_t>(ctx->mpos), tr, new_off_dev);
     TRY(hipGetLastError());
 #undef TRY
     std::swap(ctx->st_vid, ctx->st_vid2);

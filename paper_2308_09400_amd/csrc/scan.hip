@@ -1,5 +1,5 @@
 // Device-wide exclusive scan (three passes: block sums, scan of the block
-// sums in one workgroup, block-local scans plus carry) and an integer max.
+// sums in one workgroup, block-local scans plus carry).
 // Integer arithmetic only, so the results are deterministic.
 #include "internal.hpp"
 
@@ -106,21 +106,6 @@ __global__ void __launch_bounds__(kBlock) k_scan_final(const TIn* __restrict__ i
     }
 }
 
-__global__ void __launch_bounds__(kBlock) k_max_i32(const int32_t* __restrict__ in, int64_t n, int32_t* out) {
-    __shared__ int32_t lds[kBlock / 64];
-    int32_t m = 0;
-    for (int64_t i = (int64_t)blockIdx.x * kBlock + threadIdx.x; i < n; i += (int64_t)gridDim.x * kBlock)
-        m = max(m, in[i]);
-#pragma unroll
-    for (int o = 32; o > 0; o >>= 1) m = max(m, __shfl_xor(m, o, 64));
-    if ((threadIdx.x & 63) == 0) lds[threadIdx.x >> 6] = m;
-    __syncthreads();
-    if (threadIdx.x == 0) {
-        for (int w = 1; w < kBlock / 64; ++w) m = max(m, lds[w]);
-        atomicMax(out, m);
-    }
-}
-
 }  // namespace
 
 template <typename TIn, typename TOut>
@@ -162,18 +147,6 @@ __global__ void __launch_bounds__(kBlock) k_zero_i32(int32_t* __restrict__ a, in
 hipError_t zero_i32(int32_t* a, int32_t* b, int32_t* c, int64_t n, hipStream_t s) {
     if (n <= 0) return hipSuccess;
     k_zero_i32<<<(unsigned)((n + kBlock - 1) / kBlock), kBlock, 0, s>>>(a, b, c, n);
-    return hipGetLastError();
-}
-
-hipError_t reduce_max_i32(const int32_t* in, int64_t n, int32_t* out_dev, hipStream_t s) {
-    hipError_t e = hipMemsetAsync(out_dev, 0, sizeof(int32_t), s);
-    if (e != hipSuccess) return e;
-    if (n <= 0) return hipSuccess;
-    // one atomic per workgroup on the same word: few workgroups, each
-    // striding over many elements
-    int64_t blocks = (n + kBlock - 1) / kBlock;
-    if (blocks > 256) blocks = 256;
-    k_max_i32<<<(unsigned)blocks, kBlock, 0, s>>>(in, n, out_dev);
     return hipGetLastError();
 }
 

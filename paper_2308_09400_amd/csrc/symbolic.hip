@@ -23,49 +23,54 @@
 namespace gipc {
 namespace {
 
-// Lanes of the wavefront with equal keys (key, key2) form a group led by its
-// lowest lane, wherever they sit in the wavefront: one atomic per group
-// instead of one per lane.  The loop runs once per distinct key (the
-// pending mask is the same in every lane).
-struct WaveGroup {
-    int leader;                  // -1 for lanes not in
-    unsigned long long members;  // the group's lanes
-};
-
-__device__ __forceinline__ WaveGroup wave_group(int key, int key2, bool in) {
-    WaveGroup g{-1, 0ull};
-    unsigned long long pending = __ballot(in);
-    while (pending) {
-        const int l = __ffsll((long long)pending) - 1;
-        const int a = __shfl(key, l, 64), b = __shfl(key2, l, 64);
-        const bool same = in && key == a && key2 == b;
-        const unsigned long long grp = __ballot(same);
-        if (same) {
-            g.leader = l;
-            g.members = grp;
-        }
-        pending &= ~grp;
-    }
-    return g;
-}
-
+// Degrees (low half of both) and block contributions (high half) of the
+// vertices, and every pair's place among its vertices' pairs, which is the
+// value an atomic returns plus the rank in the wavefront's group: the scatter
+// needs no atomics of its own.
 __global__ void __launch_bounds__(kBlock) k_sym_count(const int4* __restrict__ st_vid, TypeRanges tr,
-                                                      int32_t* __restrict__ deg, int32_t* __restrict__ kcount) {
+                                                      unsigned long long* __restrict__ both,
+                                                      int4* __restrict__ rank) {
+    __shared__ uint32_t tab[kBlock / 64][kGroupSlots];
     const int64_t k = (int64_t)blockIdx.x * kBlock + threadIdx.x;
     const bool in = k < tr.off[8];
     const int nv = in ? ft_nverts(type_of(k, tr)) : 0;
     const int4 v = in ? st_vid[k] : make_int4(-1, -1, -1, -1);
     const int lane = threadIdx.x & 63;
+    int at[4] = {0, 0, 0, 0};
 #pragma unroll
     for (int i = 0; i < 4; ++i) {
         const int vi = vslot(v, i);
         const bool valid = i < nv;
-        const WaveGroup g = wave_group(valid ? vi : -1, nv, valid);
-        if (valid && g.leader == lane) {
-            const int n = __popcll(g.members);
-            atomicAdd(&deg[vi], n);
-            atomicAdd(&kcount[vi], n * nv);
-        }
+        const int key[2] = {vi, nv};
+        const WaveGroup g = wave_group<2>(key, valid, tab[threadIdx.x >> 6]);
+        int base = 0;
+        if (valid && g.leader == lane)
+            base = (int)atomicAdd(&both[vi], (unsigned long long)g.count | ((unsigned long long)(g.count * nv) << 32));
+        at[i] = __shfl(base, valid ? g.leader : lane, 64) + g.rank;
+    }
+    if (in) rank[k] = make_int4(at[0], at[1], at[2], at[3]);
+}
+
+// both taken apart, and the largest degree
+__global__ void __launch_bounds__(kBlock) k_sym_degrees(int32_t V, const unsigned long long* __restrict__ both,
+                                                        int32_t* __restrict__ deg, int32_t* __restrict__ kcount,
+                                                        int32_t* __restrict__ max_deg) {
+    __shared__ int32_t lds[kBlock / 64];
+    int32_t m = 0;
+    for (int64_t i = (int64_t)blockIdx.x * kBlock + threadIdx.x; i < V; i += (int64_t)gridDim.x * kBlock) {
+        const unsigned long long w = both[i];
+        const int32_t d = (int32_t)(w & 0xffffffffull);
+        deg[i] = d;
+        kcount[i] = (int32_t)(w >> 32);
+        m = max(m, d);
+    }
+#pragma unroll
+    for (int o = 32; o > 0; o >>= 1) m = max(m, __shfl_xor(m, o, 64));
+    if ((threadIdx.x & 63) == 0) lds[threadIdx.x >> 6] = m;
+    __syncthreads();
+    if (threadIdx.x == 0) {
+        for (int w = 1; w < kBlock / 64; ++w) m = max(m, lds[w]);
+        atomicMax(max_deg, m);
     }
 }
 
@@ -73,31 +78,22 @@ __global__ void __launch_bounds__(kBlock) k_sym_count(const int4* __restrict__ s
 // streams one record per incidence instead of gathering the staged list
 __global__ void __launch_bounds__(kBlock) k_sym_scatter(const int4* __restrict__ st_vid, TypeRanges tr,
                                                         const int64_t* __restrict__ inc_ptr,
-                                                        int32_t* __restrict__ fill, int4* __restrict__ incr) {
+                                                        const int4* __restrict__ rank, int4* __restrict__ incr) {
     const int64_t k = (int64_t)blockIdx.x * kBlock + threadIdx.x;
-    const bool in = k < tr.off[8];
-    const int nv = in ? ft_nverts(type_of(k, tr)) : 0;
-    const int4 v = in ? st_vid[k] : make_int4(-1, -1, -1, -1);
-    const int lane = threadIdx.x & 63;
+    if (k >= tr.off[8]) return;
+    const int nv = ft_nverts(type_of(k, tr));
+    const int4 v = st_vid[k], at = rank[k];
 #pragma unroll
     for (int i = 0; i < 4; ++i) {
-        const int vi = vslot(v, i);
-        const bool valid = i < nv;
-        const WaveGroup g = wave_group(valid ? vi : -1, 0, valid);
-        int base = 0;
-        if (valid && g.leader == lane) base = atomicAdd(&fill[vi], __popcll(g.members));
-        base = __shfl(base, valid ? g.leader : lane, 64);
-        if (valid) {
-            const unsigned long long below = lane == 0 ? 0ull : (~0ull >> (64 - lane));
-            const int64_t at = inc_ptr[vi] + base + __popcll(g.members & below);
-            int o[3];
+        if (i >= nv) break;
+        int o[3];
 #pragma unroll
-            for (int m = 0; m < 3; ++m) {
-                const int j = m < i ? m : m + 1;
-                o[m] = j < nv ? vslot(v, j) : -1;
-            }
-            incr[at] = make_int4((int)(((uint32_t)k << 2) | (uint32_t)i), o[0], o[1], o[2]);
+        for (int m = 0; m < 3; ++m) {
+            const int j = m < i ? m : m + 1;
+            o[m] = j < nv ? vslot(v, j) : -1;
         }
+        incr[inc_ptr[vslot(v, i)] + vslot(at, i)] =
+            make_int4((int)(((uint32_t)k << 2) | (uint32_t)i), o[0], o[1], o[2]);
     }
 }
 
@@ -535,18 +531,27 @@ __global__ void __launch_bounds__(kBlock) k_sym_fill(int32_t V, const int64_t* _
 
 }  // namespace
 
-hipError_t launch_sym_count(const int4* st_vid, TypeRanges tr, int32_t* deg, int32_t* kcount, hipStream_t s) {
+hipError_t launch_sym_count(const int4* st_vid, TypeRanges tr, int32_t V, unsigned long long* both, int4* rank,
+                            int32_t* deg, int32_t* kcount, int32_t* max_deg, hipStream_t s) {
     int64_t nb = (tr.off[8] + kBlock - 1) / kBlock;
-    if (nb == 0) return hipSuccess;
-    k_sym_count<<<(unsigned)nb, kBlock, 0, s>>>(st_vid, tr, deg, kcount);
+    if (nb > 0) {
+        k_sym_count<<<(unsigned)nb, kBlock, 0, s>>>(st_vid, tr, both, rank);
+        hipError_t e = hipGetLastError();
+        if (e != hipSuccess) return e;
+    }
+    if (V <= 0) return hipSuccess;
+    // one atomic per workgroup on the same word: few workgroups, each
+    // striding over many elements
+    nb = ((int64_t)V + kBlock - 1) / kBlock;
+    k_sym_degrees<<<(unsigned)(nb < 256 ? nb : 256), kBlock, 0, s>>>(V, both, deg, kcount, max_deg);
     return hipGetLastError();
 }
 
-hipError_t launch_sym_scatter(const int4* st_vid, TypeRanges tr, const int64_t* inc_ptr, int32_t* fill,
+hipError_t launch_sym_scatter(const int4* st_vid, TypeRanges tr, const int64_t* inc_ptr, const int4* rank,
                               int4* incr, hipStream_t s) {
     int64_t nb = (tr.off[8] + kBlock - 1) / kBlock;
     if (nb == 0) return hipSuccess;
-    k_sym_scatter<<<(unsigned)nb, kBlock, 0, s>>>(st_vid, tr, inc_ptr, fill, incr);
+    k_sym_scatter<<<(unsigned)nb, kBlock, 0, s>>>(st_vid, tr, inc_ptr, rank, incr);
     return hipGetLastError();
 }
 
