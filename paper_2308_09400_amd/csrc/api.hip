@@ -317,22 +317,32 @@ gipc_status gipc_pairs_build(gipc_ctx* ctx, const gipc_mesh* mesh, const gipc_pa
             pcs.push_back(make_int2((int)v, (int)std::min<int64_t>(v + kEnergyPiece, voff[k + 1])));
     }
     po[Sc] = (int32_t)pcs.size();
-    CK(ensure(ctx->pieces, sizeof(int2) * pcs.size()), "alloc energy pieces");
-    CK(ensure(ctx->poff, sizeof(int32_t) * po.size()), "alloc energy pieces");
-    if (!pcs.empty())
-        CK(hipMemcpyAsync(ctx->pieces.p, pcs.data(), sizeof(int2) * pcs.size(), hipMemcpyHostToDevice, s),
+    // uploaded when they differ from what the buffers hold
+    const auto same = [](const std::vector<int2>& u, const std::vector<int2>& v) {
+        return u.size() == v.size() && (u.empty() || !std::memcmp(u.data(), v.data(), sizeof(int2) * u.size()));
+    };
+    if (ctx->h_poff != po || !same(ctx->h_pieces, pcs)) {
+        ctx->h_poff.clear();
+        ctx->h_pieces = std::move(pcs);
+        CK(ensure(ctx->pieces, sizeof(int2) * ctx->h_pieces.size()), "alloc energy pieces");
+        CK(ensure(ctx->poff, sizeof(int32_t) * po.size()), "alloc energy pieces");
+        if (!ctx->h_pieces.empty())
+            CK(hipMemcpyAsync(ctx->pieces.p, ctx->h_pieces.data(), sizeof(int2) * ctx->h_pieces.size(),
+                              hipMemcpyHostToDevice, s),
+               "upload energy pieces");
+        CK(hipMemcpyAsync(ctx->poff.p, po.data(), sizeof(int32_t) * po.size(), hipMemcpyHostToDevice, s),
            "upload energy pieces");
-    CK(hipMemcpyAsync(ctx->poff.p, po.data(), sizeof(int32_t) * po.size(), hipMemcpyHostToDevice, s),
-       "upload energy pieces");
+        CK(hipStreamSynchronize(s), "stream synchronize");
+        ctx->h_poff = std::move(po);
+    }
     if (batch) {
         CK(ensure(ctx->vscene, sizeof(int32_t) * (size_t)(V > 0 ? V : 1)), "alloc vertex scenes");
         CK(launch_vertex_scene(batch->vert_off, Sc, V, as<int32_t>(ctx->vscene), s), "vertex scenes");
         pm.vscene = as<int32_t>(ctx->vscene);
     }
-    CK(hipStreamSynchronize(s), "stream synchronize");  // the host tables above go out of scope
     ctx->S = Sc;
     ctx->batched = batch != nullptr;
-    ctx->npieces = (int32_t)pcs.size();
+    ctx->npieces = (int32_t)ctx->h_pieces.size();
 
     // ---- staging
     const int64_t nb = (P + kBlock - 1) / kBlock;
@@ -913,7 +923,7 @@ gipc_status gipc_candidates(gipc_ctx* ctx, const gipc_mesh* mesh, const gipc_top
     const double* x = mesh->x;
 
     // topology ids
-    CK(ensure(ctx->ccnt, sizeof(int64_t) * 2), "alloc candidates");
+    CK(ensure(ctx->ccnt, sizeof(int64_t) * 8), "alloc candidates");
     const int64_t init[2] = {0, INT64_MAX};
     CK(hipMemcpyAsync(ctx->ccnt.p, init, sizeof(init), hipMemcpyHostToDevice, s), "copy");
     CK(launch_cand_check(V, topo->vobj, topo->tris, F, topo->edges, E, as<int64_t>(ctx->ccnt), s), "topology check");
@@ -986,17 +996,19 @@ gipc_status gipc_candidates(gipc_ctx* ctx, const gipc_mesh* mesh, const gipc_top
     CK(ensure(ctx->crec_e, (size_t)kPrimRecBytes * (size_t)(E > 0 ? E : 1)), "alloc candidates");
     CK(launch_prim_records(x, topo->tris, 3, F, topo->vobj, ctx->crec_t.p, s), "triangle records");
     CK(launch_prim_records(x, topo->edges, 2, E, topo->vobj, ctx->crec_e.p, s), "edge records");
-    CK(launch_cell_count(ctx, x, topo->tris, 3, F, g, cnt4, fill4, as<int64_t>(ctx->coff_t), s), "triangle cells");
-    CK(launch_cell_count(ctx, x, topo->edges, 2, E, g, cnt4 + ncell, fill4 + ncell, as<int64_t>(ctx->coff_e), s),
+    // triangle entries, edge entries, point visits, edge visits, mask slots
+    // (2), then the candidates of either kind: the scans leave them side by side
+    int64_t* totd = as<int64_t>(ctx->ccnt);
+    CK(zero_i32(cnt4, fill4, nullptr, 4 * ncell, s), "clear");
+    CK(launch_cell_count(ctx, x, topo->tris, 3, F, g, cnt4, as<int64_t>(ctx->coff_t), totd, s), "triangle cells");
+    CK(launch_cell_count(ctx, x, topo->edges, 2, E, g, cnt4 + ncell, as<int64_t>(ctx->coff_e), totd + 1, s),
        "edge cells");
-    CK(hipMemsetAsync(cnt4 + 2 * ncell, 0, sizeof(int32_t) * 2 * (size_t)ncell, s), "clear");
-    CK(hipMemsetAsync(fill4 + 2 * ncell, 0, sizeof(int32_t) * 2 * (size_t)ncell, s), "clear");
     for (int k = 0; k < 2; ++k) {
         int32_t* span = as<int32_t>(ctx->qcnt);
         CK(launch_qcells_count(k, x, Q[k], k ? ctx->crec_e.p : nullptr, g, dhat, span, cnt4 + (2 + k) * ncell, s),
            "query cells");
         CK((exclusive_scan<int32_t, int64_t>(cnt4 + (2 + k) * ncell, ncell, as<int64_t>(*qtoff[k]), ctx, s)), "scan");
-        CK((exclusive_scan<int32_t, int64_t>(span, Q[k], as<int64_t>(*qeoff[k]), ctx, s)), "scan");
+        CK((exclusive_scan<int32_t, int64_t>(span, Q[k], as<int64_t>(*qeoff[k]), ctx, s, totd + 2 + k)), "scan");
     }
     // hit-mask slots of each kind's pairs pass, per cell
     DevBuf* boff[2] = {&ctx->boff_p, &ctx->boff_e};
@@ -1007,15 +1019,12 @@ gipc_status gipc_candidates(gipc_ctx* ctx, const gipc_mesh* mesh, const gipc_top
         CK(ensure(*boff[k], sizeof(int64_t) * (size_t)(ncell + 1)), "alloc candidates");
         CK(launch_cell_slots(k, g, as<int64_t>(*qtoff[k]), as<int64_t>(*toff[k]), as<int64_t>(ctx->bslot), s),
            "mask slots");
-        CK((exclusive_scan<int64_t, int64_t>(as<int64_t>(ctx->bslot), ncell, as<int64_t>(*boff[k]), ctx, s)), "scan");
+        CK((exclusive_scan<int64_t, int64_t>(as<int64_t>(ctx->bslot), ncell, as<int64_t>(*boff[k]), ctx, s,
+                                             totd + 4 + k)),
+           "scan");
     }
-    int64_t tot[6];  // triangle entries, edge entries, point visits, edge visits, mask slots (2)
-    CK(hipMemcpyAsync(&tot[0], as<int64_t>(ctx->coff_t) + ncell, sizeof(int64_t), hipMemcpyDeviceToHost, s), "copy");
-    CK(hipMemcpyAsync(&tot[1], as<int64_t>(ctx->coff_e) + ncell, sizeof(int64_t), hipMemcpyDeviceToHost, s), "copy");
-    CK(hipMemcpyAsync(&tot[2], as<int64_t>(ctx->qoff_p) + V, sizeof(int64_t), hipMemcpyDeviceToHost, s), "copy");
-    CK(hipMemcpyAsync(&tot[3], as<int64_t>(ctx->qoff_e) + E, sizeof(int64_t), hipMemcpyDeviceToHost, s), "copy");
-    CK(hipMemcpyAsync(&tot[4], as<int64_t>(ctx->boff_p) + ncell, sizeof(int64_t), hipMemcpyDeviceToHost, s), "copy");
-    CK(hipMemcpyAsync(&tot[5], as<int64_t>(ctx->boff_e) + ncell, sizeof(int64_t), hipMemcpyDeviceToHost, s), "copy");
+    int64_t tot[6];
+    CK(hipMemcpyAsync(tot, totd, sizeof(tot), hipMemcpyDeviceToHost, s), "copy");
     CK(hipStreamSynchronize(s), "stream synchronize");
 
     // fills, then per query and cell visited: candidate counts, offsets
@@ -1041,13 +1050,14 @@ gipc_status gipc_candidates(gipc_ctx* ctx, const gipc_mesh* mesh, const gipc_top
                              as<int64_t>(*toff[k]), as<int32_t>(*tent[k]), as<int32_t>(*ecnt[k]), nullptr,
                              as<int64_t>(*boff[k]), as<uint64_t>(*bal[k]), as<int64_t>(*evis[k]), nullptr, s),
            k ? "edge-edge count" : "point-triangle count");
-        CK((exclusive_scan<int32_t, int64_t>(as<int32_t>(*ecnt[k]), tot[2 + k], as<int64_t>(*eoff[k]), ctx, s)),
+        CK((exclusive_scan<int32_t, int64_t>(as<int32_t>(*ecnt[k]), tot[2 + k], as<int64_t>(*eoff[k]), ctx, s,
+                                             totd + 6 + k)),
            "scan");
     }
-    int64_t npt = 0, nee = 0;
-    CK(hipMemcpyAsync(&npt, as<int64_t>(ctx->eoff_p) + tot[2], sizeof(int64_t), hipMemcpyDeviceToHost, s), "copy");
-    CK(hipMemcpyAsync(&nee, as<int64_t>(ctx->eoff_e) + tot[3], sizeof(int64_t), hipMemcpyDeviceToHost, s), "copy");
+    int64_t nc[2];
+    CK(hipMemcpyAsync(nc, totd + 6, sizeof(nc), hipMemcpyDeviceToHost, s), "copy");
     CK(hipStreamSynchronize(s), "stream synchronize");
+    const int64_t npt = nc[0], nee = nc[1];
     *count = npt + nee;
     if (!tuples) return GIPC_OK;
     if (cap < *count)

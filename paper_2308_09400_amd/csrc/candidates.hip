@@ -632,18 +632,16 @@ hipError_t launch_cand_check(int32_t V, const int32_t* vobj, const int32_t* tris
 }
 
 hipError_t launch_cell_count(gipc_ctx* ctx, const double* x, const int32_t* prims, int nper, int64_t n,
-                             const CandGrid& cg, int32_t* count, int32_t* fill, int64_t* off, hipStream_t s) {
+                             const CandGrid& cg, int32_t* count, int64_t* off, int64_t* total, hipStream_t s) {
     const Grid g = to_grid(cg);
     const int64_t ncell = (int64_t)g.n[0] * g.n[1] * g.n[2];
-    hipError_t e;
-    if ((e = hipMemsetAsync(count, 0, sizeof(int32_t) * ncell, s)) != hipSuccess) return e;
-    if ((e = hipMemsetAsync(fill, 0, sizeof(int32_t) * ncell, s)) != hipSuccess) return e;
     if (n > 0) {
         if (nper == 3) k_cell_count_prims<3><<<grid1(n), kBlock, 0, s>>>(x, prims, n, g, count);
         else k_cell_count_prims<2><<<grid1(n), kBlock, 0, s>>>(x, prims, n, g, count);
-        if ((e = hipGetLastError()) != hipSuccess) return e;
+        hipError_t e = hipGetLastError();
+        if (e != hipSuccess) return e;
     }
-    return exclusive_scan<int32_t, int64_t>(count, ncell, off, ctx, s);
+    return exclusive_scan<int32_t, int64_t>(count, ncell, off, ctx, s, total);
 }
 
 hipError_t launch_cell_fill(const double* x, const int32_t* prims, int nper, int64_t n, const CandGrid& cg,

@@ -7,6 +7,7 @@
 
 #include <string>
 #include <utility>
+#include <vector>
 
 #include "../../include/gipc.h"
 #include "device_math.hpp"
@@ -224,6 +225,8 @@ struct gipc_ctx {
     // (vertex ranges of at most kEnergyPiece inside one scene) and the
     // scenes' piece offsets
     gipc::DevBuf vscene, pieces, poff;
+    std::vector<int2> h_pieces;   // the tables pieces and poff hold
+    std::vector<int32_t> h_poff;
     int32_t S = 1, npieces = 0;
     bool batched = false;
     // factors of the last eval; per-vertex energy shares and piece sums
@@ -417,11 +420,12 @@ hipError_t launch_cand_bounds(const double* x, int32_t V, const int32_t* tris, i
                               int64_t E, double* part, int32_t nb, hipStream_t s);
 hipError_t launch_cand_check(int32_t V, const int32_t* vobj, const int32_t* tris, int64_t F, const int32_t* edges,
                              int64_t E, int64_t* counters, hipStream_t s);
-// cell table of n primitives of nper vertices: counts and offsets off
+// cell table of n primitives of nper vertices: counts (zero on entry; total
+// receives their sum) and offsets off
 // [ncell+1] (off[ncell] = entries), then the entries ent [off[ncell]],
 // each cell's in increasing id (raw [off[ncell]]: unsorted, scratch)
 hipError_t launch_cell_count(gipc_ctx* ctx, const double* x, const int32_t* prims, int nper, int64_t n,
-                             const CandGrid& g, int32_t* count, int32_t* fill, int64_t* off, hipStream_t s);
+                             const CandGrid& g, int32_t* count, int64_t* off, int64_t* total, hipStream_t s);
 hipError_t launch_cell_fill(const double* x, const int32_t* prims, int nper, int64_t n, const CandGrid& g,
                             int32_t* fill, const int64_t* off, int32_t* raw, int32_t* ent, hipStream_t s);
 // 64-byte query records of n primitives (box, vertex ids, object)

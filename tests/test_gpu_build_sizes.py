@@ -1,0 +1,89 @@
+"""The pattern build at the sizes where its passes change or end raggedly.
+
+* scans: one workgroup (16384 elements), the last pass adding the block sums
+  itself (up to 1024 blocks of 2048), three passes beyond: row pointers of V
+  vertices of which a random half is paired up, against numpy, exactly;
+* merging: point-point and point-edge constraints repeated a random number of
+  times in random order and with their vertices swapped, lists that end inside
+  a wavefront, a workgroup and beyond: staged pairs, their first tuples and
+  multiplicities against numpy, exactly.
+"""
+import numpy as np
+import pytest
+
+pytestmark = pytest.mark.gpu
+
+torch = pytest.importorskip("torch")
+
+
+@pytest.fixture(scope="module")
+def gp():
+    if not torch.cuda.is_available():
+        pytest.skip("no GPU")
+    import paper_2308_09400_amd as gp
+    torch.cuda.set_device(0)
+    return gp
+
+
+def _dev(a, dt):
+    return torch.tensor(np.ascontiguousarray(a), dtype=dt, device="cuda")
+
+
+@pytest.mark.parametrize("V", [2, 2047, 2048, 2049, 16383, 16384, 16385, 2 ** 21, 2 ** 21 + 1, 2 ** 21 + 4099])
+def test_row_pointers(gp, V):
+    rng = np.random.default_rng(V)
+    n = V // 2
+    close = rng.random(n) < 0.5
+    x = np.zeros((V, 3))
+    x[:, 0] = np.arange(V) // 2 * 1.0
+    x[1:2 * n:2, 1] = np.where(close, 0.5, 2.0)
+    t = np.full((n, 4), -1, np.int32)
+    t[:, 0], t[:, 1] = -(2 * np.arange(n) + 1), 2 * np.arange(n) + 1
+    ctx = gp.Context()
+    info = gp.pairs_build(ctx, _dev(x, torch.float64), _dev(t, torch.int32), gp.params(dhat=1.0))
+    A = gp.BsrMatrix(ctx)
+    blocks = np.ones(V, np.int64)
+    blocks[:2 * n] += np.repeat(close, 2)
+    assert info["n_active"] == info["n_staged"] == int(close.sum()) and info["nnzb"] == int(blocks.sum())
+    assert info["max_row_pairs"] == int(close.any())
+    assert np.array_equal(A.row_ptr().cpu().numpy(), np.concatenate([[0], np.cumsum(blocks)]))
+    cols = np.stack([np.arange(V), np.arange(V) ^ 1], 1)
+    paired = blocks == 2
+    want = np.concatenate([np.sort(c) if p else c[:1] for c, p in zip(cols, paired)]) if V < 20000 else None
+    if want is not None:
+        assert np.array_equal(A.col_idx().cpu().numpy(), want)
+    ctx.close()
+
+
+@pytest.mark.parametrize("P", [1, 63, 64, 65, 255, 256, 257, 4000, 70001])
+def test_merged_multiplicities(gp, P):
+    rng = np.random.default_rng(P)
+    n = max(P // 6, 1)            # distinct constraints, each of its own four vertices
+    kind = rng.random(n) < 0.5    # point-edge, else point-point
+    x = np.zeros((4 * n, 3))
+    base = np.arange(n) * 10.0
+    x[0::4, 0], x[1::4, 0], x[2::4, 0] = base, np.where(kind, base - 2, base), base + 2
+    x[1::4, 1] = x[2::4, 1] = 0.5
+    c = rng.integers(0, n, P)
+    flip = rng.random(P) < 0.5
+    a, b = 4 * c + 1, 4 * c + 2
+    t = np.full((P, 4), -1, np.int64)
+    pe = kind[c]
+    t[pe, 0] = -(4 * c[pe] + 1)
+    t[pe, 1], t[pe, 2] = np.where(flip, b, a)[pe], np.where(flip, a, b)[pe]
+    pp = ~pe
+    t[pp, 0], t[pp, 1] = -(np.where(flip, a, 4 * c)[pp] + 1), np.where(flip, 4 * c, a)[pp]
+    ctx = gp.Context()
+    info = gp.pairs_build(ctx, _dev(x, torch.float64), _dev(t, torch.int32), gp.params(dhat=1.0))
+    got = gp.pair_inspect(ctx, want=("src", "mult", "type"))
+    src, mult, ty = (got[k].cpu().numpy() for k in ("src", "mult", "type"))
+    first = {}
+    for i, k in enumerate(c):
+        first.setdefault(int(k), i)
+    count = np.bincount(c, minlength=n)
+    order = sorted(first, key=lambda k: (not kind[k], first[k]))  # point-edge before point-point, tuple order
+    assert info["n_active"] == P and info["n_staged"] == len(first)
+    assert np.array_equal(src, [first[k] for k in order])
+    assert np.array_equal(mult, [count[k] for k in order])
+    assert np.array_equal(ty, [2 if kind[k] else 3 for k in order])
+    ctx.close()
