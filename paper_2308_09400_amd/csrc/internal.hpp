@@ -61,6 +61,57 @@ __device__ __forceinline__ int vslot(const int4& v, int j) {
     return j == 0 ? v.x : (j == 1 ? v.y : (j == 2 ? v.z : v.w));
 }
 
+__device__ __forceinline__ void wave_lds_fence() {
+    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+    __builtin_amdgcn_wave_barrier();
+    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+}
+
+template <int D>
+__device__ __forceinline__ double quad_xor(double v) {  // the value of lane ^ D, D = 1 or 2
+    constexpr int ctrl = D == 1 ? 0xB1 : 0x4E;           // quad_perm [1,0,3,2], [2,3,0,1]
+    const long long b = __double_as_longlong(v);
+    const int lo = __builtin_amdgcn_mov_dpp((int)b, ctrl, 0xF, 0xF, false);
+    const int hi = __builtin_amdgcn_mov_dpp((int)(b >> 32), ctrl, 0xF, 0xF, false);
+    return __longlong_as_double(((long long)hi << 32) | (long long)(unsigned)lo);
+}
+
+template <int D>
+__device__ __forceinline__ void quad_swap(double2& a, double2& b, bool odd) {
+    const double2 s = odd ? a : b;
+    const double2 r = make_double2(quad_xor<D>(s.x), quad_xor<D>(s.y));
+    if (odd) a = r;
+    else b = r;
+}
+
+// element t of lane p becomes element p of lane t
+__device__ __forceinline__ void quad_transpose(double2 (&v)[4]) {
+    const bool p1 = threadIdx.x & 1, p2 = threadIdx.x & 2;
+    quad_swap<1>(v[0], v[1], p1);
+    quad_swap<1>(v[2], v[3], p1);
+    quad_swap<2>(v[0], v[2], p2);
+    quad_swap<2>(v[1], v[3], p2);
+}
+
+template <int T>
+__device__ __forceinline__ uint32_t quad_lane(uint32_t v) {  // the value of the quad's lane T
+    return (uint32_t)__builtin_amdgcn_mov_dpp((int)v, 0x55 * T, 0xF, 0xF, false);
+}
+
+// Writes 64-byte records, one per lane, a quad of lanes at a time: after a
+// transpose within the quad each of four steps writes one record whole, 16
+// bytes per lane, so an instruction touches 16 lines and not 64.  All four
+// lanes of a quad must be active; record ~0u: none.  Loading records the same
+// way did not pay (ten 256 x 256 sheets: both assembly passes within 5%).
+__device__ __forceinline__ void quad_store(double* __restrict__ base, uint32_t rec, double2 (&v)[4]) {
+    double2* b = reinterpret_cast<double2*>(base) + (threadIdx.x & 3);
+    const uint32_t k[4] = {quad_lane<0>(rec), quad_lane<1>(rec), quad_lane<2>(rec), quad_lane<3>(rec)};
+    quad_transpose(v);
+#pragma unroll
+    for (int t = 0; t < 4; ++t)
+        if (k[t] != ~0u) b[4 * (int64_t)k[t]] = v[t];
+}
+
 // Groups of equal keys among the lanes of a wavefront, wherever they sit: a
 // group's leader is its lowest lane, rank numbers its lanes from 0 (in no
 // particular order), count is its size.  One atomic per group then replaces
@@ -70,12 +121,6 @@ __device__ __forceinline__ int vslot(const int4& v, int j) {
 // 25 distinct keys in a wavefront that is about two rounds of 25
 // instructions, where one round per distinct key took 25 rounds of 15.
 // tab: 128 words of LDS of this wavefront alone.
-__device__ __forceinline__ void wave_lds_fence() {
-    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
-    __builtin_amdgcn_wave_barrier();
-    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
-}
-
 constexpr int kGroupSlots = 128;
 
 struct WaveGroup {
