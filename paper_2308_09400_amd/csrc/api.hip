@@ -1117,14 +1117,14 @@ gipc_status gipc_friction_eval(gipc_ctx* ctx, const double* x, double* energy, d
         if (!same_pattern(ctx, A)) return fail(ctx, GIPC_ERR_STATE, "A is not the pattern of the last build");
     }
     const int64_t Ps = ctx->Ps;
-    CK(ensure(ctx->ffr, sizeof(double) * 16 * (size_t)(Ps > 0 ? Ps : 1)), "alloc friction");
+    CK(ensure(ctx->ffr, sizeof(double) * 12 * (size_t)(Ps > 0 ? Ps : 1)), "alloc friction");
     CK(ensure(ctx->fev, sizeof(double) * (size_t)(ctx->V > 0 ? ctx->V : 1)), "alloc friction");
     CK(ensure(ctx->fpart, sizeof(double) * (size_t)(ctx->npieces > 0 ? ctx->npieces : 1)), "alloc friction");
     hipStream_t s = S(stream);
     CK(launch_fric_eval(ctx->V, as<int4>(ctx->st_vid), ctx->ranges, as<double>(ctx->flag), x, ctx->fric_sv,
                         as<double>(ctx->ffr), as<int32_t>(ctx->row_ptr), as<int32_t>(ctx->diag_slot),
-                        as<int64_t>(ctx->cptr), as<uint32_t>(ctx->contrib), grad, as<double>(ctx->fev),
-                        A ? A->val : nullptr, A ? A->dtype : 0, ctx->nnzb, s),
+                        as<int64_t>(ctx->cptr), as<uint32_t>(ctx->contrib), as<int32_t>(ctx->order), grad,
+                        as<double>(ctx->fev), A ? A->val : nullptr, A ? A->dtype : 0, ctx->nnzb, s),
        "friction eval");
     CK(launch_energy(as<double>(ctx->fev), as<int2>(ctx->pieces), ctx->npieces, as<int32_t>(ctx->poff), ctx->S,
                      as<double>(ctx->fpart), energy, s),

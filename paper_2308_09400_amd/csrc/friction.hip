@@ -27,7 +27,7 @@ namespace {
 
 constexpr int kFrLanes = 16;
 
-// lag record [c1, c2, nx, ny, nz, mu lambda m, ax, ay, az]
+// lag record [c1, c2, nx, ny, nz, mu lambda m, ax, ay, az], component-major [9][Ps]
 __global__ void __launch_bounds__(kBlock) k_fric_lag(const int4* __restrict__ st_vid,
                                                      const int32_t* __restrict__ mult, TypeRanges tr,
                                                      const double* __restrict__ X, const double* __restrict__ XR,
@@ -52,27 +52,33 @@ __global__ void __launch_bounds__(kBlock) k_fric_lag(const int4* __restrict__ st
     for (int i = 0; i < 4; ++i)
         if (i < nv) s = s + o.c[i] * ld3(X, v[i]);
     const d3 a = s - dot(n, s) * n;
-    double* r = lag + 9 * k;
-    r[0] = o.c[1]; r[1] = o.c[2];
-    r[2] = n.x; r[3] = n.y; r[4] = n.z;
-    r[5] = ml;
-    r[6] = a.x; r[7] = a.y; r[8] = a.z;
+    const double L[9] = {o.c[1], o.c[2], n.x, n.y, n.z, ml, a.x, a.y, a.z};
+#pragma unroll
+    for (int q = 0; q < 9; ++q) lag[q * tr.off[8] + k] = L[q];
 }
 
-// friction record, 16 doubles (one 128-byte line per pair for the row pass):
-// [D, gx, gy, gz, S00, S01, S02, S11, S12, S22, c1, c2, -, -, -, -]
-constexpr int kFr = 16;
+// Friction records: fr [Ps][8] = S00 S01 S02 S11 S12 S22 c1 c2, the 64 bytes
+// the off-diagonal blocks gather, and behind them [Ps][4] = D gx gy gz, which
+// only the row pass reads too.  Bound by the record's lines: on five 150 x 150
+// sheets (0.7 M pairs) 39 us with the lag component-major, the first records
+// written by quads and 96 bytes each; 60 us with [Ps][9] lags and records of
+// 128 bytes, three quarters used, stored lane by lane.
+constexpr int kFr = 8, kFrG = 4;
 __global__ void __launch_bounds__(kBlock) k_fric_pair(const int4* __restrict__ st_vid, TypeRanges tr,
                                                       const double* __restrict__ lag, const double* __restrict__ X,
                                                       double sv, double* __restrict__ fr) {
     const int64_t k = (int64_t)blockIdx.x * kBlock + threadIdx.x;
-    if (k >= tr.off[8]) return;
-    const int ft = type_of(k, tr);
+    const int64_t Ps = tr.off[8];
+    const bool in = k < Ps;  // all lanes stay: the records leave by quads
+    const int64_t kc = in ? k : 0;
+    const int ft = type_of(kc, tr);
     const int nv = ft_nverts(ft);
-    const int4 v4 = st_vid[k];
-    const double* L = lag + 9 * k;
+    const int4 v4 = st_vid[kc];
+    double L[9];
+#pragma unroll
+    for (int q = 0; q < 9; ++q) L[q] = lag[q * Ps + kc];
     const double m[8] = {L[0], L[1], 0, 0, 0, 0, 0, 0};
-    const bool ee = k >= tr.off[FT_EE];
+    const bool ee = kc >= tr.off[FT_EE];
     d3 s = mk(0, 0, 0);
 #pragma unroll
     for (int i = 0; i < 4; ++i)
@@ -95,23 +101,22 @@ __global__ void __launch_bounds__(kBlock) k_fric_pair(const int4* __restrict__ s
     const double be = ml * fmax(f1y, 0.0);
     const double al = y > 0.0 ? (ml * fmax(df1, 0.0) - be) / (y * y) : 0.0;
     const d3 g = (ml * f1y) * t;
-    double* r = fr + kFr * k;
-    r[10] = L[0];
-    r[11] = L[1];
-    r[0] = ml * f0;
-    r[1] = g.x; r[2] = g.y; r[3] = g.z;
     // S = be (I - n n^T) + al t t^T
-    r[4] = be * (1.0 - n.x * n.x) + al * t.x * t.x;
-    r[5] = -be * n.x * n.y + al * t.x * t.y;
-    r[6] = -be * n.x * n.z + al * t.x * t.z;
-    r[7] = be * (1.0 - n.y * n.y) + al * t.y * t.y;
-    r[8] = -be * n.y * n.z + al * t.y * t.z;
-    r[9] = be * (1.0 - n.z * n.z) + al * t.z * t.z;
+    double2 r[4] = {make_double2(be * (1.0 - n.x * n.x) + al * t.x * t.x, -be * n.x * n.y + al * t.x * t.y),
+                    make_double2(-be * n.x * n.z + al * t.x * t.z, be * (1.0 - n.y * n.y) + al * t.y * t.y),
+                    make_double2(-be * n.y * n.z + al * t.y * t.z, be * (1.0 - n.z * n.z) + al * t.z * t.z),
+                    make_double2(L[0], L[1])};
+    quad_store(fr, in ? (uint32_t)k : ~0u, r);
+    if (in) {
+        double2* d = reinterpret_cast<double2*>(fr + kFr * Ps + kFrG * k);
+        d[0] = make_double2(ml * f0, g.x);
+        d[1] = make_double2(g.y, g.z);
+    }
 }
 
 // c_i of pair k from its friction record
 __device__ __forceinline__ double fr_coef(const double* f, uint32_t k, int i, int64_t e0) {
-    const double m[8] = {f[10], f[11], 0, 0, 0, 0, 0, 0};
+    const double m[8] = {f[6], f[7], 0, 0, 0, 0, 0, 0};
     return rec_coef(m, i, (int64_t)k >= e0);
 }
 
@@ -132,32 +137,59 @@ __device__ __forceinline__ void add_block_sym(void* val, int dtype, int64_t nnzb
 // kFrLanes lanes per row.  The diagonal list (the row's incidences) is
 // split over the lanes and reduced by a fixed butterfly: gradient, energy
 // share (pairs whose slot 0 is the row) and, with val, the diagonal block.
-__global__ void __launch_bounds__(kBlock) k_fric_rows(int32_t V, const int32_t* __restrict__ row_ptr,
+// Bound by the gather of the records: rows go in the spatial order of the
+// assembly, so neighbouring groups meet in L2, and each lane has two records
+// in flight (five 150 x 150 sheets: 113 us; 183 us in vertex order, one at a
+// time).
+__global__ void __launch_bounds__(kBlock) k_fric_rows(int32_t V, const int32_t* __restrict__ order,
+                                                      const int32_t* __restrict__ row_ptr,
                                                       const int32_t* __restrict__ diag_slot,
                                                       const int64_t* __restrict__ cptr,
                                                       const uint32_t* __restrict__ contrib,
-                                                      const double* __restrict__ fr, int64_t e0,
+                                                      const double* __restrict__ fr, int64_t Ps, int64_t e0,
                                                       double* __restrict__ grad, double* __restrict__ ev,
                                                       void* __restrict__ val, int dtype, int64_t nnzb) {
-    const int64_t r = xcd_block() * (kBlock / kFrLanes) + threadIdx.x / kFrLanes;
+    const int64_t gi = xcd_block() * (kBlock / kFrLanes) + threadIdx.x / kFrLanes;
     const int lg = threadIdx.x % kFrLanes;
-    const bool valid = r < V;
+    const bool valid = gi < V;
+    const int64_t r = valid ? order[gi] : 0;
     const int32_t ds = valid ? diag_slot[r] : 0;
     double acc[10] = {0, 0, 0, 0, 0, 0, 0, 0, 0, 0};  // gradient, energy, diagonal block
     if (valid) {
-        for (int64_t t = cptr[ds] + lg; t < cptr[ds + 1]; t += kFrLanes) {
-            const uint32_t code = contrib[t];
-            const uint32_t k = code >> 4;
-            const int i = (int)((code >> 2) & 3u);
-            const double* f = fr + kFr * (int64_t)k;
-            const double ci = fr_coef(f, k, i, e0);
-            acc[0] += ci * f[1];
-            acc[1] += ci * f[2];
-            acc[2] += ci * f[3];
-            if (i == 0) acc[3] += f[0];
-            const double cc = ci * ci;
+        const int64_t t1 = cptr[ds + 1];
+        // two records in flight per lane, summed in list order
+        for (int64_t t = cptr[ds] + lg; t < t1; t += 2 * kFrLanes) {
+            const bool two = t + kFrLanes < t1;
+            const uint32_t code[2] = {contrib[t], two ? contrib[t + kFrLanes] : 0u};
+            double f[2][8], d[2][4];
 #pragma unroll
-            for (int q = 0; q < 6; ++q) acc[4 + q] += cc * f[4 + q];
+            for (int u = 0; u < 2; ++u)
+                if (u == 0 || two) {
+                    const int64_t k = code[u] >> 4;
+                    const double2* w = reinterpret_cast<const double2*>(fr + kFr * k);
+                    const double2* z = reinterpret_cast<const double2*>(fr + kFr * Ps + kFrG * k);
+#pragma unroll
+                    for (int q = 0; q < 4; ++q) {
+                        const double2 x = w[q];
+                        f[u][2 * q] = x.x;
+                        f[u][2 * q + 1] = x.y;
+                    }
+                    const double2 z0 = z[0], z1 = z[1];
+                    d[u][0] = z0.x; d[u][1] = z0.y; d[u][2] = z1.x; d[u][3] = z1.y;
+                }
+#pragma unroll
+            for (int u = 0; u < 2; ++u) {
+                if (u == 1 && !two) break;
+                const int i = (int)((code[u] >> 2) & 3u);
+                const double ci = fr_coef(f[u], code[u] >> 4, i, e0);
+                acc[0] += ci * d[u][1];
+                acc[1] += ci * d[u][2];
+                acc[2] += ci * d[u][3];
+                if (i == 0) acc[3] += d[u][0];
+                const double cc = ci * ci;
+#pragma unroll
+                for (int q = 0; q < 6; ++q) acc[4 + q] += cc * f[u][q];
+            }
         }
     }
 #pragma unroll
@@ -181,11 +213,13 @@ __global__ void __launch_bounds__(kBlock) k_fric_rows(int32_t V, const int32_t* 
 // lane writes its terms c_i c_j S (upper triangles) to LDS and the owner of
 // each block adds its own in list order.  Block (c, r) sums the same pairs
 // as (r, c) in the same order with the same products c_i c_j, so the two
-// are equal, as S is symmetric.
+// are equal, as S is symmetric.  In the assembly's row order, with the
+// record's 64 bytes alone: 288 us on five 150 x 150 sheets, 330 us before.
 constexpr int kFoLanes = 32, kFoGroup = 2;
 
 template <int BLOCK>
-__global__ void __launch_bounds__(BLOCK) k_fric_offdiag(int32_t V, const int32_t* __restrict__ row_ptr,
+__global__ void __launch_bounds__(BLOCK) k_fric_offdiag(int32_t V, const int32_t* __restrict__ order,
+                                                        const int32_t* __restrict__ row_ptr,
                                                         const int32_t* __restrict__ diag_slot,
                                                         const int64_t* __restrict__ cptr,
                                                         const uint32_t* __restrict__ contrib,
@@ -193,8 +227,9 @@ __global__ void __launch_bounds__(BLOCK) k_fric_offdiag(int32_t V, const int32_t
                                                         void* __restrict__ val, int dtype, int64_t nnzb) {
     constexpr int L = kFoLanes, G = kFoGroup, C = L * G;
     __shared__ double lds[BLOCK / L][C][6];
-    const int64_t r = xcd_block() * (BLOCK / L) + threadIdx.x / L;
-    if (r >= V) return;  // the whole lane group (L divides the wavefront)
+    const int64_t gi = xcd_block() * (BLOCK / L) + threadIdx.x / L;
+    if (gi >= V) return;  // the whole lane group (L divides the wavefront)
+    const int64_t r = order[gi];
     const int lg = threadIdx.x % L;
     double(*T)[6] = lds[threadIdx.x / L];
     const int32_t ds = diag_slot[r];
@@ -227,7 +262,7 @@ __global__ void __launch_bounds__(BLOCK) k_fric_offdiag(int32_t V, const int32_t
                         const double* f = fr + kFr * (int64_t)k;
                         const double cc = fr_coef(f, k, i, e0) * fr_coef(f, k, j, e0);
 #pragma unroll
-                        for (int c = 0; c < 6; ++c) T[u * L + lg][c] = cc * f[4 + c];
+                        for (int c = 0; c < 6; ++c) T[u * L + lg][c] = cc * f[c];
                     }
                 }
                 // the lane group lies in one wavefront: its LDS writes are
@@ -264,8 +299,8 @@ hipError_t launch_fric_lag(const int4* st_vid, const int32_t* mult, const TypeRa
 
 hipError_t launch_fric_eval(int32_t V, const int4* st_vid, const TypeRanges& tr, const double* lag, const double* x,
                             double sv, double* fr, const int32_t* row_ptr, const int32_t* diag_slot,
-                            const int64_t* cptr, const uint32_t* contrib, double* grad, double* ev, void* val,
-                            int dtype, int64_t nnzb, hipStream_t s) {
+                            const int64_t* cptr, const uint32_t* contrib, const int32_t* order, double* grad,
+                            double* ev, void* val, int dtype, int64_t nnzb, hipStream_t s) {
     if (tr.off[8] > 0) {
         k_fric_pair<<<grid(tr.off[8]), kBlock, 0, s>>>(st_vid, tr, lag, x, sv, fr);
         hipError_t e = hipGetLastError();
@@ -273,13 +308,13 @@ hipError_t launch_fric_eval(int32_t V, const int4* st_vid, const TypeRanges& tr,
     }
     if (V == 0) return hipSuccess;
     const int64_t nb = ((int64_t)V * kFrLanes + kBlock - 1) / kBlock;
-    k_fric_rows<<<(unsigned)nb, kBlock, 0, s>>>(V, row_ptr, diag_slot, cptr, contrib, fr, tr.off[FT_EE], grad, ev,
-                                                val, dtype, nnzb);
+    k_fric_rows<<<(unsigned)nb, kBlock, 0, s>>>(V, order, row_ptr, diag_slot, cptr, contrib, fr, tr.off[8],
+                                                tr.off[FT_EE], grad, ev, val, dtype, nnzb);
     hipError_t e = hipGetLastError();
     if (e != hipSuccess || !val) return e;
     const int64_t nbo = ((int64_t)V * kFoLanes + kBlock - 1) / kBlock;
-    k_fric_offdiag<kBlock><<<(unsigned)nbo, kBlock, 0, s>>>(V, row_ptr, diag_slot, cptr, contrib, fr, tr.off[FT_EE],
-                                                            val, dtype, nnzb);
+    k_fric_offdiag<kBlock><<<(unsigned)nbo, kBlock, 0, s>>>(V, order, row_ptr, diag_slot, cptr, contrib, fr,
+                                                            tr.off[FT_EE], val, dtype, nnzb);
     return hipGetLastError();
 }
 

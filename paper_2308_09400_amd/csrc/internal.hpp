@@ -444,14 +444,15 @@ int64_t mf_num_parts(int32_t V);
 hipError_t launch_proxy_dense(int method, const int4* st_vid, const int32_t* mult, const TypeRanges& tr,
                               const double* x, const double* xr, const DevParams& pm, double* hess, hipStream_t s);
 
-// lagged friction (friction.hip): lag [Ps][9] at x^n; eval writes fr [Ps][16],
+// lagged friction (friction.hip): lag [9][Ps] at x^n; eval writes fr
+// (S [Ps][8], then D and g [Ps][4]),
 // grad [V][3], energy shares ev [V] and, with val, adds the blocks
 hipError_t launch_fric_lag(const int4* st_vid, const int32_t* mult, const TypeRanges& tr, const double* x,
                            const double* xr, const DevParams& pm, double mu, double* lag, hipStream_t s);
 hipError_t launch_fric_eval(int32_t V, const int4* st_vid, const TypeRanges& tr, const double* lag, const double* x,
                             double sv, double* fr, const int32_t* row_ptr, const int32_t* diag_slot,
-                            const int64_t* cptr, const uint32_t* contrib, double* grad, double* ev, void* val,
-                            int dtype, int64_t nnzb, hipStream_t s);
+                            const int64_t* cptr, const uint32_t* contrib, const int32_t* order, double* grad,
+                            double* ev, void* val, int dtype, int64_t nnzb, hipStream_t s);
 
 // contact candidates (candidates.hip)
 struct CandGrid {
