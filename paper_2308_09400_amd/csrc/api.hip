@@ -1045,7 +1045,7 @@ gipc_status gipc_candidates(gipc_ctx* ctx, const gipc_mesh* mesh, const gipc_top
            "query cells");
     }
     for (int k = 0; k < 2; ++k) {
-        CK(launch_cell_pairs(k, false, x, topo->vobj, k ? ctx->crec_e.p : nullptr, trec[k]->p, g, dhat,
+        CK(launch_cell_pairs(k, false, x, topo->vobj, tp[k], trec[k]->p, g, dhat,
                              as<int64_t>(*qtoff[k]), as<int32_t>(*qent[k]), as<int64_t>(*qeoff[k]),
                              as<int64_t>(*toff[k]), as<int32_t>(*tent[k]), as<int32_t>(*ecnt[k]), nullptr,
                              as<int64_t>(*boff[k]), as<uint64_t>(*bal[k]), as<int64_t>(*evis[k]), nullptr, s),
@@ -1064,7 +1064,7 @@ gipc_status gipc_candidates(gipc_ctx* ctx, const gipc_mesh* mesh, const gipc_top
         return fail(ctx, GIPC_ERR_WORKSPACE, "cap = %lld is below the %lld candidates", (long long)cap,
                     (long long)*count);
     for (int k = 0; k < 2; ++k) {
-        CK(launch_cell_pairs(k, true, x, topo->vobj, k ? ctx->crec_e.p : nullptr, trec[k]->p, g, dhat,
+        CK(launch_cell_pairs(k, true, x, topo->vobj, tp[k], trec[k]->p, g, dhat,
                              as<int64_t>(*qtoff[k]), as<int32_t>(*qent[k]), as<int64_t>(*qeoff[k]),
                              as<int64_t>(*toff[k]), as<int32_t>(*tent[k]), nullptr, as<int64_t>(*eoff[k]),
                              as<int64_t>(*boff[k]), as<uint64_t>(*bal[k]), as<int64_t>(*evis[k]),

@@ -30,7 +30,7 @@ namespace {
 
 struct Grid {
     double org[3];
-    double h[3];
+    double h[3], inv[3];  // cell size and its reciprocal
     int32_t n[3];
 };
 
@@ -39,7 +39,8 @@ struct Box {
 };
 
 // one 64-byte record per primitive for the queries: its box, its vertex
-// ids (v[2] = v[1] for edges) and its object
+// ids and its object, that of v[0]; v[2] also tells of vertices of different
+// objects (triangles: ~v[2] in its place, edges: 1, otherwise 0)
 struct __align__(64) PrimRec {
     double lo[3], hi[3];
     int32_t v[3];
@@ -56,9 +57,15 @@ __device__ __forceinline__ Box prim_box(const double* __restrict__ X, const int3
     return b;
 }
 
-__device__ __forceinline__ int cell_of(double c, double org, double h, int32_t n) {
-    const int i = (int)floor((c - org) / h);
-    return i < 0 ? 0 : (i >= n ? n - 1 : i);
+// floor((c - org) / h), clamped to the grid.  The product with the reciprocal
+// is within 1.2e-7 of the quotient up to 2^28 cells, so it has the same floor
+// unless it lies next to a whole number; only then is the division done.
+__device__ __forceinline__ int cell_of(double c, const Grid& g, int d) {
+    const double a = c - g.org[d];
+    double f = a * g.inv[d], w = floor(f);
+    if (!(f - w > 1e-6 && f - w < 1.0 - 1e-6)) w = floor(a / g.h[d]);
+    const int i = (int)w;
+    return i < 0 ? 0 : (i >= g.n[d] ? g.n[d] - 1 : i);
 }
 
 __device__ __forceinline__ double get(const d3& v, int d) { return d == 0 ? v.x : (d == 1 ? v.y : v.z); }
@@ -213,8 +220,8 @@ __global__ void __launch_bounds__(kBlock) k_cell_count_prims(const double* __res
     const Box b = prim_box(X, prims + NPER * i, NPER);
     int lo[3], hi[3];
     for (int d = 0; d < 3; ++d) {
-        lo[d] = cell_of(get(b.lo, d), g.org[d], g.h[d], g.n[d]);
-        hi[d] = cell_of(get(b.hi, d), g.org[d], g.h[d], g.n[d]);
+        lo[d] = cell_of(get(b.lo, d), g, d);
+        hi[d] = cell_of(get(b.hi, d), g, d);
     }
     __shared__ uint32_t tab[kBlock / 64][kGroupSlots];
     const auto vcell = [&](int a, int c, int e) { return ((int64_t)a * g.n[1] + c) * g.n[2] + e; };
@@ -234,8 +241,8 @@ __global__ void __launch_bounds__(kBlock) k_cell_fill_prims(const double* __rest
     const Box b = prim_box(X, prims + NPER * i, NPER);
     int lo[3], hi[3];
     for (int d = 0; d < 3; ++d) {
-        lo[d] = cell_of(get(b.lo, d), g.org[d], g.h[d], g.n[d]);
-        hi[d] = cell_of(get(b.hi, d), g.org[d], g.h[d], g.n[d]);
+        lo[d] = cell_of(get(b.lo, d), g, d);
+        hi[d] = cell_of(get(b.hi, d), g, d);
     }
     __shared__ uint32_t tab[kBlock / 64][kGroupSlots];
     const auto vcell = [&](int a, int c, int e) { return ((int64_t)a * g.n[1] + c) * g.n[2] + e; };
@@ -256,7 +263,8 @@ __global__ void __launch_bounds__(kBlock) k_prim_records(const double* __restric
     PrimRec r;
     r.lo[0] = b.lo.x; r.lo[1] = b.lo.y; r.lo[2] = b.lo.z;
     r.hi[0] = b.hi.x; r.hi[1] = b.hi.y; r.hi[2] = b.hi.z;
-    r.v[0] = v[0]; r.v[1] = v[1]; r.v[2] = NPER == 3 ? v[2] : v[1];
+    r.v[0] = v[0]; r.v[1] = v[1]; const bool mixed = vobj[v[0]] != vobj[v[1]] || (NPER == 3 && vobj[v[0]] != vobj[v[NPER - 1]]);
+    r.v[2] = NPER == 3 ? (mixed ? ~v[2] : v[2]) : mixed;
     r.obj = vobj[v[0]];
     rec[i] = r;
 }
@@ -276,7 +284,7 @@ __global__ void __launch_bounds__(kBlock) k_cell_sort(int64_t ncell, const int64
     for (int64_t c0 = 0; c0 < n; c0 += 64) {
         const bool mine_ok = c0 + lane < n;
         const int32_t mine = mine_ok ? raw[b + c0 + lane] : 0;
-        int64_t rank = 0;
+        int rank = 0;
         for (int64_t c1 = 0; c1 < n; c1 += 64) {
             const int32_t other = c1 + lane < n ? raw[b + c1 + lane] : 0;
             const int m = (int)(n - c1 < 64 ? n - c1 : 64);
@@ -307,8 +315,8 @@ __device__ __forceinline__ void query_of(int64_t q, const double* __restrict__ X
 // the cells covered by a query's box inflated by dhat
 __device__ __forceinline__ void query_cells(const Box& qb, const Grid& g, double dhat, int lo[3], int hi[3]) {
     for (int d = 0; d < 3; ++d) {
-        lo[d] = cell_of(get(qb.lo, d) - dhat, g.org[d], g.h[d], g.n[d]);
-        hi[d] = cell_of(get(qb.hi, d) + dhat, g.org[d], g.h[d], g.n[d]);
+        lo[d] = cell_of(get(qb.lo, d) - dhat, g, d);
+        hi[d] = cell_of(get(qb.hi, d) + dhat, g, d);
     }
 }
 
@@ -372,18 +380,66 @@ __device__ __forceinline__ double read_lane(double v, int k) {
     return __longlong_as_double(((long long)hi << 32) | (long long)(unsigned)lo);
 }
 
+// Boxes in whole steps of 1/2048 cell about a cell's corner, for a first test
+// that rejects a pair by integers: a coordinate goes to -16383 .. 16383 by
+// operations that never swap two values, so integers in strict order prove the
+// order of the values (equal ones prove nothing).  Two axis ends per word: a primitive
+// holds (hi, -lo) and a query (lo - dhat, -(hi + dhat)); a negative half of
+// their difference says that the boxes are apart.
+struct CellSteps {
+    double org[3], inv[3];
+};
+
+__device__ __forceinline__ CellSteps cell_steps(const Grid& g, const int cc[3]) {
+    CellSteps c;
+#pragma unroll
+    for (int d = 0; d < 3; ++d) {
+        c.org[d] = g.org[d] + cc[d] * g.h[d];
+        c.inv[d] = 2048.0 * g.inv[d];
+    }
+    return c;
+}
+
+typedef short short2_t __attribute__((ext_vector_type(2)));
+
+__device__ __forceinline__ int step_of(double v, const CellSteps& c, int d) {
+    return min(max((int)((v - c.org[d]) * c.inv[d]), -16383), 16383);
+}
+
+__device__ __forceinline__ int pack_steps(int a, int b) { return (a & 0xffff) | (b << 16); }
+
+__device__ __forceinline__ short2_t gap_steps(int prim, int query) {
+    return __builtin_bit_cast(short2_t, prim) - __builtin_bit_cast(short2_t, query);
+}
+
+__device__ __forceinline__ short2_t min_steps(short2_t a, short2_t b) { return __builtin_elementwise_min(a, b); }
+
+__device__ __forceinline__ int neg_steps(short2_t a) { return __builtin_bit_cast(int, a) & (int)0x80008000; }
+
+// the words of a primitive's box and of a query's (already inflated) box
+__device__ __forceinline__ void prim_steps(const double* lo, const double* hi, const CellSteps& c, int w[3]) {
+#pragma unroll
+    for (int d = 0; d < 3; ++d) w[d] = pack_steps(step_of(hi[d], c, d), -step_of(lo[d], c, d));
+}
+
+__device__ __forceinline__ void query_steps(const double* lo, const double* hi, const CellSteps& c, int w[3]) {
+#pragma unroll
+    for (int d = 0; d < 3; ++d) w[d] = pack_steps(step_of(lo[d], c, d), -step_of(hi[d], c, d));
+}
+
 // Edge-edge pairs, one wave per cell: its lanes take the edge queries
 // covering the cell, 64 at a time, and the cell's edge list 64 records at a
 // time, one record per lane; each record is then handed to every lane from
 // the lane holding it (a lane read, no memory access), so the records are
-// read once per 64 queries.  The query q's visit of the cell is entry e = qeoff[q] + j, j the
-// cell's rank in the query's walk (x slowest, z fastest): EMIT = false
-// stores the entry's candidate count in cnt[e], EMIT = true writes its
-// candidates at out + eoff[e], in list order.  Only edges of larger index
+// read once, or once per 64 queries where there are more than 64 of them.
+// The query q's visit of the cell is entry e = qeoff[q] + j, j the cell's
+// rank in the query's walk (x slowest, z fastest): EMIT = false stores the
+// entry's candidate count in cnt[e], EMIT = true writes its candidates at
+// out + eoff[e], in list order.  Only edges of larger index
 // than the query are taken.  The counting pass also stores, per record
 // and chunk of queries, the 64-lane mask of the queries it pairs with
 // (bal, from boff[cell]); the emitting pass replays those masks instead of
-// testing again, reading only the records' vertex ids, and writes query by
+// testing again, reading only the edges' vertex ids, and writes query by
 // query so that a store covers consecutive slots of one query.  The
 // counting pass also leaves each visit's entry e in evis (by position in
 // the cell's query list), so the emitting pass needs no query boxes.
@@ -396,14 +452,22 @@ __device__ __forceinline__ double read_lane(double v, int k) {
 // this cell's when, along every axis, one of the two lower cells is this
 // cell's.
 //
-// (Seven waves per SIMD asked for: the compiler then keeps the counting
-// pass at 66 registers instead of 84, without spills; the point-triangle
-// pass below at 68.)
+// The counting pass is bound by its instructions: some 24 records against 64
+// queries a wave, 9 pairs in 100 a hit, so an early way out of the test is
+// worth nothing (6%); integer steps with the coordinates looked at only for
+// ties, one cell's setup without 64-bit divisions and with a reciprocal, and
+// short lists kept for all queries took it from 956 to 690 us on ten
+// 256 x 256 sheets (the point-triangle pass below from 461 to 310).  The
+// emitting pass is bound by the lines it touches: the vertex ids come from the
+// edges and not from the records, and consecutive cells share an L2 (613 ->
+// 550 us; writing record by record, each query's lane its own slot, took 750).
+// Six waves per SIMD: seven leave the counting pass 72 registers, ten spilled.
 template <bool EMIT>
-__global__ void __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(7))) k_cell_pairs_ee(const double* __restrict__ X,
+__global__ void __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(6))) k_cell_pairs_ee(
+                                                       const double* __restrict__ X,
                                                        const int32_t* __restrict__ vobj,
-                                                       const PrimRec* __restrict__ qrec,
-                                                       const PrimRec* __restrict__ trec, Grid g, double dhat,
+                                                       const PrimRec* __restrict__ erec,
+                                                       const int32_t* __restrict__ edges, Grid g, double dhat,
                                                        int64_t ncell, const int64_t* __restrict__ qtoff,
                                                        const int32_t* __restrict__ qent,
                                                        const int64_t* __restrict__ qeoff,
@@ -415,33 +479,54 @@ __global__ void __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(7))
                                                        int64_t* __restrict__ evis, int4* __restrict__ out) {
     const int lane = threadIdx.x & 63;
     const int64_t cell =
-        (int64_t)blockIdx.x * (kBlock / 64) + __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
+        xcd_block() * (kBlock / 64) + __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
     if (cell >= ncell) return;
     const int64_t qa = qtoff[cell], qz = qtoff[cell + 1];
     const int64_t ta = coff[cell], tz = coff[cell + 1];
     if (qa == qz || (EMIT && ta == tz)) return;
-    const int cc[3] = {(int)(cell / ((int64_t)g.n[1] * g.n[2])), (int)((cell / g.n[2]) % g.n[1]),
-                       (int)(cell % g.n[2])};
+    const uint32_t row = (uint32_t)cell / (uint32_t)g.n[2];  // at most 2^28 cells
+    const int cc[3] = {(int)(row / (uint32_t)g.n[1]), (int)(row % (uint32_t)g.n[1]),
+                       (int)((uint32_t)cell - row * (uint32_t)g.n[2])};
+    const CellSteps st = cell_steps(g, cc);
+    // the records in the lanes, those of the cell's first 64 on their way
+    // beside the first queries; a short list stays for all queries
+    int64_t at = ta;
+    const int64_t bcell = boff[cell];
+    int32_t id = 0;
+    PrimRec r{};
+    const auto load = [&](PrimRec& r) {
+        if (EMIT) {
+            r.v[0] = edges[2 * (int64_t)id];
+            r.v[1] = edges[2 * (int64_t)id + 1];
+        } else {
+            r = erec[id];
+        }
+    };
+    if (ta < tz) {
+        id = cent[ta + lane < tz ? ta + lane : ta];
+        load(r);
+    }
     for (int64_t qb0 = qa; qb0 < qz; qb0 += 64) {
         const int64_t i = qb0 + lane;
         const bool act = i < qz;
         const int64_t q = qent[act ? i : qa];
         Box qb{};
         int32_t q0 = 0, q1 = 0, qo = 0;
+        bool mixed = false;
         int lo[3] = {0, 0, 0}, hi[3] = {0, 0, 0};
         int64_t e, w = 0, wz = 0;
         if (EMIT) {
             // the counting pass left the visit's entry; only the query's ids
             // are needed
             e = act ? evis[i] : 0;
-            const int4 qv = *reinterpret_cast<const int4*>(&qrec[q].v[0]);
-            q0 = qv.x;
-            q1 = qv.y;
+            q0 = edges[2 * q];
+            q1 = edges[2 * q + 1];
             w = act ? eoff[e] : 0;
             wz = act ? eoff[e + 1] : 0;
             if (__ballot(w < wz) == 0) continue;
         } else {
-            query_of<1>(q, X, vobj, qrec, qb, q0, q1, qo);
+            query_of<1>(q, X, vobj, erec, qb, q0, q1, qo);
+            mixed = erec[q].v[2] != 0;
             query_cells(qb, g, dhat, lo, hi);
             e = qeoff[q] + ((int64_t)(cc[0] - lo[0]) * (hi[1] - lo[1] + 1) + (cc[1] - lo[1])) *
                                (hi[2] - lo[2] + 1) + (cc[2] - lo[2]);
@@ -450,35 +535,35 @@ __global__ void __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(7))
         const bool own0 = lo[0] == cc[0], own1 = lo[1] == cc[1], own2 = lo[2] == cc[2];
         const double qlx = qb.lo.x - dhat, qly = qb.lo.y - dhat, qlz = qb.lo.z - dhat;
         const double qhx = qb.hi.x + dhat, qhy = qb.hi.y + dhat, qhz = qb.hi.z + dhat;
-        int64_t t0 = ta;
+        int qw[3] = {0, 0, 0};
+        if (!EMIT) {
+            const double ql[3] = {qlx, qly, qlz}, qh[3] = {qhx, qhy, qhz};
+            query_steps(ql, qh, st, qw);
+        }
+        // axes whose lower cell is not this one, bit 3: no query
+        const int qno = (own0 ? 0 : 1) | (own1 ? 0 : 2) | (own2 ? 0 : 4) | (act ? 0 : 8);
+        const int32_t qid = (int32_t)q;
         // the list is in increasing edge id: skip what no lane takes
-        int64_t qmin = act ? q : INT64_MAX;
+        int32_t qmin = act ? (int32_t)q : INT32_MAX;
 #pragma unroll
-        for (int o = 32; o > 0; o >>= 1) {
-            const int64_t v = __shfl_xor(qmin, o, 64);
-            qmin = v < qmin ? v : qmin;
-        }
-        qmin = __builtin_amdgcn_readfirstlane((int)qmin);
-        // (64 entries a step: they form a prefix of each window)
-        for (;;) {
-            const int64_t j = t0 + lane;
-            const unsigned long long m = __ballot(j < tz && (int64_t)cent[j] <= qmin);
-            t0 += __popcll(m);
-            if (m != ~0ull) break;
-        }
+        for (int o = 32; o > 0; o >>= 1) qmin = min(qmin, __shfl_xor(qmin, o, 64));
+        qmin = __builtin_amdgcn_readfirstlane(qmin);
         int32_t found = 0;
         // this chunk's hit masks: slot (chunk of queries, record) of the cell
-        const int64_t bslot = boff[cell] + ((qb0 - qa) >> 6) * (tz - ta);
-        for (int64_t tb0 = t0; tb0 < tz; tb0 += 64) {
-            // this lane's record of the chunk
-            const int64_t j = tb0 + lane;
-            const int32_t id = cent[j < tz ? j : tb0];
+        const int64_t bslot = bcell + ((qb0 - qa) >> 6) * (tz - ta);
+        for (int64_t tb0 = ta; tb0 < tz; tb0 += 64) {
             const int nk = (int)(tz - tb0 < 64 ? tz - tb0 : 64);
+            if (at != tb0) {
+                at = tb0;
+                id = cent[tb0 + (lane < nk ? lane : 0)];
+                load(r);
+            }
+            const int k0 = __popcll(__ballot(lane < nk && id <= qmin));
+            if (k0 == nk) continue;
             if (EMIT) {
                 // replay the counting pass's masks, query by query (only
                 // the queries with a hit in this chunk): the hit records'
                 // lanes write the query's next candidates side by side
-                const int4 rv = *reinterpret_cast<const int4*>(&trec[id].v[0]);
                 const unsigned long long mine = lane < nk ? bal[bslot + (tb0 - ta) + lane] : 0ull;
                 unsigned long long any = mine;
 #pragma unroll
@@ -494,29 +579,42 @@ __global__ void __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(7))
                     const int32_t a0 = __builtin_amdgcn_readlane(q0, jq), a1 = __builtin_amdgcn_readlane(q1, jq);
                     if (bit)
                         out[base + __popcll(bm & below)] =
-                            make_int4(a0, a1, rv.x, rv.y);
+                            make_int4(a0, a1, r.v[0], r.v[1]);
                     if (lane == jq) w += __popcll(bm);
                 }
                 if (__ballot(w < wz) == 0) break;
                 continue;
             }
-            const PrimRec r = trec[id];
-            int tsel = 0;
+            int tno = 8;  // as qno, bit 3 always
+#pragma unroll
             for (int d = 0; d < 3; ++d)
-                tsel |= (cell_of(r.lo[d], g.org[d], g.h[d], g.n[d]) == cc[d]) << d;
+                tno |= (cell_of(r.lo[d], g, d) != cc[d]) << d;
+            int tw[3];
+            prim_steps(r.lo, r.hi, st, tw);
+            // ends of different objects: two edges of different objects may
+            // share a vertex
+            const unsigned long long share = __ballot((lane < nk && r.v[2] != 0) || mixed) ? ~0ull : 0ull;
             unsigned long long mine = 0;
-            for (int k = 0; k < nk; ++k) {
-                const double lx = read_lane(r.lo[0], k), ly = read_lane(r.lo[1], k), lz = read_lane(r.lo[2], k);
-                const double hx = read_lane(r.hi[0], k), hy = read_lane(r.hi[1], k), hz = read_lane(r.hi[2], k);
-                const int32_t v0 = __builtin_amdgcn_readlane(r.v[0], k), v1 = __builtin_amdgcn_readlane(r.v[1], k);
-                const int32_t ob = __builtin_amdgcn_readlane(r.obj, k), tid = __builtin_amdgcn_readlane(id, k);
-                const int ts = __builtin_amdgcn_readlane(tsel, k);
-                bool hit = act && ob != qo && (int64_t)tid > q && v0 != q0 && v0 != q1 && v1 != q0 && v1 != q1;
-                hit = hit && !(qlx > hx || lx > qhx || qly > hy || ly > qhy || qlz > hz || lz > qhz);
-                hit = hit && (own0 || (ts & 1)) && (own1 || (ts & 2)) && (own2 || (ts & 4));
-                const unsigned long long m = __ballot(hit);
+            for (int k = k0; k < nk; ++k) {
+                const short2_t gap =
+                    min_steps(min_steps(gap_steps(__builtin_amdgcn_readlane(tw[0], k), qw[0]),
+                                        gap_steps(__builtin_amdgcn_readlane(tw[1], k), qw[1])),
+                              gap_steps(__builtin_amdgcn_readlane(tw[2], k), qw[2]));
+                // wave masks: not apart and reported here, other object, later edge
+                unsigned long long m =
+                    __ballot((neg_steps(gap) | (__builtin_amdgcn_readlane(tno, k) & qno)) == 0) &
+                    __ballot(__builtin_amdgcn_readlane(r.obj, k) != qo) &
+                    __ballot(__builtin_amdgcn_readlane(id, k) > qid);
+                const unsigned long long tie = __ballot(neg_steps(gap - (short)1) != 0);
+                if ((m & (tie | share)) != 0ull) {
+                    const double lx = read_lane(r.lo[0], k), ly = read_lane(r.lo[1], k), lz = read_lane(r.lo[2], k);
+                    const double hx = read_lane(r.hi[0], k), hy = read_lane(r.hi[1], k), hz = read_lane(r.hi[2], k);
+                    const int32_t v0 = __builtin_amdgcn_readlane(r.v[0], k), v1 = __builtin_amdgcn_readlane(r.v[1], k);
+                    m &= ~__ballot(v0 == q0 || v0 == q1 || v1 == q0 || v1 == q1 || qlx > hx || lx > qhx || qly > hy ||
+                                   ly > qhy || qlz > hz || lz > qhz);
+                }
                 if (lane == k) mine = m;
-                found += hit;
+                found += __builtin_amdgcn_inverse_ballot_w64(m) ? 1 : 0;
             }
             if (lane < nk) bal[bslot + (tb0 - ta) + lane] = mine;
         }
@@ -539,7 +637,7 @@ __global__ void __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(7))
 template <bool EMIT>
 __global__ void __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(7)))
 k_cell_pairs_pt(const double* __restrict__ X, const int32_t* __restrict__ vobj, const PrimRec* __restrict__ trec,
-                Grid g, double dhat, int64_t ncell, const int64_t* __restrict__ qtoff,
+                const int32_t* __restrict__ tris, Grid g, double dhat, int64_t ncell, const int64_t* __restrict__ qtoff,
                 const int32_t* __restrict__ qent, const int64_t* __restrict__ qeoff,
                 const int64_t* __restrict__ coff, const int32_t* __restrict__ cent, int32_t* __restrict__ cnt,
                 const int64_t* __restrict__ eoff, const int64_t* __restrict__ boff,
@@ -551,8 +649,10 @@ k_cell_pairs_pt(const double* __restrict__ X, const int32_t* __restrict__ vobj, 
     const int64_t qa = qtoff[cell], qz = qtoff[cell + 1];
     const int64_t ta = coff[cell], tz = coff[cell + 1];
     if (qa == qz || (EMIT && ta == tz)) return;
-    const int cc[3] = {(int)(cell / ((int64_t)g.n[1] * g.n[2])), (int)((cell / g.n[2]) % g.n[1]),
-                       (int)(cell % g.n[2])};
+    const uint32_t row = (uint32_t)cell / (uint32_t)g.n[2];  // at most 2^28 cells
+    const int cc[3] = {(int)(row / (uint32_t)g.n[1]), (int)(row % (uint32_t)g.n[1]),
+                       (int)((uint32_t)cell - row * (uint32_t)g.n[2])};
+    const CellSteps st = cell_steps(g, cc);
     const int64_t nq = qz - qa;
     const unsigned long long below = (1ull << lane) - 1ull;
     for (int64_t qb0 = qa; qb0 < qz; qb0 += 64) {
@@ -561,7 +661,8 @@ k_cell_pairs_pt(const double* __restrict__ X, const int32_t* __restrict__ vobj, 
         const int32_t q = qent[act ? i : qa];
         const int nqk = (int)(qz - qb0 < 64 ? qz - qb0 : 64);
         d3 pq = mk(0.0, 0.0, 0.0);
-        int32_t qo = 0, own = 0;
+        int32_t qo = 0, qno = 0;
+        int qw[3] = {0, 0, 0};
         int64_t e, w = 0, wz = 0;
         if (EMIT) {
             e = act ? evis[i] : 0;
@@ -578,7 +679,11 @@ k_cell_pairs_pt(const double* __restrict__ X, const int32_t* __restrict__ vobj, 
             e = qeoff[q] + ((int64_t)(cc[0] - lo[0]) * (hi[1] - lo[1] + 1) + (cc[1] - lo[1])) *
                                (hi[2] - lo[2] + 1) + (cc[2] - lo[2]);
             if (act) evis[i] = e;
-            own = (lo[0] == cc[0]) | ((lo[1] == cc[1]) << 1) | ((lo[2] == cc[2]) << 2);
+            // axes whose lower cell is not this one, bit 3 always
+            qno = (lo[0] != cc[0]) | ((lo[1] != cc[1]) << 1) | ((lo[2] != cc[2]) << 2) | 8;
+            const double ql[3] = {pq.x - dhat, pq.y - dhat, pq.z - dhat};
+            const double qh[3] = {pq.x + dhat, pq.y + dhat, pq.z + dhat};
+            query_steps(ql, qh, st, qw);
         }
         int32_t found = 0;
         for (int64_t tb0 = ta; tb0 < tz; tb0 += 64) {
@@ -587,33 +692,48 @@ k_cell_pairs_pt(const double* __restrict__ X, const int32_t* __restrict__ vobj, 
             const int32_t id = cent[tact ? j : tb0];
             const int64_t slot = boff[cell] + ((tb0 - ta) >> 6) * nq + (qb0 - qa);
             if (EMIT) {
-                const int4 rv = *reinterpret_cast<const int4*>(&trec[id].v[0]);
+                const int32_t* rv = tris + 3 * (int64_t)id;
+                const int32_t r0 = rv[0], r1 = rv[1], r2 = rv[2];
                 const unsigned long long mq = lane < nqk ? bal[slot + lane] : 0ull;
                 for (int k = 0; k < nqk; ++k) {
                     const unsigned long long m = read_lane_u64(mq, k);
                     if (m == 0) continue;
                     const int64_t base = (int64_t)read_lane_u64((unsigned long long)w, k);
                     const int32_t a0 = __builtin_amdgcn_readlane(q, k);
-                    if ((m >> lane) & 1ull) out[base + __popcll(m & below)] = make_int4(-(a0 + 1), rv.x, rv.y, rv.z);
+                    if ((m >> lane) & 1ull) out[base + __popcll(m & below)] = make_int4(-(a0 + 1), r0, r1, r2);
                     if (lane == k) w += __popcll(m);
                 }
                 if (__ballot(w < wz) == 0) break;
                 continue;
             }
-            const PrimRec r = trec[id];
-            int tsel = 0;
+            PrimRec r = trec[id];
+            // vertices of different objects: a point of another object than
+            // the first vertex's may be one of the others
+            const unsigned long long share = __ballot(tact && r.v[2] < 0) ? ~0ull : 0ull;
+            r.v[2] = r.v[2] < 0 ? ~r.v[2] : r.v[2];
+            int tno = tact ? 0 : 8;  // as qno, bit 3: no triangle
+#pragma unroll
             for (int d = 0; d < 3; ++d)
-                tsel |= (cell_of(r.lo[d], g.org[d], g.h[d], g.n[d]) == cc[d]) << d;
+                tno |= (cell_of(r.lo[d], g, d) != cc[d]) << d;
+            int tw[3];
+            prim_steps(r.lo, r.hi, st, tw);
             unsigned long long mine = 0;
             for (int k = 0; k < nqk; ++k) {
-                const double px = read_lane(pq.x, k), py = read_lane(pq.y, k), pz = read_lane(pq.z, k);
-                const int32_t a0 = __builtin_amdgcn_readlane(q, k), ob = __builtin_amdgcn_readlane(qo, k);
-                const int ow = __builtin_amdgcn_readlane(own, k) | tsel;
-                bool hit = tact && r.obj != ob && r.v[0] != a0 && r.v[1] != a0 && r.v[2] != a0;
-                hit = hit && !(px - dhat > r.hi[0] || r.lo[0] > px + dhat || py - dhat > r.hi[1] ||
-                               r.lo[1] > py + dhat || pz - dhat > r.hi[2] || r.lo[2] > pz + dhat);
-                hit = hit && ow == 7;
-                const unsigned long long m = __ballot(hit);
+                const short2_t gap =
+                    min_steps(min_steps(gap_steps(tw[0], __builtin_amdgcn_readlane(qw[0], k)),
+                                        gap_steps(tw[1], __builtin_amdgcn_readlane(qw[1], k))),
+                              gap_steps(tw[2], __builtin_amdgcn_readlane(qw[2], k)));
+                unsigned long long m =
+                    __ballot((neg_steps(gap) | (__builtin_amdgcn_readlane(qno, k) & tno)) == 0) &
+                    __ballot(__builtin_amdgcn_readlane(qo, k) != r.obj);
+                const unsigned long long tie = __ballot(neg_steps(gap - (short)1) != 0);
+                if ((m & (tie | share)) != 0ull) {
+                    const double px = read_lane(pq.x, k), py = read_lane(pq.y, k), pz = read_lane(pq.z, k);
+                    const int32_t a0 = __builtin_amdgcn_readlane(q, k);
+                    m &= ~__ballot(r.v[0] == a0 || r.v[1] == a0 || r.v[2] == a0 || px - dhat > r.hi[0] ||
+                                   r.lo[0] > px + dhat || py - dhat > r.hi[1] || r.lo[1] > py + dhat ||
+                                   pz - dhat > r.hi[2] || r.lo[2] > pz + dhat);
+                }
                 if (lane == k) {
                     mine = m;
                     found += __popcll(m);
@@ -640,7 +760,9 @@ unsigned grid1(int64_t n) { return (unsigned)((n + kBlock - 1) / kBlock); }
 
 Grid to_grid(const CandGrid& cg) {
     Grid g;
-    for (int d = 0; d < 3; ++d) { g.org[d] = cg.org[d]; g.n[d] = cg.n[d]; g.h[d] = cg.h[d]; }
+    for (int d = 0; d < 3; ++d) { g.org[d] = cg.org[d]; g.n[d] = cg.n[d]; g.h[d] = cg.h[d]; g.inv[d] = 1.0 / cg.h[d];
+        if (!std::isfinite(g.inv[d])) g.inv[d] = 0.0;  // every test then falls back to the division
+    }
     return g;
 }
 
@@ -730,8 +852,8 @@ hipError_t launch_cell_slots(int kind, const CandGrid& cg, const int64_t* qtoff,
     return hipGetLastError();
 }
 
-hipError_t launch_cell_pairs(int kind, bool emit, const double* x, const int32_t* vobj, const void* qrec,
-                             const void* trec, const CandGrid& cg, double dhat, const int64_t* qtoff,
+hipError_t launch_cell_pairs(int kind, bool emit, const double* x, const int32_t* vobj, const int32_t* prims,
+                             const void* rec, const CandGrid& cg, double dhat, const int64_t* qtoff,
                              const int32_t* qent, const int64_t* qeoff, const int64_t* coff, const int32_t* cent,
                              int32_t* cnt, const int64_t* eoff, const int64_t* boff, uint64_t* bal,
                              int64_t* evis, int32_t* out, hipStream_t s) {
@@ -739,22 +861,21 @@ hipError_t launch_cell_pairs(int kind, bool emit, const double* x, const int32_t
     const int64_t ncell = (int64_t)g.n[0] * g.n[1] * g.n[2];
     const unsigned nb = (unsigned)((ncell + kBlock / 64 - 1) / (kBlock / 64));
     int4* o = reinterpret_cast<int4*>(out);
-    const PrimRec* qr = static_cast<const PrimRec*>(qrec);
-    const PrimRec* tr = static_cast<const PrimRec*>(trec);
+    const PrimRec* pr = static_cast<const PrimRec*>(rec);
     unsigned long long* b = reinterpret_cast<unsigned long long*>(bal);
     if (kind == 0) {
         if (emit)
-            k_cell_pairs_pt<true><<<nb, kBlock, 0, s>>>(x, vobj, tr, g, dhat, ncell, qtoff, qent, qeoff, coff, cent,
+            k_cell_pairs_pt<true><<<nb, kBlock, 0, s>>>(x, vobj, pr, prims, g, dhat, ncell, qtoff, qent, qeoff, coff, cent,
                                                         cnt, eoff, boff, b, evis, o);
         else
-            k_cell_pairs_pt<false><<<nb, kBlock, 0, s>>>(x, vobj, tr, g, dhat, ncell, qtoff, qent, qeoff, coff, cent,
+            k_cell_pairs_pt<false><<<nb, kBlock, 0, s>>>(x, vobj, pr, prims, g, dhat, ncell, qtoff, qent, qeoff, coff, cent,
                                                          cnt, eoff, boff, b, evis, o);
     } else {
         if (emit)
-            k_cell_pairs_ee<true><<<nb, kBlock, 0, s>>>(x, vobj, qr, tr, g, dhat, ncell, qtoff, qent, qeoff, coff, cent,
+            k_cell_pairs_ee<true><<<nb, kBlock, 0, s>>>(x, vobj, pr, prims, g, dhat, ncell, qtoff, qent, qeoff, coff, cent,
                                                         cnt, eoff, boff, b, evis, o);
         else
-            k_cell_pairs_ee<false><<<nb, kBlock, 0, s>>>(x, vobj, qr, tr, g, dhat, ncell, qtoff, qent, qeoff, coff,
+            k_cell_pairs_ee<false><<<nb, kBlock, 0, s>>>(x, vobj, pr, prims, g, dhat, ncell, qtoff, qent, qeoff, coff,
                                                          cent, cnt, eoff, boff, b, evis, o);
     }
     return hipGetLastError();

@@ -492,14 +492,14 @@ hipError_t launch_qcells_fill(int kind, const double* x, int64_t nq, const void*
 // queries times primitives; kind 0: chunks of 64 triangles times points)
 hipError_t launch_cell_slots(int kind, const CandGrid& g, const int64_t* qtoff, const int64_t* coff, int64_t* n,
                              hipStream_t s);
-// per cell, its queries (qtoff/qent) against its primitives (coff/cent,
-// records trec): kind 0 points vs triangles, 1 edges vs edges of larger
+// per cell, its queries (qtoff/qent) against its primitives (coff/cent, vertex
+// ids prims, records rec): kind 0 points vs triangles, 1 edges vs edges of larger
 // index; per visit e = qeoff[q] + rank of the cell in q's walk, counts into
 // cnt[e] and hit masks into bal + boff[cell] (emit = false), or int32 [4]
 // tuples at out + 4 eoff[e] from those masks (emit = true); evis (one per
 // query-table entry) carries each visit's e from the first to the second
-hipError_t launch_cell_pairs(int kind, bool emit, const double* x, const int32_t* vobj, const void* qrec,
-                             const void* trec, const CandGrid& g, double dhat, const int64_t* qtoff,
+hipError_t launch_cell_pairs(int kind, bool emit, const double* x, const int32_t* vobj, const int32_t* prims,
+                             const void* rec, const CandGrid& g, double dhat, const int64_t* qtoff,
                              const int32_t* qent, const int64_t* qeoff, const int64_t* coff, const int32_t* cent,
                              int32_t* cnt, const int64_t* eoff, const int64_t* boff, uint64_t* bal,
                              int64_t* evis, int32_t* out, hipStream_t s);
