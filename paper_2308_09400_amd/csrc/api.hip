@@ -252,7 +252,10 @@ std::vector<DevBuf*> ctx_buffers(gipc_ctx* ctx) {
                       &ctx->contrib, &ctx->kcol, &ctx->kbeg, &ctx->ncols, &ctx->row_ptr, &ctx->col_idx, &ctx->cptr,
                       &ctx->slot_row, &ctx->diag_slot, &ctx->whead, &ctx->wrow, &ctx->maxbuf, &ctx->bigrows, &ctx->tslot, &ctx->incr, &ctx->order,
                       &ctx->obox, &ctx->ocell, &ctx->ohist, &ctx->ooff, &ctx->ofill, &ctx->rec_main, &ctx->rec_extra, &ctx->rec_a1, &ctx->ev,
-                      &ctx->epart, &ctx->mfg, &ctx->mfab, &ctx->flag, &ctx->ffr, &ctx->fev, &ctx->fpart, &ctx->cpart, &ctx->ccnt, &ctx->ccount, &ctx->cfill, &ctx->coff_t, &ctx->cent_t, &ctx->coff_e, &ctx->cent_e, &ctx->qcnt, &ctx->qoff_p, &ctx->qoff_e, &ctx->crec_t, &ctx->crec_e, &ctx->qtoff_p, &ctx->qtoff_e, &ctx->qent_p, &ctx->qent_e, &ctx->ecnt_p, &ctx->ecnt_e, &ctx->eoff_p, &ctx->eoff_e, &ctx->craw, &ctx->bslot, &ctx->boff_p, &ctx->boff_e, &ctx->bal_p, &ctx->bal_e, &ctx->evis_p, &ctx->evis_e, &ctx->vscene, &ctx->pieces, &ctx->poff,
+                      &ctx->epart, &ctx->mfg, &ctx->mfab, &ctx->flag, &ctx->ffr, &ctx->fev, &ctx->fpart, &ctx->cpart, &ctx->ccnt, &ctx->ccount, &ctx->cfill,
+                      &ctx->coff, &ctx->cent, &ctx->craw, &ctx->crec_t, &ctx->crec_e, &ctx->cspan, &ctx->cqoff,
+                      &ctx->ecnt, &ctx->eoff, &ctx->bslot, &ctx->cboff, &ctx->bal, &ctx->evis,
+                      &ctx->vscene, &ctx->pieces, &ctx->poff,
                       &ctx->r, &ctx->z, &ctx->p, &ctx->q, &ctx->p32, &ctx->minv, &ctx->part, &ctx->scal, &ctx->scan_tmp,
                       &ctx->scan_tmp2, &ctx->chk, &ctx->accd_cnt};
 }
@@ -970,107 +973,75 @@ gipc_status gipc_candidates(gipc_ctx* ctx, const gipc_mesh* mesh, const gipc_top
                     "grid of %.0f cells exceeds 2^28 (extent too large for the largest primitive plus dhat)", ncell_d);
     const int64_t ncell = (int64_t)g.n[0] * g.n[1] * g.n[2];
 
-    // four cell tables: triangles, edges (each primitive in the cells its box
-    // covers, lists sorted by id), and the point and edge queries (each in
-    // the cells its box inflated by dhat covers); counters and fills per table
-    const int64_t Q[2] = {V, E};
+    // four cell tables, one after the other: points and edges as queries (each
+    // in the cells its box inflated by dhat covers), then triangles and edges
+    // (each in the cells its box covers, lists sorted by id).  One scan per
+    // step covers all tables, so a cell's entries, a query's visits (points
+    // before edges) and a visit's candidates are numbered through.
+    const int64_t Q = (int64_t)V + E;
     CK(ensure(ctx->ccount, sizeof(int32_t) * 4 * (size_t)ncell), "alloc candidates");
     CK(ensure(ctx->cfill, sizeof(int32_t) * 4 * (size_t)ncell), "alloc candidates");
-    int32_t* cnt4 = as<int32_t>(ctx->ccount);
-    int32_t* fill4 = as<int32_t>(ctx->cfill);
-    DevBuf* toff[2] = {&ctx->coff_t, &ctx->coff_e};
-    DevBuf* tent[2] = {&ctx->cent_t, &ctx->cent_e};
-    DevBuf* trec[2] = {&ctx->crec_t, &ctx->crec_e};
-    DevBuf* qtoff[2] = {&ctx->qtoff_p, &ctx->qtoff_e};
-    DevBuf* qent[2] = {&ctx->qent_p, &ctx->qent_e};
-    DevBuf* qeoff[2] = {&ctx->qoff_p, &ctx->qoff_e};
-    DevBuf* ecnt[2] = {&ctx->ecnt_p, &ctx->ecnt_e};
-    DevBuf* eoff[2] = {&ctx->eoff_p, &ctx->eoff_e};
-    for (int k = 0; k < 2; ++k) {
-        CK(ensure(*toff[k], sizeof(int64_t) * (size_t)(ncell + 1)), "alloc candidates");
-        CK(ensure(*qtoff[k], sizeof(int64_t) * (size_t)(ncell + 1)), "alloc candidates");
-        CK(ensure(*qeoff[k], sizeof(int64_t) * (size_t)(Q[k] + 1)), "alloc candidates");
-    }
-    CK(ensure(ctx->qcnt, sizeof(int32_t) * (size_t)std::max<int64_t>(std::max<int64_t>(V, E), 1)), "alloc candidates");
+    CK(ensure(ctx->coff, sizeof(int64_t) * (size_t)(4 * ncell + 1)), "alloc candidates");
+    CK(ensure(ctx->cspan, sizeof(int32_t) * (size_t)Q), "alloc candidates");
+    CK(ensure(ctx->cqoff, sizeof(int64_t) * (size_t)(Q + 1)), "alloc candidates");
     CK(ensure(ctx->crec_t, (size_t)kPrimRecBytes * (size_t)(F > 0 ? F : 1)), "alloc candidates");
     CK(ensure(ctx->crec_e, (size_t)kPrimRecBytes * (size_t)(E > 0 ? E : 1)), "alloc candidates");
-    CK(launch_prim_records(x, topo->tris, 3, F, topo->vobj, ctx->crec_t.p, s), "triangle records");
-    CK(launch_prim_records(x, topo->edges, 2, E, topo->vobj, ctx->crec_e.p, s), "edge records");
-    // triangle entries, edge entries, point visits, edge visits, mask slots
-    // (2), then the candidates of either kind: the scans leave them side by side
+    CK(ensure(ctx->bslot, sizeof(int64_t) * 2 * (size_t)ncell), "alloc candidates");
+    CK(ensure(ctx->cboff, sizeof(int64_t) * (size_t)(2 * ncell + 1)), "alloc candidates");
+    int32_t* count4 = as<int32_t>(ctx->ccount);
+    int32_t* fill4 = as<int32_t>(ctx->cfill);
+    int64_t* off = as<int64_t>(ctx->coff);
+    int64_t* qoff = as<int64_t>(ctx->cqoff);
+    int64_t* boff = as<int64_t>(ctx->cboff);
+    CK(launch_prim_records(x, topo->tris, F, topo->edges, E, topo->vobj, ctx->crec_t.p, ctx->crec_e.p, s),
+       "primitive records");
+    // table entries, visits and mask slots, then the candidates: the scans
+    // leave the totals side by side
     int64_t* totd = as<int64_t>(ctx->ccnt);
-    CK(zero_i32(cnt4, fill4, nullptr, 4 * ncell, s), "clear");
-    CK(launch_cell_count(ctx, x, topo->tris, 3, F, g, cnt4, as<int64_t>(ctx->coff_t), totd, s), "triangle cells");
-    CK(launch_cell_count(ctx, x, topo->edges, 2, E, g, cnt4 + ncell, as<int64_t>(ctx->coff_e), totd + 1, s),
-       "edge cells");
-    for (int k = 0; k < 2; ++k) {
-        int32_t* span = as<int32_t>(ctx->qcnt);
-        CK(launch_qcells_count(k, x, Q[k], k ? ctx->crec_e.p : nullptr, g, dhat, span, cnt4 + (2 + k) * ncell, s),
-           "query cells");
-        CK((exclusive_scan<int32_t, int64_t>(cnt4 + (2 + k) * ncell, ncell, as<int64_t>(*qtoff[k]), ctx, s)), "scan");
-        CK((exclusive_scan<int32_t, int64_t>(span, Q[k], as<int64_t>(*qeoff[k]), ctx, s, totd + 2 + k)), "scan");
-    }
-    // hit-mask slots of each kind's pairs pass, per cell
-    DevBuf* boff[2] = {&ctx->boff_p, &ctx->boff_e};
-    DevBuf* bal[2] = {&ctx->bal_p, &ctx->bal_e};
-    DevBuf* evis[2] = {&ctx->evis_p, &ctx->evis_e};
-    CK(ensure(ctx->bslot, sizeof(int64_t) * (size_t)ncell), "alloc candidates");
-    for (int k = 0; k < 2; ++k) {
-        CK(ensure(*boff[k], sizeof(int64_t) * (size_t)(ncell + 1)), "alloc candidates");
-        CK(launch_cell_slots(k, g, as<int64_t>(*qtoff[k]), as<int64_t>(*toff[k]), as<int64_t>(ctx->bslot), s),
-           "mask slots");
-        CK((exclusive_scan<int64_t, int64_t>(as<int64_t>(ctx->bslot), ncell, as<int64_t>(*boff[k]), ctx, s,
-                                             totd + 4 + k)),
-           "scan");
-    }
-    int64_t tot[6];
+    CK(zero_i32(count4, fill4, nullptr, 4 * ncell, s), "clear");
+    CK(launch_cells_count(x, V, topo->tris, F, topo->edges, E, ctx->crec_e.p, g, dhat, as<int32_t>(ctx->cspan), count4,
+                          s),
+       "cell counts");
+    CK((exclusive_scan<int32_t, int64_t>(count4, 4 * ncell, off, ctx, s, totd)), "scan");
+    CK((exclusive_scan<int32_t, int64_t>(as<int32_t>(ctx->cspan), Q, qoff, ctx, s, totd + 1)), "scan");
+    CK(launch_cell_slots(g, off, as<int64_t>(ctx->bslot), s), "mask slots");
+    CK((exclusive_scan<int64_t, int64_t>(as<int64_t>(ctx->bslot), 2 * ncell, boff, ctx, s, totd + 2)), "scan");
+    int64_t tot[3];
     CK(hipMemcpyAsync(tot, totd, sizeof(tot), hipMemcpyDeviceToHost, s), "copy");
     CK(hipStreamSynchronize(s), "stream synchronize");
 
     // fills, then per query and cell visited: candidate counts, offsets
-    const int32_t* tp[2] = {topo->tris, topo->edges};
-    CK(ensure(ctx->craw, sizeof(int32_t) * (size_t)(std::max(tot[0], tot[1]) + 1)), "alloc candidates");
-    for (int k = 0; k < 2; ++k) {
-        CK(ensure(*tent[k], sizeof(int32_t) * (size_t)(tot[k] + 1)), "alloc candidates");
-        CK(ensure(*qent[k], sizeof(int32_t) * (size_t)(tot[2 + k] + 1)), "alloc candidates");
-        CK(ensure(*ecnt[k], sizeof(int32_t) * (size_t)(tot[2 + k] + 1)), "alloc candidates");
-        CK(ensure(*eoff[k], sizeof(int64_t) * (size_t)(tot[2 + k] + 1)), "alloc candidates");
-        CK(ensure(*bal[k], sizeof(uint64_t) * (size_t)(tot[4 + k] + 1)), "alloc candidates");
-        CK(ensure(*evis[k], sizeof(int64_t) * (size_t)(tot[2 + k] + 1)), "alloc candidates");
-        CK(launch_cell_fill(x, tp[k], 3 - k, k ? E : F, g, fill4 + k * ncell, as<int64_t>(*toff[k]),
-                            as<int32_t>(ctx->craw), as<int32_t>(*tent[k]), s),
-           "primitive cells");
-        CK(launch_qcells_fill(k, x, Q[k], k ? ctx->crec_e.p : nullptr, g, dhat, as<int64_t>(*qtoff[k]),
-                              fill4 + (2 + k) * ncell, as<int32_t>(*qent[k]), s),
-           "query cells");
-    }
-    for (int k = 0; k < 2; ++k) {
-        CK(launch_cell_pairs(k, false, x, topo->vobj, tp[k], trec[k]->p, g, dhat,
-                             as<int64_t>(*qtoff[k]), as<int32_t>(*qent[k]), as<int64_t>(*qeoff[k]),
-                             as<int64_t>(*toff[k]), as<int32_t>(*tent[k]), as<int32_t>(*ecnt[k]), nullptr,
-                             as<int64_t>(*boff[k]), as<uint64_t>(*bal[k]), as<int64_t>(*evis[k]), nullptr, s),
-           k ? "edge-edge count" : "point-triangle count");
-        CK((exclusive_scan<int32_t, int64_t>(as<int32_t>(*ecnt[k]), tot[2 + k], as<int64_t>(*eoff[k]), ctx, s,
-                                             totd + 6 + k)),
-           "scan");
-    }
-    int64_t nc[2];
-    CK(hipMemcpyAsync(nc, totd + 6, sizeof(nc), hipMemcpyDeviceToHost, s), "copy");
+    const int64_t nent = tot[0], nvis = tot[1];
+    CK(ensure(ctx->craw, sizeof(int32_t) * (size_t)(nent - nvis + 1)), "alloc candidates");
+    CK(ensure(ctx->cent, sizeof(int32_t) * (size_t)(nent + 1)), "alloc candidates");
+    CK(ensure(ctx->ecnt, sizeof(int32_t) * (size_t)(nvis + 1)), "alloc candidates");
+    CK(ensure(ctx->eoff, sizeof(int64_t) * (size_t)(nvis + 1)), "alloc candidates");
+    CK(ensure(ctx->bal, sizeof(uint64_t) * (size_t)(tot[2] + 1)), "alloc candidates");
+    CK(ensure(ctx->evis, sizeof(int64_t) * (size_t)(nvis + 1)), "alloc candidates");
+    CK(launch_cells_fill(x, V, topo->tris, F, topo->edges, E, ctx->crec_e.p, g, dhat, off, fill4,
+                         as<int32_t>(ctx->craw), as<int32_t>(ctx->cent), s),
+       "cell entries");
+    const auto pairs = [&](int k, bool emit) {
+        return launch_cell_pairs(k, emit, x, topo->vobj, k ? topo->edges : topo->tris, k ? ctx->crec_e.p : ctx->crec_t.p,
+                                 g, dhat, off + k * ncell, as<int32_t>(ctx->cent), qoff + (k ? (int64_t)V : 0),
+                                 off + (2 + k) * ncell, as<int32_t>(ctx->cent), as<int32_t>(ctx->ecnt),
+                                 as<int64_t>(ctx->eoff), boff + k * ncell, as<uint64_t>(ctx->bal),
+                                 as<int64_t>(ctx->evis), tuples, s);
+    };
+    CK(pairs(0, false), "point-triangle count");
+    CK(pairs(1, false), "edge-edge count");
+    CK((exclusive_scan<int32_t, int64_t>(as<int32_t>(ctx->ecnt), nvis, as<int64_t>(ctx->eoff), ctx, s, totd + 3)),
+       "scan");
+    int64_t nc;
+    CK(hipMemcpyAsync(&nc, totd + 3, sizeof(nc), hipMemcpyDeviceToHost, s), "copy");
     CK(hipStreamSynchronize(s), "stream synchronize");
-    const int64_t npt = nc[0], nee = nc[1];
-    *count = npt + nee;
+    *count = nc;
     if (!tuples) return GIPC_OK;
     if (cap < *count)
         return fail(ctx, GIPC_ERR_WORKSPACE, "cap = %lld is below the %lld candidates", (long long)cap,
                     (long long)*count);
-    for (int k = 0; k < 2; ++k) {
-        CK(launch_cell_pairs(k, true, x, topo->vobj, tp[k], trec[k]->p, g, dhat,
-                             as<int64_t>(*qtoff[k]), as<int32_t>(*qent[k]), as<int64_t>(*qeoff[k]),
-                             as<int64_t>(*toff[k]), as<int32_t>(*tent[k]), nullptr, as<int64_t>(*eoff[k]),
-                             as<int64_t>(*boff[k]), as<uint64_t>(*bal[k]), as<int64_t>(*evis[k]),
-                             tuples + (k ? 4 * npt : 0), s),
-           k ? "edge-edge emit" : "point-triangle emit");
-    }
+    CK(pairs(0, true), "point-triangle emit");
+    CK(pairs(1, true), "edge-edge emit");
     CK(hipStreamSynchronize(s), "stream synchronize");
     return GIPC_OK;
 }

@@ -11,11 +11,11 @@
 //
 //  1. bounds: per-block minima / maxima of the positions and the largest
 //     primitive extent (the host finishes the reduction and sizes the grid);
-//  2. per primitive kind, a cell table: counts (integer atomics), scan,
-//     fill, then each cell's list sorted by primitive id, so the table does
-//     not depend on the order of the atomics;
-//  3. per query kind (points, edges), a cell table of the queries whose
-//     box inflated by dhat covers the cell, in any order;
+//  2. four cell tables numbered through: of the queries (points, then edges,
+//     in the cells their box inflated by dhat covers, in any order) and of the
+//     primitives (triangles, then edges): counts, one scan, one fill;
+//  3. each primitive cell's list sorted by id, so the tables do not depend on
+//     the order of the atomics;
 //  4. one wave per cell pairing its queries with its primitives (points
 //     against triangles, edges against edges of larger index): a counting
 //     pass that also keeps the hit masks, a scan over the queries' visits
@@ -37,6 +37,13 @@ struct Grid {
 struct Box {
     d3 lo, hi;
 };
+
+struct Prims {
+    const int32_t *tris, *edges;
+    int64_t F, E;
+};
+
+__host__ __device__ __forceinline__ int64_t blocks_of(int64_t n) { return (n + kBlock - 1) / kBlock; }
 
 // one 64-byte record per primitive for the queries: its box, its vertex
 // ids and its object, that of v[0]; v[2] also tells of vertices of different
@@ -74,12 +81,6 @@ __device__ __forceinline__ double get(const d3& v, int d) { return d == 0 ? v.x 
 __device__ __forceinline__ bool overlap(const Box& a, double dhat, const Box& b) {
     return !(a.lo.x - dhat > b.hi.x || b.lo.x > a.hi.x + dhat || a.lo.y - dhat > b.hi.y || b.lo.y > a.hi.y + dhat ||
              a.lo.z - dhat > b.hi.z || b.lo.z > a.hi.z + dhat);
-}
-
-// the item of a lane, -1 past the end
-__device__ __forceinline__ int64_t item_of(int64_t n) {
-    const int64_t i = (int64_t)blockIdx.x * kBlock + threadIdx.x;
-    return i < n ? i : -1;
 }
 
 // A wave's visits of cells flattened: each lane's cells lo..hi (x slowest,
@@ -210,90 +211,6 @@ __device__ __forceinline__ void fill_visit(int64_t cell, int32_t item, bool ther
     if (there) ent[off[cell] + at + grp.rank] = item;
 }
 
-template <int NPER>
-__global__ void __launch_bounds__(kBlock) k_cell_count_prims(const double* __restrict__ X,
-                                                             const int32_t* __restrict__ prims, int64_t n, Grid g,
-                                                             int32_t* __restrict__ count) {
-    const int64_t i0 = item_of(n);
-    const bool valid = i0 >= 0;
-    const int64_t i = valid ? i0 : 0;
-    const Box b = prim_box(X, prims + NPER * i, NPER);
-    int lo[3], hi[3];
-    for (int d = 0; d < 3; ++d) {
-        lo[d] = cell_of(get(b.lo, d), g, d);
-        hi[d] = cell_of(get(b.hi, d), g, d);
-    }
-    __shared__ uint32_t tab[kBlock / 64][kGroupSlots];
-    const auto vcell = [&](int a, int c, int e) { return ((int64_t)a * g.n[1] + c) * g.n[2] + e; };
-    wave_visits(lo, hi, valid, (int32_t)i, vcell, [&](int64_t cell, int32_t, bool there) {
-        count_visit(cell, there, count, tab[threadIdx.x >> 6]);
-    });
-}
-
-template <int NPER>
-__global__ void __launch_bounds__(kBlock) k_cell_fill_prims(const double* __restrict__ X,
-                                                            const int32_t* __restrict__ prims, int64_t n, Grid g,
-                                                            const int64_t* __restrict__ off,
-                                                            int32_t* __restrict__ fill, int32_t* __restrict__ ent) {
-    const int64_t i0 = item_of(n);
-    const bool valid = i0 >= 0;
-    const int64_t i = valid ? i0 : 0;
-    const Box b = prim_box(X, prims + NPER * i, NPER);
-    int lo[3], hi[3];
-    for (int d = 0; d < 3; ++d) {
-        lo[d] = cell_of(get(b.lo, d), g, d);
-        hi[d] = cell_of(get(b.hi, d), g, d);
-    }
-    __shared__ uint32_t tab[kBlock / 64][kGroupSlots];
-    const auto vcell = [&](int a, int c, int e) { return ((int64_t)a * g.n[1] + c) * g.n[2] + e; };
-    wave_visits(lo, hi, valid, (int32_t)i, vcell, [&](int64_t cell, int32_t item, bool there) {
-        fill_visit(cell, item, there, off, fill, ent, tab[threadIdx.x >> 6]);
-    });
-}
-
-template <int NPER>
-__global__ void __launch_bounds__(kBlock) k_prim_records(const double* __restrict__ X,
-                                                         const int32_t* __restrict__ prims, int64_t n,
-                                                         const int32_t* __restrict__ vobj,
-                                                         PrimRec* __restrict__ rec) {
-    const int64_t i = (int64_t)blockIdx.x * kBlock + threadIdx.x;
-    if (i >= n) return;
-    const int32_t* v = prims + NPER * i;
-    const Box b = prim_box(X, v, NPER);
-    PrimRec r;
-    r.lo[0] = b.lo.x; r.lo[1] = b.lo.y; r.lo[2] = b.lo.z;
-    r.hi[0] = b.hi.x; r.hi[1] = b.hi.y; r.hi[2] = b.hi.z;
-    r.v[0] = v[0]; r.v[1] = v[1]; const bool mixed = vobj[v[0]] != vobj[v[1]] || (NPER == 3 && vobj[v[0]] != vobj[v[NPER - 1]]);
-    r.v[2] = NPER == 3 ? (mixed ? ~v[2] : v[2]) : mixed;
-    r.obj = vobj[v[0]];
-    rec[i] = r;
-}
-
-// each cell's list in increasing primitive id, one wave per cell: an entry's
-// place is the number of entries of the cell below it (the ids of a cell
-// are distinct), counted against the others handed over by lane reads;
-// raw -> ent
-__global__ void __launch_bounds__(kBlock) k_cell_sort(int64_t ncell, const int64_t* __restrict__ off,
-                                                      const int32_t* __restrict__ raw,
-                                                      int32_t* __restrict__ ent) {
-    const int lane = threadIdx.x & 63;
-    const int64_t c =
-        (int64_t)blockIdx.x * (kBlock / 64) + __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
-    if (c >= ncell) return;
-    const int64_t b = off[c], n = off[c + 1] - b;
-    for (int64_t c0 = 0; c0 < n; c0 += 64) {
-        const bool mine_ok = c0 + lane < n;
-        const int32_t mine = mine_ok ? raw[b + c0 + lane] : 0;
-        int rank = 0;
-        for (int64_t c1 = 0; c1 < n; c1 += 64) {
-            const int32_t other = c1 + lane < n ? raw[b + c1 + lane] : 0;
-            const int m = (int)(n - c1 < 64 ? n - c1 : 64);
-            for (int k = 0; k < m; ++k) rank += __builtin_amdgcn_readlane(other, k) < mine;
-        }
-        if (mine_ok) ent[b + rank] = mine;
-    }
-}
-
 // The queries' side, one record per query primitive: KIND 0 = points (their
 // position, a zero-size box), 1 = edges (their 64-byte record).
 template <int KIND>
@@ -320,49 +237,131 @@ __device__ __forceinline__ void query_cells(const Box& qb, const Grid& g, double
     }
 }
 
-// query table, counting: span[q] = cells the query covers, count[cell] +=
-// queries covering the cell
-template <int KIND>
-__global__ void __launch_bounds__(kBlock) k_qcells_count(const double* __restrict__ X, int64_t nq,
-                                                         const PrimRec* __restrict__ qrec, Grid g, double dhat,
-                                                         int32_t* __restrict__ span, int32_t* __restrict__ count) {
-    const int64_t qi = item_of(nq);
-    const bool valid = qi >= 0;
-    const int64_t q = valid ? qi : 0;
-    Box qb;
-    int32_t q0, q1, qo;
-    query_of<KIND>(q, X, nullptr, qrec, qb, q0, q1, qo);
+template <int NPER>
+__device__ __forceinline__ void prim_record(const double* __restrict__ X, const int32_t* __restrict__ v,
+                                            const int32_t* __restrict__ vobj, PrimRec* __restrict__ rec) {
+    const Box b = prim_box(X, v, NPER);
+    PrimRec r;
+    r.lo[0] = b.lo.x; r.lo[1] = b.lo.y; r.lo[2] = b.lo.z;
+    r.hi[0] = b.hi.x; r.hi[1] = b.hi.y; r.hi[2] = b.hi.z;
+    const bool mixed = vobj[v[0]] != vobj[v[1]] || (NPER == 3 && vobj[v[0]] != vobj[v[NPER - 1]]);
+    r.v[0] = v[0]; r.v[1] = v[1];
+    r.v[2] = NPER == 3 ? (mixed ? ~v[2] : v[2]) : mixed;
+    r.obj = vobj[v[0]];
+    *rec = r;
+}
+
+// workgroups of the triangles first, then of the edges
+__global__ void __launch_bounds__(kBlock) k_prim_records(const double* __restrict__ X, Prims pr,
+                                                         const int32_t* __restrict__ vobj,
+                                                         PrimRec* __restrict__ trec, PrimRec* __restrict__ erec) {
+    const int64_t nt = blocks_of(pr.F);
+    const bool tri = (int64_t)blockIdx.x < nt;
+    const int64_t i = ((int64_t)blockIdx.x - (tri ? 0 : nt)) * kBlock + threadIdx.x;
+    if (i >= (tri ? pr.F : pr.E)) return;
+    if (tri) prim_record<3>(X, pr.tris + 3 * i, vobj, trec + i);
+    else prim_record<2>(X, pr.edges + 2 * i, vobj, erec + i);
+}
+
+// The four cell tables in one: the queries' (points and edges, by their boxes
+// inflated by dhat), then the primitives' (triangles and edges), table t's
+// cells at t ncell.  A launch's workgroups go through the points, the edges
+// as queries, the triangles and the edges as primitives; this is a lane's
+// item: its table, its number and the cells it covers.  One launch and one scan
+// per step for all tables: on small scenes, which are bound by launches,
+// 19 fewer of 48 (two 16 x 16 sheets, a Newton step: 725 -> 655 us; three
+// 101 x 101: 1250 -> 1150 us).
+struct Item {
+    int table;
+    int64_t i;
+    bool valid;
     int lo[3], hi[3];
-    query_cells(qb, g, dhat, lo, hi);
-    if (valid) span[q] = (hi[0] - lo[0] + 1) * (hi[1] - lo[1] + 1) * (hi[2] - lo[2] + 1);
+};
+
+__device__ __forceinline__ Item item_cells(const double* __restrict__ X, int64_t V, const Prims& pr,
+                                           const PrimRec* __restrict__ erec, const Grid& g, double dhat) {
+    Item it;
+    const int64_t n[4] = {V, pr.E, pr.F, pr.E};
+    int64_t b = blockIdx.x;
+    it.table = 0;
+    while (it.table < 3 && b >= blocks_of(n[it.table])) b -= blocks_of(n[it.table++]);
+    const int64_t i = b * kBlock + threadIdx.x;
+    it.valid = i < n[it.table];
+    it.i = it.valid ? i : 0;
+    Box box;
+    if (it.table == 0) {
+        box.lo = box.hi = ld3(X, (int)it.i);
+    } else if (it.table == 2) {
+        box = prim_box(X, pr.tris + 3 * it.i, 3);
+    } else {
+        const PrimRec& r = erec[it.i];
+        box.lo = mk(r.lo[0], r.lo[1], r.lo[2]);
+        box.hi = mk(r.hi[0], r.hi[1], r.hi[2]);
+    }
+    query_cells(box, g, it.table < 2 ? dhat : 0.0, it.lo, it.hi);
+    return it;
+}
+
+// count[table ncell + cell] += items covering the cell; span[query] = cells
+// the query covers (points first, then edges)
+__global__ void __launch_bounds__(kBlock) k_cells_count(const double* __restrict__ X, int64_t V, Prims pr,
+                                                        const PrimRec* __restrict__ erec, Grid g, double dhat,
+                                                        int32_t* __restrict__ span, int32_t* __restrict__ count) {
     __shared__ uint32_t tab[kBlock / 64][kGroupSlots];
+    const Item it = item_cells(X, V, pr, erec, g, dhat);
+    if (it.valid && it.table < 2)
+        span[(it.table ? V : 0) + it.i] =
+            (it.hi[0] - it.lo[0] + 1) * (it.hi[1] - it.lo[1] + 1) * (it.hi[2] - it.lo[2] + 1);
+    count += it.table * ((int64_t)g.n[0] * g.n[1] * g.n[2]);
     const auto vcell = [&](int a, int c, int e) { return ((int64_t)a * g.n[1] + c) * g.n[2] + e; };
-    wave_visits(lo, hi, valid, (int32_t)q, vcell, [&](int64_t cell, int32_t, bool there) {
-        count_visit(cell, there, count, tab[threadIdx.x >> 6]);
+    wave_visits(it.lo, it.hi, it.valid, (int32_t)it.i, vcell,
+                [&](int64_t cell, int32_t, bool there) { count_visit(cell, there, count, tab[threadIdx.x >> 6]); });
+}
+
+// the items covering each cell, in no particular order: queries into ent
+// (output positions come from the query and the cell, not from this order),
+// primitives into raw, which lacks the queries' part
+__global__ void __launch_bounds__(kBlock) k_cells_fill(const double* __restrict__ X, int64_t V, Prims pr,
+                                                       const PrimRec* __restrict__ erec, Grid g, double dhat,
+                                                       const int64_t* __restrict__ off, int32_t* __restrict__ fill,
+                                                       int32_t* __restrict__ raw, int32_t* __restrict__ ent) {
+    __shared__ uint32_t tab[kBlock / 64][kGroupSlots];
+    const Item it = item_cells(X, V, pr, erec, g, dhat);
+    const int64_t ncell = (int64_t)g.n[0] * g.n[1] * g.n[2];
+    int32_t* to = it.table < 2 ? ent : raw - off[2 * ncell];
+    off += it.table * ncell;
+    fill += it.table * ncell;
+    const auto vcell = [&](int a, int c, int e) { return ((int64_t)a * g.n[1] + c) * g.n[2] + e; };
+    wave_visits(it.lo, it.hi, it.valid, (int32_t)it.i, vcell, [&](int64_t cell, int32_t item, bool there) {
+        fill_visit(cell, item, there, off, fill, to, tab[threadIdx.x >> 6]);
     });
 }
 
-// query table, filling: the queries covering each cell, in no particular
-// order (the output positions come from the query and the cell, not from
-// this order)
-template <int KIND>
-__global__ void __launch_bounds__(kBlock) k_qcells_fill(const double* __restrict__ X, int64_t nq,
-                                                        const PrimRec* __restrict__ qrec, Grid g, double dhat,
-                                                        const int64_t* __restrict__ off, int32_t* __restrict__ fill,
-                                                        int32_t* __restrict__ ent) {
-    const int64_t qi = item_of(nq);
-    const bool valid = qi >= 0;
-    const int64_t q = valid ? qi : 0;
-    Box qb;
-    int32_t q0, q1, qo;
-    query_of<KIND>(q, X, nullptr, qrec, qb, q0, q1, qo);
-    int lo[3], hi[3];
-    query_cells(qb, g, dhat, lo, hi);
-    __shared__ uint32_t tab[kBlock / 64][kGroupSlots];
-    const auto vcell = [&](int a, int c, int e) { return ((int64_t)a * g.n[1] + c) * g.n[2] + e; };
-    wave_visits(lo, hi, valid, (int32_t)q, vcell, [&](int64_t cell, int32_t item, bool there) {
-        fill_visit(cell, item, there, off, fill, ent, tab[threadIdx.x >> 6]);
-    });
+// each cell's list in increasing primitive id, one wave per cell: an entry's
+// place is the number of entries of the cell below it (the ids of a cell
+// are distinct), counted against the others handed over by lane reads;
+// raw (which starts at the first cell's entry) -> ent; ncell = cells of both
+// primitive tables
+__global__ void __launch_bounds__(kBlock) k_cell_sort(int64_t ncell, const int64_t* __restrict__ off,
+                                                      const int32_t* __restrict__ raw,
+                                                      int32_t* __restrict__ ent) {
+    const int lane = threadIdx.x & 63;
+    const int64_t c =
+        (int64_t)blockIdx.x * (kBlock / 64) + __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
+    if (c >= ncell) return;
+    const int64_t b = off[c], n = off[c + 1] - b;
+    raw -= off[0];
+    for (int64_t c0 = 0; c0 < n; c0 += 64) {
+        const bool mine_ok = c0 + lane < n;
+        const int32_t mine = mine_ok ? raw[b + c0 + lane] : 0;
+        int rank = 0;
+        for (int64_t c1 = 0; c1 < n; c1 += 64) {
+            const int32_t other = c1 + lane < n ? raw[b + c1 + lane] : 0;
+            const int m = (int)(n - c1 < 64 ? n - c1 : 64);
+            for (int k = 0; k < m; ++k) rank += __builtin_amdgcn_readlane(other, k) < mine;
+        }
+        if (mine_ok) ent[b + rank] = mine;
+    }
 }
 
 // a lane's 64-bit value, read by every lane (k wave-uniform)
@@ -745,15 +744,15 @@ k_cell_pairs_pt(const double* __restrict__ X, const int32_t* __restrict__ vobj, 
     }
 }
 
-// per cell, the hit-mask slots of its pairs pass: one per chunk of 64
-// queries and primitive of the cell, or (by_points, the point-triangle
-// pass) one per chunk of 64 triangles and point of the cell
-__global__ void __launch_bounds__(kBlock) k_cell_slots(int64_t ncell, int by_points, const int64_t* __restrict__ qtoff,
-                                                       const int64_t* __restrict__ coff, int64_t* __restrict__ n) {
+// per cell, the hit-mask slots of its pairs passes: of the point-triangle
+// pass (one per chunk of 64 triangles and point of the cell) at c, of the
+// edge-edge pass (one per chunk of 64 queries and edge) at ncell + c
+__global__ void __launch_bounds__(kBlock) k_cell_slots(int64_t ncell, const int64_t* __restrict__ off,
+                                                       int64_t* __restrict__ n) {
     const int64_t c = (int64_t)blockIdx.x * kBlock + threadIdx.x;
-    if (c >= ncell) return;
-    const int64_t nq = qtoff[c + 1] - qtoff[c], nt = coff[c + 1] - coff[c];
-    n[c] = by_points ? ((nt + 63) >> 6) * nq : ((nq + 63) >> 6) * nt;
+    if (c >= 2 * ncell) return;
+    const int64_t nq = off[c + 1] - off[c], nt = off[2 * ncell + c + 1] - off[2 * ncell + c];
+    n[c] = c < ncell ? ((nt + 63) >> 6) * nq : ((nq + 63) >> 6) * nt;
 }
 
 unsigned grid1(int64_t n) { return (unsigned)((n + kBlock - 1) / kBlock); }
@@ -788,67 +787,44 @@ hipError_t launch_cand_check(int32_t V, const int32_t* vobj, const int32_t* tris
     return hipGetLastError();
 }
 
-hipError_t launch_cell_count(gipc_ctx* ctx, const double* x, const int32_t* prims, int nper, int64_t n,
-                             const CandGrid& cg, int32_t* count, int64_t* off, int64_t* total, hipStream_t s) {
+hipError_t launch_prim_records(const double* x, const int32_t* tris, int64_t F, const int32_t* edges, int64_t E,
+                               const int32_t* vobj, void* trec, void* erec, hipStream_t s) {
+    const int64_t nb = blocks_of(F) + blocks_of(E);
+    if (nb == 0) return hipSuccess;
+    k_prim_records<<<(unsigned)nb, kBlock, 0, s>>>(x, Prims{tris, edges, F, E}, vobj, static_cast<PrimRec*>(trec),
+                                                   static_cast<PrimRec*>(erec));
+    return hipGetLastError();
+}
+
+hipError_t launch_cells_count(const double* x, int32_t V, const int32_t* tris, int64_t F, const int32_t* edges,
+                              int64_t E, const void* erec, const CandGrid& cg, double dhat, int32_t* span,
+                              int32_t* count, hipStream_t s) {
+    const int64_t nb = blocks_of(V) + blocks_of(F) + 2 * blocks_of(E);
+    if (nb == 0) return hipSuccess;
+    k_cells_count<<<(unsigned)nb, kBlock, 0, s>>>(x, V, Prims{tris, edges, F, E}, static_cast<const PrimRec*>(erec),
+                                                  to_grid(cg), dhat, span, count);
+    return hipGetLastError();
+}
+
+hipError_t launch_cells_fill(const double* x, int32_t V, const int32_t* tris, int64_t F, const int32_t* edges,
+                             int64_t E, const void* erec, const CandGrid& cg, double dhat, const int64_t* off,
+                             int32_t* fill, int32_t* raw, int32_t* ent, hipStream_t s) {
     const Grid g = to_grid(cg);
     const int64_t ncell = (int64_t)g.n[0] * g.n[1] * g.n[2];
-    if (n > 0) {
-        if (nper == 3) k_cell_count_prims<3><<<grid1(n), kBlock, 0, s>>>(x, prims, n, g, count);
-        else k_cell_count_prims<2><<<grid1(n), kBlock, 0, s>>>(x, prims, n, g, count);
-        hipError_t e = hipGetLastError();
-        if (e != hipSuccess) return e;
-    }
-    return exclusive_scan<int32_t, int64_t>(count, ncell, off, ctx, s, total);
-}
-
-hipError_t launch_cell_fill(const double* x, const int32_t* prims, int nper, int64_t n, const CandGrid& cg,
-                            int32_t* fill, const int64_t* off, int32_t* raw, int32_t* ent, hipStream_t s) {
-    const Grid g = to_grid(cg);
-    const int64_t ncell = (int64_t)g.n[0] * g.n[1] * g.n[2];
-    if (n > 0) {
-        if (nper == 3) k_cell_fill_prims<3><<<grid1(n), kBlock, 0, s>>>(x, prims, n, g, off, fill, raw);
-        else k_cell_fill_prims<2><<<grid1(n), kBlock, 0, s>>>(x, prims, n, g, off, fill, raw);
-        hipError_t e = hipGetLastError();
-        if (e != hipSuccess) return e;
-    }
-    k_cell_sort<<<(unsigned)((ncell + kBlock / 64 - 1) / (kBlock / 64)), kBlock, 0, s>>>(ncell, off, raw, ent);
+    const int64_t nb = blocks_of(V) + blocks_of(F) + 2 * blocks_of(E);
+    if (nb == 0) return hipSuccess;
+    k_cells_fill<<<(unsigned)nb, kBlock, 0, s>>>(x, V, Prims{tris, edges, F, E}, static_cast<const PrimRec*>(erec),
+                                                 g, dhat, off, fill, raw, ent);
+    hipError_t e = hipGetLastError();
+    if (e != hipSuccess) return e;
+    k_cell_sort<<<(unsigned)((2 * ncell + kBlock / 64 - 1) / (kBlock / 64)), kBlock, 0, s>>>(
+        2 * ncell, off + 2 * ncell, raw, ent);
     return hipGetLastError();
 }
 
-hipError_t launch_prim_records(const double* x, const int32_t* prims, int nper, int64_t n, const int32_t* vobj,
-                               void* rec, hipStream_t s) {
-    if (n == 0) return hipSuccess;
-    if (nper == 3)
-        k_prim_records<3><<<grid1(n), kBlock, 0, s>>>(x, prims, n, vobj, static_cast<PrimRec*>(rec));
-    else
-        k_prim_records<2><<<grid1(n), kBlock, 0, s>>>(x, prims, n, vobj, static_cast<PrimRec*>(rec));
-    return hipGetLastError();
-}
-
-hipError_t launch_qcells_count(int kind, const double* x, int64_t nq, const void* qrec, const CandGrid& cg,
-                               double dhat, int32_t* span, int32_t* count, hipStream_t s) {
-    if (nq == 0) return hipSuccess;
-    const Grid g = to_grid(cg);
-    const PrimRec* qr = static_cast<const PrimRec*>(qrec);
-    if (kind == 0) k_qcells_count<0><<<grid1(nq), kBlock, 0, s>>>(x, nq, qr, g, dhat, span, count);
-    else k_qcells_count<1><<<grid1(nq), kBlock, 0, s>>>(x, nq, qr, g, dhat, span, count);
-    return hipGetLastError();
-}
-
-hipError_t launch_qcells_fill(int kind, const double* x, int64_t nq, const void* qrec, const CandGrid& cg,
-                              double dhat, const int64_t* off, int32_t* fill, int32_t* ent, hipStream_t s) {
-    if (nq == 0) return hipSuccess;
-    const Grid g = to_grid(cg);
-    const PrimRec* qr = static_cast<const PrimRec*>(qrec);
-    if (kind == 0) k_qcells_fill<0><<<grid1(nq), kBlock, 0, s>>>(x, nq, qr, g, dhat, off, fill, ent);
-    else k_qcells_fill<1><<<grid1(nq), kBlock, 0, s>>>(x, nq, qr, g, dhat, off, fill, ent);
-    return hipGetLastError();
-}
-
-hipError_t launch_cell_slots(int kind, const CandGrid& cg, const int64_t* qtoff, const int64_t* coff, int64_t* n,
-                             hipStream_t s) {
+hipError_t launch_cell_slots(const CandGrid& cg, const int64_t* off, int64_t* n, hipStream_t s) {
     const int64_t ncell = (int64_t)cg.n[0] * cg.n[1] * cg.n[2];
-    k_cell_slots<<<grid1(ncell), kBlock, 0, s>>>(ncell, kind == 0, qtoff, coff, n);
+    k_cell_slots<<<(unsigned)blocks_of(2 * ncell), kBlock, 0, s>>>(ncell, off, n);
     return hipGetLastError();
 }
 

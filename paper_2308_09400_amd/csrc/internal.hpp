@@ -285,10 +285,10 @@ struct gipc_ctx {
     // lagged friction: per-pair lag and eval records, energy shares and
     // pieces; the build it was lagged for and eps_v dt
     gipc::DevBuf flag, ffr, fev, fpart;
-    // contact candidates: bounds partials, counters, cell tables (points
-    // against triangles, edges against edges), per-query counts and offsets
-    gipc::DevBuf cpart, ccnt, ccount, cfill, coff_t, cent_t, coff_e, cent_e, qcnt, qoff_p, qoff_e, crec_t, crec_e;
-    gipc::DevBuf qtoff_p, qtoff_e, qent_p, qent_e, ecnt_p, ecnt_e, eoff_p, eoff_e, craw, bslot, boff_p, boff_e, bal_p, bal_e, evis_p, evis_e;
+    // contact candidates: bounds partials, counters, cell tables, primitive
+    // records, per query its cells, per visit its candidates, hit masks
+    gipc::DevBuf cpart, ccnt, ccount, cfill, coff, cent, craw, crec_t, crec_e, cspan, cqoff, ecnt, eoff, bslot, cboff,
+        bal, evis;
     uint64_t fric_gen = 0;
     double fric_sv = 0.0;
     uint64_t eval_gen = 0;   // bumped by every eval
@@ -469,29 +469,26 @@ hipError_t launch_cand_bounds(const double* x, int32_t V, const int32_t* tris, i
                               int64_t E, double* part, int32_t nb, hipStream_t s);
 hipError_t launch_cand_check(int32_t V, const int32_t* vobj, const int32_t* tris, int64_t F, const int32_t* edges,
                              int64_t E, int64_t* counters, hipStream_t s);
-// cell table of n primitives of nper vertices: counts (zero on entry; total
-// receives their sum) and offsets off
-// [ncell+1] (off[ncell] = entries), then the entries ent [off[ncell]],
-// each cell's in increasing id (raw [off[ncell]]: unsorted, scratch)
-hipError_t launch_cell_count(gipc_ctx* ctx, const double* x, const int32_t* prims, int nper, int64_t n,
-                             const CandGrid& g, int32_t* count, int64_t* off, int64_t* total, hipStream_t s);
-hipError_t launch_cell_fill(const double* x, const int32_t* prims, int nper, int64_t n, const CandGrid& g,
-                            int32_t* fill, const int64_t* off, int32_t* raw, int32_t* ent, hipStream_t s);
-// 64-byte query records of n primitives (box, vertex ids, object)
+// 64-byte records of the triangles and edges (box, vertex ids, object)
 constexpr int kPrimRecBytes = 64;
-hipError_t launch_prim_records(const double* x, const int32_t* prims, int nper, int64_t n, const int32_t* vobj,
-                               void* rec, hipStream_t s);
-// query tables, kind 0: points, 1: edge records (qrec): span[q] = cells
-// the query's box inflated by dhat covers, count[cell] += queries covering
-// it; then the queries of each cell at ent + off[cell]
-hipError_t launch_qcells_count(int kind, const double* x, int64_t nq, const void* qrec, const CandGrid& g,
-                               double dhat, int32_t* span, int32_t* count, hipStream_t s);
-hipError_t launch_qcells_fill(int kind, const double* x, int64_t nq, const void* qrec, const CandGrid& g,
-                              double dhat, const int64_t* off, int32_t* fill, int32_t* ent, hipStream_t s);
-// n[cell] = hit-mask slots of the cell's pairs pass (kind 1: chunks of 64
-// queries times primitives; kind 0: chunks of 64 triangles times points)
-hipError_t launch_cell_slots(int kind, const CandGrid& g, const int64_t* qtoff, const int64_t* coff, int64_t* n,
-                             hipStream_t s);
+hipError_t launch_prim_records(const double* x, const int32_t* tris, int64_t F, const int32_t* edges, int64_t E,
+                               const int32_t* vobj, void* trec, void* erec, hipStream_t s);
+// the cell tables of points and edges as queries (inflated by dhat), of
+// triangles and of edges, one after the other: counts [4 ncell] (zero on
+// entry) and the queries' numbers of cells span [V + E], then with the scanned
+// counts off [4 ncell + 1] the entries ent [off[4 ncell]], a primitive
+// table's in increasing id (raw [off[4 ncell] - off[2 ncell]]: scratch, fill
+// [4 ncell]: zero on entry)
+hipError_t launch_cells_count(const double* x, int32_t V, const int32_t* tris, int64_t F, const int32_t* edges,
+                              int64_t E, const void* erec, const CandGrid& g, double dhat, int32_t* span,
+                              int32_t* count, hipStream_t s);
+hipError_t launch_cells_fill(const double* x, int32_t V, const int32_t* tris, int64_t F, const int32_t* edges,
+                             int64_t E, const void* erec, const CandGrid& g, double dhat, const int64_t* off,
+                             int32_t* fill, int32_t* raw, int32_t* ent, hipStream_t s);
+// n [2 ncell]: hit-mask slots of the cells' point-triangle passes (chunks of
+// 64 triangles times points), then of their edge-edge passes (chunks of 64
+// queries times edges)
+hipError_t launch_cell_slots(const CandGrid& g, const int64_t* off, int64_t* n, hipStream_t s);
 // per cell, its queries (qtoff/qent) against its primitives (coff/cent, vertex
 // ids prims, records rec): kind 0 points vs triangles, 1 edges vs edges of larger
 // index; per visit e = qeoff[q] + rank of the cell in q's walk, counts into
