@@ -79,12 +79,8 @@ enum {
 
 // every build counter to zero, the "first index" slots to all ones (so an
 // atomic minimum over the flagged indices gives the first one)
-__global__ void k_reset_counters(int64_t* __restrict__ cnt) {
-    const int i = threadIdx.x;
-    if (i >= C_NSLOTS) return;
-    const bool first = i == C_FIRST_BAD || i == C_FIRST_DEG || i == C_FIRST_DPRIM || i == C_FIRST_SPAN;
-    cnt[i] = first ? -1 : 0;
-}
+constexpr uint64_t kCountersOnes = (1ull << C_FIRST_BAD) | (1ull << C_FIRST_DEG) | (1ull << C_FIRST_DPRIM) |
+                                   (1ull << C_FIRST_SPAN);
 
 gipc_status fail(gipc_ctx* ctx, gipc_status st, const char* fmt, ...) {
     if (ctx) {
@@ -356,8 +352,12 @@ gipc_status gipc_pairs_build(gipc_ctx* ctx, const gipc_mesh* mesh, const gipc_pa
     CK(ensure(ctx->st_vid, sizeof(int4) * (size_t)P), "alloc staged pairs");
     CK(ensure(ctx->st_src, sizeof(int32_t) * (size_t)P), "alloc staged pairs");
     int64_t* cnt = as<int64_t>(ctx->counters);
-    k_reset_counters<<<1, 64, 0, s>>>(cnt);
-    CK(hipGetLastError(), "clear counters");
+    const size_t Vs = (size_t)(V > 0 ? V : 1);
+    CK(ensure(ctx->fill, sizeof(uint64_t) * Vs), "alloc pattern");
+    ZeroList zero;  // with the pattern's counts and the row order's buckets
+    zero.p[0] = as<int32_t>(ctx->fill), zero.n[0] = 2 * (int64_t)Vs;
+    CK(row_order_tables(ctx, V, Sc, zero, 1), "row order");
+    CK(zero_i32(zero, s, cnt, C_NSLOTS, kCountersOnes), "clear counters");
     if (P > 0) {
         CK(launch_stage_classify(pairs->tuples, P, V, mesh->x, xr, pm, as<uint8_t>(ctx->cand_ft),
                                  as<int4>(ctx->cand_vid), as<int32_t>(ctx->bcount), cnt, s),
@@ -366,9 +366,8 @@ gipc_status gipc_pairs_build(gipc_ctx* ctx, const gipc_mesh* mesh, const gipc_pa
                                              cnt + C_ACTIVE)),
            "stage scan");
         CK(launch_stage_scatter(as<uint8_t>(ctx->cand_ft), as<int4>(ctx->cand_vid), P, as<int64_t>(ctx->boff),
-                                as<int4>(ctx->st_vid), as<int32_t>(ctx->st_src), s),
+                                as<int4>(ctx->st_vid), as<int32_t>(ctx->st_src), cnt + C_OFF, s),
            "stage scatter");
-        CK(launch_stage_offsets(as<int64_t>(ctx->boff), nb, cnt + C_OFF, s), "stage offsets");
     }
     int64_t hc[C_NSLOTS] = {0};
     if ((st = read_counters(ctx, hc, 0, C_NSLOTS, s)) != GIPC_OK) return st;
@@ -396,17 +395,14 @@ gipc_status gipc_pairs_build(gipc_ctx* ctx, const gipc_mesh* mesh, const gipc_pa
     if (Ps >= (int64_t(1) << 28)) return fail(ctx, GIPC_ERR_WORKSPACE, "more than 2^28 staged pairs (%lld)", (long long)Ps);
 
     // ---- symbolic
-    const size_t Vs = (size_t)(V > 0 ? V : 1);
     CK(ensure(ctx->deg, sizeof(int32_t) * Vs), "alloc pattern");
     CK(ensure(ctx->kcount, sizeof(int32_t) * Vs), "alloc pattern");
-    CK(ensure(ctx->fill, sizeof(uint64_t) * Vs), "alloc pattern");
     CK(ensure(ctx->st_vid2, sizeof(int4) * (size_t)(Ps > 0 ? Ps : 1)), "alloc pattern");  // places (free here)
     CK(ensure(ctx->inc_ptr, sizeof(int64_t) * (Vs + 1)), "alloc pattern");
     CK(ensure(ctx->kptr, sizeof(int64_t) * (Vs + 1)), "alloc pattern");
     CK(ensure(ctx->ncols, sizeof(int32_t) * Vs), "alloc pattern");
     CK(ensure(ctx->row_ptr, sizeof(int32_t) * (Vs + 1)), "alloc pattern");
     CK(ensure(ctx->diag_slot, sizeof(int32_t) * Vs), "alloc pattern");
-    CK(zero_i32(as<int32_t>(ctx->fill), nullptr, nullptr, 2 * (int64_t)Vs, s), "clear pattern");
     CK(launch_sym_count(as<int4>(ctx->st_vid), tr, V, as<unsigned long long>(ctx->fill), as<int4>(ctx->st_vid2),
                         as<int32_t>(ctx->deg), as<int32_t>(ctx->kcount), reinterpret_cast<int32_t*>(cnt + C_MAXDEG),
                         s),
@@ -998,7 +994,10 @@ gipc_status gipc_candidates(gipc_ctx* ctx, const gipc_mesh* mesh, const gipc_top
     // table entries, visits and mask slots, then the candidates: the scans
     // leave the totals side by side
     int64_t* totd = as<int64_t>(ctx->ccnt);
-    CK(zero_i32(count4, fill4, nullptr, 4 * ncell, s), "clear");
+    ZeroList zero;
+    zero.p[0] = count4, zero.n[0] = 4 * ncell;
+    zero.p[1] = fill4, zero.n[1] = 4 * ncell;
+    CK(zero_i32(zero, s), "clear");
     CK(launch_cells_count(x, V, topo->tris, F, topo->edges, E, ctx->crec_e.p, g, dhat, as<int32_t>(ctx->cspan), count4,
                           s),
        "cell counts");

@@ -317,8 +317,14 @@ namespace gipc {
 template <typename TIn, typename TOut>
 hipError_t exclusive_scan(const TIn* in, int64_t n, TOut* out, gipc_ctx* ctx, hipStream_t s,
                           int64_t* total_dev = nullptr);
-// zeroes a[0..n), and b and c when not null, in one launch
-hipError_t zero_i32(int32_t* a, int32_t* b, int32_t* c, int64_t n, hipStream_t s);
+// zeroes up to four int32 arrays in one launch and, with counters, sets its
+// slots i < nslots to -1 where bit i of ones is set and to 0 otherwise
+struct ZeroList {
+    int32_t* p[4] = {nullptr, nullptr, nullptr, nullptr};
+    int64_t n[4] = {0, 0, 0, 0};
+};
+hipError_t zero_i32(const ZeroList& z, hipStream_t s, int64_t* counters = nullptr, int nslots = 0,
+                    uint64_t ones = 0);
 
 // ---- stage.hip
 hipError_t launch_vertex_scene(const int32_t* vert_off, int32_t S, int32_t V, int32_t* vscene, hipStream_t s);
@@ -326,7 +332,7 @@ hipError_t launch_stage_classify(const int32_t* tuples, int64_t P, int32_t V, co
                                  const DevParams& pm, uint8_t* ft, int4* vid, int32_t* bcount, int64_t* counters,
                                  hipStream_t s);
 hipError_t launch_stage_scatter(const uint8_t* ft, const int4* vid, int64_t P, const int64_t* boff, int4* st_vid,
-                                int32_t* st_src, hipStream_t s);
+                                int32_t* st_src, int64_t* type_off, hipStream_t s);
 // the build's classification (ft_b, vid_b) against the one at x; counters
 // (device int64 [kCheckCopies][kCheckStride], each copy's first six zeroed,
 // [5] = INT64_MAX): entered, left, changed, degenerate, malformed, first
@@ -335,7 +341,6 @@ constexpr int kCheckCopies = 64, kCheckStride = 16;
 hipError_t launch_stage_check(const int32_t* tuples, int64_t P, int32_t V, const double* x, const double* xr,
                               const DevParams& pm, const uint8_t* ft_b, const int4* vid_b, int64_t* counters,
                               hipStream_t s);
-hipError_t launch_stage_offsets(const int64_t* boff, int64_t nb, int64_t* out, hipStream_t s);
 
 // ---- merge.hip
 // merge duplicate PE / PP constraints of ctx->ranges (vertex ids < V) into
@@ -347,6 +352,8 @@ hipError_t merge_duplicates(gipc_ctx* ctx, int32_t V, hipStream_t s, int64_t* ne
 // ctx->order = the vertices sorted into Morton cells of their bounding cube
 // (scene-major with each scene's own cube when S > 1: vert_off device int32
 // [S+1] and ctx->vscene must be set)
+// row_order_tables first: its arrays, and in zero those that must be zeroed
+hipError_t row_order_tables(gipc_ctx* ctx, int32_t V, int32_t S, ZeroList& zero, int at);
 hipError_t build_row_order(gipc_ctx* ctx, const double* x, int32_t V, const int32_t* vert_off, int32_t S,
                            hipStream_t s);
 

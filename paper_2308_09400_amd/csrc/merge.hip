@@ -179,16 +179,27 @@ __global__ void __launch_bounds__(kBlock) k_merge_scatter(int64_t Ps, int64_t k0
                                                           const int4* __restrict__ st_vid,
                                                           const int32_t* __restrict__ st_src,
                                                           int4* __restrict__ vid_out, int32_t* __restrict__ src_out,
-                                                          int32_t* __restrict__ mult_out) {
+                                                          int32_t* __restrict__ mult_out, TypeRanges tr,
+                                                          int64_t* __restrict__ type_off) {
     __shared__ int32_t cnt[kBlock / 64];
-    const int64_t k = (int64_t)blockIdx.x * kBlock + threadIdx.x;
+    // the last nine workgroups leave the merged types' offsets: type t's is
+    // the number of survivors before o
+    const int64_t t = (int64_t)blockIdx.x - ((int64_t)gridDim.x - 9);
+    const int64_t o = t >= 0 ? tr.off[t] : Ps;
+    const int64_t b = t >= 0 ? o / kBlock : (int64_t)blockIdx.x;
+    const int64_t k = b * kBlock + threadIdx.x;
     const int wid = threadIdx.x >> 6;
-    const bool f = survives(k, Ps, k0, k1, state);
+    const bool f = k < o && survives(k, Ps, k0, k1, state);
     const unsigned long long m = __ballot(f);
     if ((threadIdx.x & 63) == 0) cnt[wid] = __popcll(m);
     __syncthreads();
+    int64_t n = boff[b];
+    if (t >= 0) {
+        for (int v = 0; v < kBlock / 64; ++v) n += cnt[v];
+        if (threadIdx.x == 0) type_off[t] = n;
+        return;
+    }
     if (!f) return;
-    int64_t n = boff[blockIdx.x];
     for (int v = 0; v < wid; ++v) n += cnt[v];
     n += __popcll(m & __lanemask_lt());
     vid_out[n] = st_vid[k];
@@ -199,26 +210,6 @@ __global__ void __launch_bounds__(kBlock) k_merge_scatter(int64_t Ps, int64_t k0
         if (w < 0) w = own[~w] + cnt_in[~w];
     }
     mult_out[n] = w;
-}
-
-// merged type offsets, one workgroup per t = 0..8: out[t] = the survivors
-// before tr.off[t]
-__global__ void __launch_bounds__(kBlock) k_merge_offsets(int64_t Ps, int64_t k0, int64_t k1,
-                                                          const int32_t* __restrict__ state,
-                                                          const int64_t* __restrict__ boff, TypeRanges tr,
-                                                          int64_t* __restrict__ out) {
-    __shared__ int32_t cnt[kBlock / 64];
-    const int64_t o = tr.off[blockIdx.x];
-    const int64_t b = o / kBlock;
-    const int64_t k = b * kBlock + threadIdx.x;
-    const unsigned long long m = __ballot(k < o && survives(k, Ps, k0, k1, state));
-    if ((threadIdx.x & 63) == 0) cnt[threadIdx.x >> 6] = __popcll(m);
-    __syncthreads();
-    if (threadIdx.x == 0) {
-        int64_t c = boff[b];
-        for (int w = 0; w < kBlock / 64; ++w) c += cnt[w];
-        out[blockIdx.x] = c;
-    }
 }
 
 unsigned grid(int64_t n) { return (unsigned)((n + kBlock - 1) / kBlock); }
@@ -252,8 +243,10 @@ hipError_t merge_duplicates(gipc_ctx* ctx, int32_t V, hipStream_t s, int64_t* ne
     int32_t* own = count + H;
     const unsigned long long* table = as<unsigned long long>(ctx->mkeys);
     if (n > 0) {
-        TRY(zero_i32(as<int32_t>(ctx->mkeys), nullptr, nullptr, 2 * (int64_t)H, s));
-        TRY(zero_i32(count, nullptr, nullptr, (int64_t)H, s));
+        ZeroList z;
+        z.p[0] = as<int32_t>(ctx->mkeys), z.n[0] = 2 * (int64_t)H;
+        z.p[1] = count, z.n[1] = (int64_t)H;
+        TRY(zero_i32(z, s));
         k_merge_insert<<<grid(n), kBlock, 0, s>>>(as<int4>(ctx->st_vid), k0, k1, pp0,
                                                   as<unsigned long long>(ctx->mkeys), count, own, scale, H - 1,
                                                   state, lone);
@@ -266,14 +259,11 @@ hipError_t merge_duplicates(gipc_ctx* ctx, int32_t V, hipStream_t s, int64_t* ne
     }
     TRY((exclusive_scan<int32_t, int64_t>(as<int32_t>(ctx->mbcount), nbk, as<int64_t>(ctx->mpos), ctx, s)));
     if (Ps > 0) {
-        k_merge_scatter<<<(unsigned)nbk, kBlock, 0, s>>>(Ps, k0, k1, state, count, own, as<int64_t>(ctx->mpos),
-                                                         as<int4>(ctx->st_vid), as<int32_t>(ctx->st_src),
-                                                         as<int4>(ctx->st_vid2), as<int32_t>(ctx->st_src2),
-                                                         as<int32_t>(ctx->mult));
+        k_merge_scatter<<<(unsigned)(nbk + 9), kBlock, 0, s>>>(
+            Ps, k0, k1, state, count, own, as<int64_t>(ctx->mpos), as<int4>(ctx->st_vid), as<int32_t>(ctx->st_src),
+            as<int4>(ctx->st_vid2), as<int32_t>(ctx->st_src2), as<int32_t>(ctx->mult), tr, new_off_dev);
         TRY(hipGetLastError());
     }
-    k_merge_offsets<<<9, kBlock, 0, s>>>(Ps, k0, k1, state, as<int64_t>(ctx->mpos), tr, new_off_dev);
-    TRY(hipGetLastError());
 #undef TRY
     std::swap(ctx->st_vid, ctx->st_vid2);
     std::swap(ctx->st_src, ctx->st_src2);

@@ -151,8 +151,22 @@ __global__ void __launch_bounds__(kBlock) k_cell_scatter(int32_t V, const int32_
 
 }  // namespace
 
-hipError_t build_row_order(gipc_ctx* ctx, const double* x, int32_t V, const int32_t* vert_off, int32_t S,
-                           hipStream_t s) {
+namespace {
+// bits per axis: at most 7, and at most about 4 V buckets in all (S scenes
+// share them), so small builds do not pay for a large histogram
+int bucket_bits(int32_t V, int32_t S) {
+    int bits = kCellBits;
+    while (bits > 0 && ((int64_t)S << (3 * bits)) > 4 * (int64_t)V) --bits;
+    return bits;
+}
+
+// One workgroup finds the box of up to this many vertices: its 16 rounds of
+// loads take no longer than the launch that joins 512 boxes (8 us with its gap).
+constexpr int32_t kBoxOne = 4096;
+constexpr int32_t kBoxParts = 512;
+}  // namespace
+
+hipError_t row_order_tables(gipc_ctx* ctx, int32_t V, int32_t S, ZeroList& zero, int at) {
     hipError_t e;
 #define TRY(x_)                                   \
     do {                                          \
@@ -160,31 +174,40 @@ hipError_t build_row_order(gipc_ctx* ctx, const double* x, int32_t V, const int3
     } while (0)
     TRY(ensure(ctx->order, sizeof(int32_t) * (size_t)(V > 0 ? V : 1)));
     if (V == 0) return hipSuccess;
-    const int32_t nparts = 512;
-    // bits per axis: at most 7, and at most about 4 V buckets in all (S
-    // scenes share them), so small builds do not pay for a large histogram
-    int bits = kCellBits;
-    while (bits > 0 && ((int64_t)S << (3 * bits)) > 4 * (int64_t)V) --bits;
-    const int64_t nbuckets = (int64_t)S << (3 * bits);
+    const int64_t nbuckets = (int64_t)S << (3 * bucket_bits(V, S));
     if (nbuckets > ((int64_t)1 << 31) - 2) return hipErrorInvalidValue;
-    TRY(ensure(ctx->obox, sizeof(double) * 6 * (size_t)(S > 1 ? S : nparts + 1)));
+    TRY(ensure(ctx->obox, sizeof(double) * 6 * (size_t)(S > 1 ? S : kBoxParts + 1)));
     TRY(ensure(ctx->ocell, sizeof(int32_t) * (size_t)V));
     TRY(ensure(ctx->ohist, sizeof(int32_t) * (size_t)nbuckets));
     TRY(ensure(ctx->ooff, sizeof(int32_t) * (size_t)(nbuckets + 1)));
     TRY(ensure(ctx->ofill, sizeof(int32_t) * (size_t)nbuckets));
+    zero.p[at] = as<int32_t>(ctx->ohist), zero.n[at] = nbuckets;
+    zero.p[at + 1] = as<int32_t>(ctx->ofill), zero.n[at + 1] = nbuckets;
+    return hipSuccess;
+}
+
+hipError_t build_row_order(gipc_ctx* ctx, const double* x, int32_t V, const int32_t* vert_off, int32_t S,
+                           hipStream_t s) {
+    hipError_t e;
+    if (V == 0) return hipSuccess;
+    const int bits = bucket_bits(V, S);
+    const int64_t nbuckets = (int64_t)S << (3 * bits);
     double* box;
     if (S > 1) {
         box = as<double>(ctx->obox);
         k_bbox_scene<<<(unsigned)S, kBlock, 0, s>>>(x, vert_off, box);
         TRY(hipGetLastError());
     } else {
-        box = as<double>(ctx->obox) + 6 * nparts;
-        k_bbox_part<<<nparts, kBlock, 0, s>>>(x, V, as<double>(ctx->obox));
+        const int32_t nparts = V <= kBoxOne ? 1 : kBoxParts;
+        box = as<double>(ctx->obox);
+        k_bbox_part<<<(unsigned)nparts, kBlock, 0, s>>>(x, V, box);
         TRY(hipGetLastError());
-        k_bbox_final<<<1, 384, 0, s>>>(as<double>(ctx->obox), nparts, box);
-        TRY(hipGetLastError());
+        if (nparts > 1) {
+            box += 6 * nparts;
+            k_bbox_final<<<1, 384, 0, s>>>(as<double>(ctx->obox), nparts, box);
+            TRY(hipGetLastError());
+        }
     }
-    TRY(zero_i32(as<int32_t>(ctx->ohist), as<int32_t>(ctx->ofill), nullptr, nbuckets, s));
     const unsigned nb = (unsigned)(((int64_t)V + kBlock - 1) / kBlock);
     k_cell_count<<<nb, kBlock, 0, s>>>(x, V, S > 1 ? as<int32_t>(ctx->vscene) : nullptr, box, bits,
                                       as<int32_t>(ctx->ocell), as<int32_t>(ctx->ohist));

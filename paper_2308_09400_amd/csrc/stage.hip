@@ -193,8 +193,11 @@ __global__ void __launch_bounds__(kBlock) k_stage_check(const int4* __restrict__
 __global__ void __launch_bounds__(kBlock) k_stage_scatter(const uint8_t* __restrict__ ft_in,
                                                           const int4* __restrict__ vid_in, int64_t P,
                                                           const int64_t* __restrict__ boff, int4* __restrict__ st_vid,
-                                                          int32_t* __restrict__ st_src) {
+                                                          int32_t* __restrict__ st_src,
+                                                          int64_t* __restrict__ type_off) {
     __shared__ int32_t cnt[kBlock / 64][8];
+    // the types' offsets, for the host (boff[8 gridDim.x] is the total)
+    if (blockIdx.x == 0 && threadIdx.x < 9) type_off[threadIdx.x] = boff[(int64_t)threadIdx.x * gridDim.x];
     const int64_t p = (int64_t)blockIdx.x * kBlock + threadIdx.x;
     const int lane = threadIdx.x & 63, wid = threadIdx.x >> 6;
     const int ft = p < P ? (int)ft_in[p] : FT_NONE;
@@ -238,29 +241,16 @@ hipError_t launch_stage_check(const int32_t* tuples, int64_t P, int32_t V, const
 }
 
 hipError_t launch_stage_scatter(const uint8_t* ft, const int4* vid, int64_t P, const int64_t* boff, int4* st_vid,
-                                int32_t* st_src, hipStream_t s) {
+                                int32_t* st_src, int64_t* type_off, hipStream_t s) {
     int64_t nb = (P + kBlock - 1) / kBlock;
     if (nb == 0) return hipSuccess;
-    k_stage_scatter<<<(unsigned)nb, kBlock, 0, s>>>(ft, vid, P, boff, st_vid, st_src);
+    k_stage_scatter<<<(unsigned)nb, kBlock, 0, s>>>(ft, vid, P, boff, st_vid, st_src, type_off);
     return hipGetLastError();
 }
 
 }  // namespace gipc
 
 namespace gipc {
-namespace {
-// type offsets: out[t] = boff[t * nb] for t = 0..8 (boff[8 nb] is the total)
-__global__ void k_stage_offsets(const int64_t* __restrict__ boff, int64_t nb, int64_t* __restrict__ out) {
-    int t = threadIdx.x;
-    if (t < 9) out[t] = boff[t * nb];
-}
-}  // namespace
-
-hipError_t launch_stage_offsets(const int64_t* boff, int64_t nb, int64_t* out, hipStream_t s) {
-    k_stage_offsets<<<1, 64, 0, s>>>(boff, nb, out);
-    return hipGetLastError();
-}
-
 namespace {
 // scene of every vertex: the last s with vert_off[s] <= v (vert_off is
 // non-decreasing with vert_off[0] = 0 and vert_off[S] = V, checked on the host)
