@@ -31,7 +31,7 @@ __global__ void __launch_bounds__(kBlock) k_sym_count(const int4* __restrict__ s
                                                       unsigned long long* __restrict__ both,
                                                       int4* __restrict__ rank) {
     __shared__ uint32_t tab[kBlock / 64][kGroupSlots];
-    const int64_t k = (int64_t)blockIdx.x * kBlock + threadIdx.x;
+    const int64_t k = xcd_block() * kBlock + threadIdx.x;
     const bool in = k < tr.off[8];
     const int nv = in ? ft_nverts(type_of(k, tr)) : 0;
     const int4 v = in ? st_vid[k] : make_int4(-1, -1, -1, -1);
@@ -79,7 +79,7 @@ __global__ void __launch_bounds__(kBlock) k_sym_degrees(int32_t V, const unsigne
 __global__ void __launch_bounds__(kBlock) k_sym_scatter(const int4* __restrict__ st_vid, TypeRanges tr,
                                                         const int64_t* __restrict__ inc_ptr,
                                                         const int4* __restrict__ rank, int4* __restrict__ incr) {
-    const int64_t k = (int64_t)blockIdx.x * kBlock + threadIdx.x;
+    const int64_t k = xcd_block() * kBlock + threadIdx.x;
     if (k >= tr.off[8]) return;
     const int nv = ft_nverts(type_of(k, tr));
     const int4 v = st_vid[k], at = rank[k];
@@ -583,7 +583,7 @@ __global__ void __launch_bounds__(kBlock) k_sym_transpose(int64_t nnzb, const in
                                                           const int32_t* __restrict__ col_idx,
                                                           const int32_t* __restrict__ row_ptr,
                                                           int32_t* __restrict__ tslot) {
-    const int64_t s = (int64_t)blockIdx.x * kBlock + threadIdx.x;
+    const int64_t s = xcd_block() * kBlock + threadIdx.x;
     if (s >= nnzb) return;
     const int32_t r = slot_row[s], c = col_idx[s];
     int32_t t = -1;
