@@ -38,23 +38,26 @@ template <typename T>
 inline T* as(DevBuf& b) { return static_cast<T*>(b.p); }
 
 // Workgroups go to the chip's 8 XCDs in turn (workgroup b runs on XCD
-// b mod 8), and every XCD has an L2 of its own.  xcd_block() renumbers the
-// launch, 8 kXcdRun workgroups at a time, so that each XCD takes a run of
-// kXcdRun neighbouring ones: the neighbouring rows of a gather kernel then
+// b mod 8), and every XCD has an L2 of its own.  xcd_run() renumbers a launch
+// of n workgroups, 8 RUN at a time, so that each XCD takes a run of RUN
+// neighbouring ones: the neighbouring rows of a gather kernel then
 // read the records they share through the same L2.  It is a permutation of
-// 0 .. gridDim.x-1.  One run per XCD over the whole launch left XCDs waiting
+// 0 .. n-1.  One run per XCD over the whole launch left XCDs waiting
 // where work is uneven and spread the traffic over eight places of every
 // array (assembly of 64 scenes of 32^2 to 256^2 vertices 7200 us, of ten
 // 256 x 256 sheets 2885); runs of 256 take 6360 and 2832, of 1024 6390 and
 // 2850, of 32 6470 and 2935, of 8 6760 and 3080.
 constexpr int kXcds = 8, kXcdRun = 256;
-__device__ __forceinline__ int64_t xcd_block() {
-    const uint32_t b = blockIdx.x, n = gridDim.x, turn = kXcds * kXcdRun;
+template <int RUN = kXcdRun>
+__device__ __forceinline__ uint32_t xcd_run(uint32_t b, uint32_t n) {
+    constexpr uint32_t turn = kXcds * RUN;
     const uint32_t base = b / turn * turn;
     const uint32_t m = n - base < turn ? n - base : turn;  // workgroups of this turn
     const uint32_t q = m / kXcds, r = m % kXcds, i = b - base, x = i % kXcds;
-    return (int64_t)(base + x * q + (x < r ? x : r) + i / kXcds);
+    return base + x * q + (x < r ? x : r) + i / kXcds;
 }
+
+__device__ __forceinline__ int64_t xcd_block() { return (int64_t)xcd_run(blockIdx.x, gridDim.x); }
 
 // Ranges of staged pairs per sub-type: pairs of type t occupy [off[t], off[t+1]).
 struct TypeRanges {

@@ -19,9 +19,11 @@
 // (281 us), as were two or four 64-block chunks per wavefront (288 us), a
 // second fix-up launch for rows that cross wavefronts (278 us),
 // non-temporal column loads (264 us) and a contiguous eighth of the
-// workgroups per XCD (259 against 257 us in that run).  For FP32 blocks the
-// row kernel stays (161 us against 163 us), and a descriptor without the map
-// uses it too.
+// workgroups per XCD (259 against 257 us in that run).  Short runs of 16
+// workgroups per XCD share the gathered x lines without touching eight far
+// places of the matrix at once: 265 against 272 us (runs of 256: 268), a solve
+// of 20 iterations 6.80 against 6.90 ms.  For FP32 blocks the row kernel
+// stays (161 us against 163 us), and a descriptor without the map uses it too.
 //
 // SpMV by rows (k_spmv): G = 32 lanes per block row (two rows per
 // wavefront); each lane walks every 32nd block of the row (component-major
@@ -31,7 +33,8 @@
 // Rows of the contact matrices hold about 27 blocks, so most lanes issue all
 // their loads at once.  Measured on the ten-sheet matrix, FP64: 4 / 8 / 16 /
 // 32 / 64 lanes = 815 / 373 / 311 / 296 / 383 us; FP32: 8 / 16 / 32 lanes =
-// 228 / 178 / 163 us.  At 8 lanes, non-temporal value loads (573 us) and
+// 228 / 178 / 163 us.  Runs of 256 workgroups per XCD: seven 201 x 201 sheets
+// in FP32 50 against 58 us (runs of 16: 52).  At 8 lanes, non-temporal value loads (573 us) and
 // XCD-contiguous row chunks (405 us) were slower; at 32 lanes, two to four
 // rows per lane group (315-340 us) were too.
 //
@@ -60,7 +63,7 @@ template <typename T>
 __global__ void __launch_bounds__(kBlock) k_spmv(int32_t nrows, const int32_t* __restrict__ rp,
                                                  const int32_t* __restrict__ ci, const T* __restrict__ val,
                                                  int64_t nnzb, const T* __restrict__ x, T* __restrict__ y) {
-    const int64_t row = ((int64_t)blockIdx.x * kBlock + threadIdx.x) / kG;
+    const int64_t row = (xcd_block() * kBlock + threadIdx.x) / kG;
     const int lg = threadIdx.x % kG;
     T a0 = 0, a1 = 0, a2 = 0;
     if (row < nrows) {
@@ -95,6 +98,7 @@ __device__ __forceinline__ void stv(double* a, int64_t r, d3 v) {
 // (sc not null) it does nothing once the solve has stopped
 constexpr int kEntWaves = 8;
 constexpr int kEntBlock = kEntWaves * 64;
+constexpr int kEntRun = 16;  // workgroups an XCD takes in a row
 
 __global__ void __launch_bounds__(kEntBlock) k_spmv_ent(int64_t nnzb, const int32_t* __restrict__ rp,
                                                         const int32_t* __restrict__ ci,
@@ -104,7 +108,8 @@ __global__ void __launch_bounds__(kEntBlock) k_spmv_ent(int64_t nnzb, const int3
                                                         const double* __restrict__ x, double* __restrict__ y,
                                                         const PcgScalars* __restrict__ sc, int rev) {
     if (sc && sc->done) return;
-    const unsigned wg = rev ? gridDim.x - 1 - blockIdx.x : blockIdx.x;
+    const unsigned xw = xcd_run<kEntRun>(blockIdx.x, gridDim.x);
+    const unsigned wg = rev ? gridDim.x - 1 - xw : xw;
     __shared__ double sf[kEntWaves][3], sl[kEntWaves][3], stail[3];
     __shared__ unsigned long long sm[kEntWaves], smn[kEntWaves];
     __shared__ int32_t srow[kEntWaves];
@@ -338,7 +343,7 @@ __global__ void __launch_bounds__(kBlock) k_pcg_spmv(int32_t nrows, const int32_
                                                      int64_t nnzb, const T* __restrict__ pm, double* __restrict__ q,
                                                      const PcgScalars* __restrict__ sc) {
     if (sc->done) return;
-    const int64_t row = ((int64_t)blockIdx.x * kBlock + threadIdx.x) / kG;
+    const int64_t row = (xcd_block() * kBlock + threadIdx.x) / kG;
     const int lg = threadIdx.x % kG;
     T a0 = 0, a1 = 0, a2 = 0;
     if (row < nrows) {
