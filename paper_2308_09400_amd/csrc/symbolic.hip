@@ -284,24 +284,41 @@ __device__ __forceinline__ void bitonic_wave(K (&key)[M]) {
     }
 }
 
-// Second half of the wavefront row sort: the T keys (column << 32 | code) of
-// the slots j != i, packed in lk, sorted with M keys per lane (64 M >= T),
-// merged with the row's n own-column contributions (dsort: their codes
-// sorted, element MD lane + q).  A single sort by (column, code) would put
+// The keys of the wavefront sort.  64 bits: column << 32 | code.  32 bits, for
+// columns below 2^23: column << 9 | t << 2 | j, t < 128 the rank of the key's
+// incidence among the row's, whose codes are sorted first anyhow; the two
+// orders are the same.  The sort is bound by its instructions (861 a row):
+// ten 256 x 256 sheets 955 us with 32 bits, 1040 with 64.
+constexpr int kNarrowCols = 1 << 23;
+
+__device__ __forceinline__ int key_col(unsigned long long key) { return (int)(key >> 32); }
+__device__ __forceinline__ int key_col(uint32_t key) { return (int)(key >> 9); }
+__device__ __forceinline__ uint32_t key_code(unsigned long long key, const uint32_t*) { return (uint32_t)key; }
+__device__ __forceinline__ uint32_t key_code(uint32_t key, const uint32_t* own) {
+    return (own[(key >> 2) & 127u] & ~3u) | (key & 3u);
+}
+
+__device__ __forceinline__ uint32_t shfl_up_key(uint32_t v, int d) { return (uint32_t)__shfl_up((int)v, d, 64); }
+__device__ __forceinline__ unsigned long long shfl_up_key(unsigned long long v, int d) { return shfl_up64(v, d); }
+
+// Second half of the wavefront row sort: the T keys of the slots j != i,
+// packed in lk, sorted with M keys per lane (64 M >= T), merged with the
+// row's n own-column contributions (dsort: their codes sorted, element
+// MD lane + q, and in own where keys are of 32 bits).  A single sort by (column, code) would put
 // the own column r between the columns below and above it; that is the list
 // written here: codes to contrib, each column's first offset to kbeg, the
 // columns to kcol, all at the row's contribution offset.
-template <int M>
+template <int M, typename K>
 __device__ __forceinline__ void rowsort_main(int64_t r, int n, int T, int MD, const uint32_t (&dsort)[2],
-                                             const unsigned long long* lk, const int64_t* __restrict__ kptr,
+                                             const K* lk, const uint32_t* own, const int64_t* __restrict__ kptr,
                                              uint32_t* __restrict__ contrib, int32_t* __restrict__ kcol,
                                              int32_t* __restrict__ kbeg, int32_t* __restrict__ ncols) {
     const int lane = threadIdx.x & 63;
-    unsigned long long key[M];
+    K key[M];
 #pragma unroll
     for (int q = 0; q < M; ++q) {
         const int e = M * lane + q;
-        key[q] = e < T ? lk[e] : ~0ull;
+        key[q] = e < T ? lk[e] : ~(K)0;
     }
     bitonic_wave<M>(key);
     const int64_t base = kptr[r];
@@ -309,12 +326,12 @@ __device__ __forceinline__ void rowsort_main(int64_t r, int n, int T, int MD, co
     // L = keys with a column below r (a prefix, the keys being sorted)
     int lt = 0;
 #pragma unroll
-    for (int q = 0; q < M; ++q) lt += (M * lane + q < T && (int)(key[q] >> 32) < ri) ? 1 : 0;
+    for (int q = 0; q < M; ++q) lt += (M * lane + q < T && key_col(key[q]) < ri) ? 1 : 0;
     const int L = wave_sum_i(lt);
 #pragma unroll
     for (int q = 0; q < M; ++q) {
         const int e = M * lane + q;
-        if (e < T) contrib[base + (e < L ? e : e + n)] = (uint32_t)key[q];
+        if (e < T) contrib[base + (e < L ? e : e + n)] = key_code(key[q], own);
     }
     for (int q = 0; q < MD; ++q) {
         const int e = MD * lane + q;
@@ -322,7 +339,7 @@ __device__ __forceinline__ void rowsort_main(int64_t r, int n, int T, int MD, co
     }
     // the first key of every column: flags, this lane's count, its rank
     // among all (exclusive scan of the counts over the lanes)
-    const unsigned long long prev_last = shfl_up64(key[M - 1], 1);
+    const K prev_last = shfl_up_key(key[M - 1], 1);
     bool first[M];
     int c = 0, cb = 0;
 #pragma unroll
@@ -330,9 +347,9 @@ __device__ __forceinline__ void rowsort_main(int64_t r, int n, int T, int MD, co
         const int e = M * lane + q;
         first[q] = false;
         if (e < T) {
-            const int col = (int)(key[q] >> 32);
-            const unsigned long long pk = q == 0 ? prev_last : key[q > 0 ? q - 1 : 0];
-            first[q] = e == 0 || (int)(pk >> 32) != col;
+            const int col = key_col(key[q]);
+            const K pk = q == 0 ? prev_last : key[q > 0 ? q - 1 : 0];
+            first[q] = e == 0 || key_col(pk) != col;
             c += first[q] ? 1 : 0;
             cb += (first[q] && col < ri) ? 1 : 0;
         }
@@ -350,7 +367,7 @@ __device__ __forceinline__ void rowsort_main(int64_t r, int n, int T, int MD, co
     for (int q = 0; q < M; ++q) {
         if (first[q]) {
             const int e = M * lane + q;
-            const int col = (int)(key[q] >> 32);
+            const int col = key_col(key[q]);
             const bool lo = col < ri;
             kcol[base + rank + (lo ? 0 : 1)] = col;
             kbeg[base + rank + (lo ? 0 : 1)] = lo ? e : e + n;
@@ -367,10 +384,11 @@ __device__ __forceinline__ void rowsort_main(int64_t r, int n, int T, int MD, co
 // one wavefront per row, keys in registers.  The slot j = i of an incidence
 // (k, i) is the row's own column, so those n keys are sorted as 32-bit codes
 // apart from the rest, and only the other slots (sum of nv - 1 over the
-// incidences, packed, not 4 slots per incidence) go through the 64-bit
+// incidences, packed, not 4 slots per incidence) go through the larger
 // network: the ten-sheet rows (about 54 incidences, 2.2 other slots each)
 // sort 128 keys instead of 256.  Rows with more than kWaveIncidences
 // incidences are appended to `big` for the workgroup sort.
+template <typename K>
 __global__ void __launch_bounds__(kBlock) k_sym_rowsort_wave(int32_t V, const int64_t* __restrict__ inc_ptr,
                                                              const int4* __restrict__ incr, TypeRanges tr,
                                                              const int64_t* __restrict__ kptr,
@@ -379,7 +397,9 @@ __global__ void __launch_bounds__(kBlock) k_sym_rowsort_wave(int32_t V, const in
                                                              int32_t* __restrict__ ncols,
                                                              int32_t* __restrict__ big,
                                                              unsigned long long* __restrict__ nbig) {
-    __shared__ unsigned long long skeys[kBlock / 64][kWaveN];
+    constexpr bool kNarrow = sizeof(K) == 4;
+    __shared__ K skeys[kBlock / 64][kWaveN];
+    __shared__ uint32_t sown[kNarrow ? kBlock / 64 : 1][kNarrow ? kWaveIncidences : 1];
     const int lane = threadIdx.x & 63;
     const int64_t r = (int64_t)blockIdx.x * (kBlock / 64) + (threadIdx.x >> 6);
     if (r >= V) return;  // the whole wavefront
@@ -396,7 +416,8 @@ __global__ void __launch_bounds__(kBlock) k_sym_rowsort_wave(int32_t V, const in
     // incidences t = lane and lane + 64: the own-column code (slot j = i) as
     // a 32-bit key, the other nv - 1 slots as (column, code) keys packed in
     // incidence order into this wavefront's LDS row
-    unsigned long long* lk = skeys[threadIdx.x >> 6];
+    K* lk = skeys[threadIdx.x >> 6];
+    uint32_t* own = sown[kNarrow ? threadIdx.x >> 6 : 0];
     uint32_t dkey[2] = {~0u, ~0u};
     int o[2] = {0, 0};
     uint32_t kc[2] = {0u, 0u};
@@ -426,19 +447,7 @@ __global__ void __launch_bounds__(kBlock) k_sym_rowsort_wave(int32_t V, const in
         pos[h] = T + sc - o[h];
         T += __shfl(sc, 63, 64);
     }
-#pragma unroll
-    for (int h = 0; h < 2; ++h) {
-        if (o[h] > 0) {
-            const uint32_t k = kc[h] >> 2, i = kc[h] & 3u;
-            int p = pos[h];
-#pragma unroll
-            for (int j = 0; j < 4; ++j)
-                if (j <= o[h] && j != (int)i)
-                    lk[p++] = ((unsigned long long)(uint32_t)rec_other(vv[h], other_slot(j, (int)i)) << 32) |
-                              (unsigned long long)((k << 4) | (i << 2) | (uint32_t)j);
-        }
-    }
-    // the own-column codes, sorted while the LDS writes land
+    // the own-column codes, sorted; narrow keys hold the place in that order
     uint32_t dsort[2] = {~0u, ~0u};
     int MD = 1;
     if (n <= 64) {
@@ -452,14 +461,40 @@ __global__ void __launch_bounds__(kBlock) k_sym_rowsort_wave(int32_t V, const in
         dsort[1] = d2[1];
         MD = 2;
     }
+    if constexpr (kNarrow) {
+        for (int q = 0; q < MD; ++q)
+            if (MD * lane + q < n) own[MD * lane + q] = dsort[q];
+        wave_lds_fence();
+    }
+#pragma unroll
+    for (int h = 0; h < 2; ++h) {
+        if (o[h] > 0) {
+            const uint32_t k = kc[h] >> 2, i = kc[h] & 3u;
+            int p = pos[h];
+            uint32_t rank = 0;
+            if constexpr (kNarrow) {
+                // dkey[h] is one of own[0 .. n), all different
+#pragma unroll
+                for (int step = kWaveIncidences / 2; step > 0; step >>= 1)
+                    if ((int)rank + step < n && own[rank + step] <= dkey[h]) rank += step;
+            }
+#pragma unroll
+            for (int j = 0; j < 4; ++j)
+                if (j <= o[h] && j != (int)i) {
+                    const uint32_t col = (uint32_t)rec_other(vv[h], other_slot(j, (int)i));
+                    if constexpr (kNarrow) lk[p++] = (col << 9) | (rank << 2) | (uint32_t)j;
+                    else lk[p++] = ((K)col << 32) | (K)((k << 4) | (i << 2) | (uint32_t)j);
+                }
+        }
+    }
     __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
     __builtin_amdgcn_wave_barrier();
     __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
     // the branch is uniform in the wavefront
-    if (T <= 64) rowsort_main<1>(r, n, T, MD, dsort, lk, kptr, contrib, kcol, kbeg, ncols);
-    else if (T <= 128) rowsort_main<2>(r, n, T, MD, dsort, lk, kptr, contrib, kcol, kbeg, ncols);
-    else if (T <= 256) rowsort_main<4>(r, n, T, MD, dsort, lk, kptr, contrib, kcol, kbeg, ncols);
-    else rowsort_main<8>(r, n, T, MD, dsort, lk, kptr, contrib, kcol, kbeg, ncols);
+    if (T <= 64) rowsort_main<1>(r, n, T, MD, dsort, lk, own, kptr, contrib, kcol, kbeg, ncols);
+    else if (T <= 128) rowsort_main<2>(r, n, T, MD, dsort, lk, own, kptr, contrib, kcol, kbeg, ncols);
+    else if (T <= 256) rowsort_main<4>(r, n, T, MD, dsort, lk, own, kptr, contrib, kcol, kbeg, ncols);
+    else rowsort_main<8>(r, n, T, MD, dsort, lk, own, kptr, contrib, kcol, kbeg, ncols);
 }
 
 // one workgroup per listed row (grid-stride over the list of rows the
@@ -562,7 +597,12 @@ hipError_t launch_sym_rowsort(int32_t V, int32_t max_deg, const int64_t* inc_ptr
     if (V == 0) return hipSuccess;
     unsigned long long* nb = reinterpret_cast<unsigned long long*>(nbig);
     const unsigned blocks = (unsigned)(((int64_t)V + kBlock / 64 - 1) / (kBlock / 64));
-    k_sym_rowsort_wave<<<blocks, kBlock, 0, s>>>(V, inc_ptr, incr, tr, kptr, contrib, kcol, kbeg, ncols, big, nb);
+    if (V <= kNarrowCols)
+        k_sym_rowsort_wave<uint32_t>
+            <<<blocks, kBlock, 0, s>>>(V, inc_ptr, incr, tr, kptr, contrib, kcol, kbeg, ncols, big, nb);
+    else
+        k_sym_rowsort_wave<unsigned long long>
+            <<<blocks, kBlock, 0, s>>>(V, inc_ptr, incr, tr, kptr, contrib, kcol, kbeg, ncols, big, nb);
     hipError_t e = hipGetLastError();
     if (e != hipSuccess || max_deg <= kWaveIncidences) return e;
     unsigned N = 64;

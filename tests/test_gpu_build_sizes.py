@@ -87,3 +87,52 @@ def test_merged_multiplicities(gp, P):
     assert np.array_equal(mult, [count[k] for k in order])
     assert np.array_equal(ty, [2 if kind[k] else 3 for k in order])
     ctx.close()
+
+
+@pytest.mark.parametrize("V", [2 ** 23, 2 ** 23 + 1])
+def test_rows_of_the_last_vertices(gp, V):
+    # the row sort's narrow keys hold columns below 2^23; fans of 1 to 128
+    # point-point pairs about centres among the last vertices, and one pair
+    # between the two last
+    rng = np.random.default_rng(V)
+    sizes = [1, 2, 63, 64, 65, 127, 128]
+    ids = V - 1 - rng.permutation(2 + sum(n + 1 for n in sizes))
+    x = np.zeros((V, 3))
+    x[:, 0] = np.arange(V) * 10.0
+    t, at = [[-V, V - 2, -1, -1]], 0
+    x[V - 2] = x[V - 1] + [0.0, 0.5, 0.0]
+    ids = ids[(ids != V - 1) & (ids != V - 2)]
+    adj = {V - 1: [V - 2], V - 2: [V - 1]}
+    for n in sizes:
+        c, leaves = ids[at], ids[at + 1:at + 1 + n]
+        at += 1 + n
+        x[leaves] = x[c] + np.stack([np.zeros(n), np.full(n, 0.5), np.arange(n) * 1e-3], 1)
+        t += [[-(c + 1), v, -1, -1] if k % 2 else [-(v + 1), c, -1, -1] for k, v in enumerate(leaves)]
+        adj[c] = list(leaves)
+        adj.update({v: [c] for v in leaves})
+    t = np.array(t)[rng.permutation(len(t))]
+    ctx = gp.Context()
+    X = _dev(x, torch.float64)
+    prm = gp.params(dhat=1.0)
+    info = gp.pairs_build(ctx, X, _dev(t, torch.int32), prm)
+    A = gp.BsrMatrix(ctx)
+    assert info["n_staged"] == len(t) and info["max_row_pairs"] == 128
+    blocks = np.ones(V, np.int64)
+    for v, c in adj.items():
+        blocks[v] += len(c)
+    rp = A.row_ptr().cpu().numpy()
+    assert np.array_equal(rp, np.concatenate([[0], np.cumsum(blocks)]))
+    ci = A.col_idx().cpu().numpy()
+    for v, c in adj.items():
+        assert np.array_equal(ci[rp[v]:rp[v + 1]], np.sort(np.append(c, v))), v
+    alone = np.flatnonzero(blocks == 1)
+    assert np.array_equal(ci[rp[alone]], alone)
+    # every contribution under its block: rows of a symmetric Laplacian sum to
+    # the diagonal added (1), the off-diagonal blocks of a pair cancel it
+    _, g = gp.eval_assemble(ctx, X, prm, A, diag=torch.ones(V, dtype=torch.float64, device="cuda"))
+    val = A.val[:, :A.nnzb].cpu().numpy().T.reshape(-1, 3, 3)
+    for v in adj:
+        big = np.abs(val[rp[v]:rp[v + 1]]).max()
+        s = val[rp[v]:rp[v + 1]].sum(0) - np.eye(3)
+        assert np.abs(s).max() <= 1e-12 * max(big, 1.0)
+    ctx.close()
