@@ -921,33 +921,28 @@ gipc_status gipc_candidates(gipc_ctx* ctx, const gipc_mesh* mesh, const gipc_top
     hipStream_t s = S(stream);
     const double* x = mesh->x;
 
-    // topology ids
-    CK(ensure(ctx->ccnt, sizeof(int64_t) * 8), "alloc candidates");
-    const int64_t init[2] = {0, INT64_MAX};
-    CK(hipMemcpyAsync(ctx->ccnt.p, init, sizeof(init), hipMemcpyHostToDevice, s), "copy");
-    CK(launch_cand_check(V, topo->vobj, topo->tris, F, topo->edges, E, as<int64_t>(ctx->ccnt), s), "topology check");
-    int64_t bad[2];
-    CK(hipMemcpyAsync(bad, ctx->ccnt.p, sizeof(bad), hipMemcpyDeviceToHost, s), "copy");
-    CK(hipStreamSynchronize(s), "stream synchronize");
-    if (bad[0] > 0)
-        return fail(ctx, GIPC_ERR_INDEX, "%lld primitives have vertex ids out of range or repeated (first: %lld)",
-                    (long long)bad[0], (long long)bad[1]);
-
-    // bounds and grid
+    // topology ids, bounds and grid
+    CK(ensure(ctx->ccnt, sizeof(int64_t) * 4), "alloc candidates");
     const int32_t nb = cand_bound_blocks(V, F + E);
-    CK(ensure(ctx->cpart, sizeof(double) * 9 * (size_t)nb), "alloc candidates");
-    CK(launch_cand_bounds(x, V, topo->tris, F, topo->edges, E, as<double>(ctx->cpart), nb, s), "bounds");
-    std::vector<double> part(9 * (size_t)nb);
-    CK(hipMemcpyAsync(part.data(), ctx->cpart.p, sizeof(double) * part.size(), hipMemcpyDeviceToHost, s), "copy");
+    CK(ensure(ctx->cpart, sizeof(CandBounds) * (size_t)nb), "alloc candidates");
+    CK(launch_cand_bounds(x, V, topo->tris, F, topo->edges, E, as<CandBounds>(ctx->cpart), nb, s), "bounds");
+    std::vector<CandBounds> part((size_t)nb);
+    CK(hipMemcpyAsync(part.data(), ctx->cpart.p, sizeof(CandBounds) * part.size(), hipMemcpyDeviceToHost, s), "copy");
     CK(hipStreamSynchronize(s), "stream synchronize");
     double lo[3] = {INFINITY, INFINITY, INFINITY}, hi[3] = {-INFINITY, -INFINITY, -INFINITY}, ext[3] = {0, 0, 0};
-    for (int32_t b = 0; b < nb; ++b) {
+    int64_t nbad = 0, first_bad = INT64_MAX;
+    for (const CandBounds& b : part) {
         for (int d = 0; d < 3; ++d) {
-            lo[d] = std::min(lo[d], part[9 * b + d]);
-            hi[d] = std::max(hi[d], part[9 * b + 3 + d]);
-            ext[d] = std::max(ext[d], part[9 * b + 6 + d]);
+            lo[d] = std::min(lo[d], b.r[d]);
+            hi[d] = std::max(hi[d], b.r[3 + d]);
+            ext[d] = std::max(ext[d], b.r[6 + d]);
         }
+        nbad += b.nbad;
+        if (b.nbad > 0) first_bad = std::min(first_bad, b.first);
     }
+    if (nbad > 0)
+        return fail(ctx, GIPC_ERR_INDEX, "%lld primitives have vertex ids out of range or repeated (first: %lld)",
+                    (long long)nbad, (long long)first_bad);
     for (int d = 0; d < 3; ++d)
         if (!std::isfinite(lo[d]) || !std::isfinite(hi[d])) return fail(ctx, GIPC_ERR_INVALID_ARG, "non-finite positions");
     // per axis: the largest extent plus dhat (at least a thousandth of the

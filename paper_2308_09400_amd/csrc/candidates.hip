@@ -10,7 +10,8 @@
 // found exactly once.
 //
 //  1. bounds: per-block minima / maxima of the positions and the largest
-//     primitive extent (the host finishes the reduction and sizes the grid);
+//     primitive extent, with a check of the vertex ids (the host finishes the
+//     reduction and sizes the grid);
 //  2. four cell tables numbered through: of the queries (points, then edges,
 //     in the cells their box inflated by dhat covers, in any order) and of the
 //     primitives (triangles, then edges): counts, one scan, one fill;
@@ -132,25 +133,44 @@ __device__ __forceinline__ void wave_visits(const int lo[3], const int hi[3], bo
     }
 }
 
-// per block: min x,y,z, max x,y,z of the positions, largest primitive
-// extent along x, y, z
-__global__ void __launch_bounds__(kBlock) k_cand_bounds(const double* __restrict__ X, int32_t V,
-                                                        const int32_t* __restrict__ tris, int64_t F,
-                                                        const int32_t* __restrict__ edges, int64_t E,
-                                                        double* __restrict__ part) {
+// per block: min x,y,z, max x,y,z of the positions, largest primitive extent
+// along x, y, z, and the primitives with invalid vertex ids (out of range or
+// repeated), which take no part in the extents: their number and the first of
+// them, as integers.  One pass for both: the check by itself read the topology
+// once more and its answer was waited for (a Newton step of two 16 x 16
+// sheets 605 us, 640 with the pass of its own; ten 256 x 256 sheets'
+// candidates 2930 and 2970).
+__global__ void __launch_bounds__(kBlock) k_cand_bounds(const double* __restrict__ X, int32_t V, Prims pr,
+                                                        CandBounds* __restrict__ part) {
     __shared__ double lds[kBlock / 64][9];
+    __shared__ unsigned long long nbad, first;
+    if (threadIdx.x == 0) {
+        nbad = 0ull;
+        first = ~0ull;
+    }
+    __syncthreads();
     double r[9] = {INFINITY, INFINITY, INFINITY, -INFINITY, -INFINITY, -INFINITY, 0.0, 0.0, 0.0};
-    const int64_t stride = (int64_t)gridDim.x * kBlock;
+    const int64_t stride = (int64_t)gridDim.x * kBlock, F = pr.F, E = pr.E;
     for (int64_t i = (int64_t)blockIdx.x * kBlock + threadIdx.x; i < V; i += stride) {
         const d3 p = ld3(X, (int)i);
         r[0] = fmin(r[0], p.x); r[1] = fmin(r[1], p.y); r[2] = fmin(r[2], p.z);
         r[3] = fmax(r[3], p.x); r[4] = fmax(r[4], p.y); r[5] = fmax(r[5], p.z);
     }
     for (int64_t i = (int64_t)blockIdx.x * kBlock + threadIdx.x; i < F + E; i += stride) {
-        const Box b = i < F ? prim_box(X, tris + 3 * i, 3) : prim_box(X, edges + 2 * (i - F), 2);
-        r[6] = fmax(r[6], b.hi.x - b.lo.x);
-        r[7] = fmax(r[7], b.hi.y - b.lo.y);
-        r[8] = fmax(r[8], b.hi.z - b.lo.z);
+        const bool tri = i < F;
+        const int32_t* v = tri ? pr.tris + 3 * i : pr.edges + 2 * (i - F);
+        const int32_t a = v[0], b = v[1], c = tri ? v[2] : b;
+        const bool ok = a >= 0 && a < V && b >= 0 && b < V && c >= 0 && c < V && a != b &&
+                        (!tri || (c != a && c != b));
+        if (!ok) {
+            atomicAdd(&nbad, 1ull);
+            atomicMin(&first, (unsigned long long)i);
+            continue;
+        }
+        const Box x = tri ? prim_box(X, v, 3) : prim_box(X, v, 2);
+        r[6] = fmax(r[6], x.hi.x - x.lo.x);
+        r[7] = fmax(r[7], x.hi.y - x.lo.y);
+        r[8] = fmax(r[8], x.hi.z - x.lo.z);
     }
 #pragma unroll
     for (int o = 32; o > 0; o >>= 1) {
@@ -166,27 +186,11 @@ __global__ void __launch_bounds__(kBlock) k_cand_bounds(const double* __restrict
         const int q = threadIdx.x;
         double v = lds[0][q];
         for (int w = 1; w < kBlock / 64; ++w) v = q < 3 ? fmin(v, lds[w][q]) : fmax(v, lds[w][q]);
-        part[9 * blockIdx.x + q] = v;
+        part[blockIdx.x].r[q] = v;
     }
-}
-
-// invalid vertex ids of the topology -> counters[0], the first one -> counters[1]
-__global__ void __launch_bounds__(kBlock) k_cand_check(int32_t V, const int32_t* __restrict__ vobj,
-                                                       const int32_t* __restrict__ tris, int64_t F,
-                                                       const int32_t* __restrict__ edges, int64_t E,
-                                                       unsigned long long* __restrict__ counters) {
-    const int64_t i = (int64_t)blockIdx.x * kBlock + threadIdx.x;
-    if (i >= F + E) return;
-    const int32_t* v = i < F ? tris + 3 * i : edges + 2 * (i - F);
-    const int n = i < F ? 3 : 2;
-    bool ok = true;
-    for (int k = 0; k < n; ++k) {
-        ok = ok && v[k] >= 0 && v[k] < V;
-        for (int l = 0; l < k; ++l) ok = ok && v[l] != v[k];
-    }
-    if (!ok) {
-        atomicAdd(&counters[0], 1ull);
-        atomicMin(&counters[1], (unsigned long long)i);
+    if (threadIdx.x == 0) {
+        part[blockIdx.x].nbad = (int64_t)nbad;
+        part[blockIdx.x].first = (int64_t)first;
     }
 }
 
@@ -755,7 +759,6 @@ __global__ void __launch_bounds__(kBlock) k_cell_slots(int64_t ncell, const int6
     n[c] = c < ncell ? ((nt + 63) >> 6) * nq : ((nq + 63) >> 6) * nt;
 }
 
-unsigned grid1(int64_t n) { return (unsigned)((n + kBlock - 1) / kBlock); }
 
 Grid to_grid(const CandGrid& cg) {
     Grid g;
@@ -774,16 +777,8 @@ int32_t cand_bound_blocks(int64_t V, int64_t FE) {
 }
 
 hipError_t launch_cand_bounds(const double* x, int32_t V, const int32_t* tris, int64_t F, const int32_t* edges,
-                              int64_t E, double* part, int32_t nb, hipStream_t s) {
-    k_cand_bounds<<<(unsigned)nb, kBlock, 0, s>>>(x, V, tris, F, edges, E, part);
-    return hipGetLastError();
-}
-
-hipError_t launch_cand_check(int32_t V, const int32_t* vobj, const int32_t* tris, int64_t F, const int32_t* edges,
-                             int64_t E, int64_t* counters, hipStream_t s) {
-    if (F + E == 0) return hipSuccess;
-    k_cand_check<<<grid1(F + E), kBlock, 0, s>>>(V, vobj, tris, F, edges, E,
-                                                 reinterpret_cast<unsigned long long*>(counters));
+                              int64_t E, CandBounds* part, int32_t nb, hipStream_t s) {
+    k_cand_bounds<<<(unsigned)nb, kBlock, 0, s>>>(x, V, Prims{tris, edges, F, E}, part);
     return hipGetLastError();
 }
 

@@ -481,11 +481,15 @@ struct CandGrid {
     int32_t n[3];
 };
 int32_t cand_bound_blocks(int64_t V, int64_t FE);
-// part [nb][9]: min x y z, max x y z, largest primitive extent along x y z
+// a workgroup's part: min x y z, max x y z, largest primitive extent along
+// x y z; primitives with invalid vertex ids and the first of them (triangles,
+// then edges)
+struct CandBounds {
+    double r[9];
+    int64_t nbad, first;
+};
 hipError_t launch_cand_bounds(const double* x, int32_t V, const int32_t* tris, int64_t F, const int32_t* edges,
-                              int64_t E, double* part, int32_t nb, hipStream_t s);
-hipError_t launch_cand_check(int32_t V, const int32_t* vobj, const int32_t* tris, int64_t F, const int32_t* edges,
-                             int64_t E, int64_t* counters, hipStream_t s);
+                              int64_t E, CandBounds* part, int32_t nb, hipStream_t s);
 // 64-byte records of the triangles and edges (box, vertex ids, object)
 constexpr int kPrimRecBytes = 64;
 hipError_t launch_prim_records(const double* x, const int32_t* tris, int64_t F, const int32_t* edges, int64_t E,
