@@ -65,11 +65,11 @@ FP64_VECTOR_TFLOPS = 78.6    # MI355X FP64 vector peak
 # only while the SHA-256 of that source file still matches, else null.
 MEASURED_TRAFFIC = {
     "kernel": "k_spmv_ent",
-    "bytes": 1.801e9,
+    "bytes": 1.706e9,
     "source": "profiles/sheets10_path.md (rocprofv3 FETCH_SIZE x 2.0 + WRITE_SIZE x 1.0 per dispatch, "
               "calibrated on the library's 2 GiB copy in the same run)",
     "file": "paper_2308_09400_amd/csrc/solve.hip",
-    "sha256": "c6291caeb05ad8fcec59206c3ce7ac75e8bd7a46e7f4f484bed6b3e3c729ff19",
+    "sha256": "690161e36e9009018877ef60b73a54984efbbb1d2236607306164743ac2a52bd",
 }
 
 
