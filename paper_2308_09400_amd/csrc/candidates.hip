@@ -386,9 +386,10 @@ __device__ __forceinline__ double read_lane(double v, int k) {
 // Boxes in whole steps of 1/2048 cell about a cell's corner, for a first test
 // that rejects a pair by integers: a coordinate goes to -16383 .. 16383 by
 // operations that never swap two values, so integers in strict order prove the
-// order of the values (equal ones prove nothing).  Two axis ends per word: a primitive
-// holds (hi, -lo) and a query (lo - dhat, -(hi + dhat)); a negative half of
-// their difference says that the boxes are apart.
+// order of the values (equal ones prove nothing, and NaN goes to the end that
+// rejects nothing, as a comparison with it does).  Two axis ends per word: a
+// primitive holds (hi, -lo) and a query (lo - dhat, -(hi + dhat)); a negative
+// half of their difference says that the boxes are apart.
 struct CellSteps {
     double org[3], inv[3];
 };
@@ -405,8 +406,12 @@ __device__ __forceinline__ CellSteps cell_steps(const Grid& g, const int cc[3]) 
 
 typedef short short2_t __attribute__((ext_vector_type(2)));
 
-__device__ __forceinline__ int step_of(double v, const CellSteps& c, int d) {
-    return min(max((int)((v - c.org[d]) * c.inv[d]), -16383), 16383);
+__device__ __forceinline__ int step_lo(double v, const CellSteps& c, int d) {
+    return (int)fmin(fmax((v - c.org[d]) * c.inv[d], -16383.0), 16383.0);
+}
+
+__device__ __forceinline__ int step_hi(double v, const CellSteps& c, int d) {
+    return (int)fmax(fmin((v - c.org[d]) * c.inv[d], 16383.0), -16383.0);
 }
 
 __device__ __forceinline__ int pack_steps(int a, int b) { return (a & 0xffff) | (b << 16); }
@@ -422,12 +427,12 @@ __device__ __forceinline__ int neg_steps(short2_t a) { return __builtin_bit_cast
 // the words of a primitive's box and of a query's (already inflated) box
 __device__ __forceinline__ void prim_steps(const double* lo, const double* hi, const CellSteps& c, int w[3]) {
 #pragma unroll
-    for (int d = 0; d < 3; ++d) w[d] = pack_steps(step_of(hi[d], c, d), -step_of(lo[d], c, d));
+    for (int d = 0; d < 3; ++d) w[d] = pack_steps(step_hi(hi[d], c, d), -step_lo(lo[d], c, d));
 }
 
 __device__ __forceinline__ void query_steps(const double* lo, const double* hi, const CellSteps& c, int w[3]) {
 #pragma unroll
-    for (int d = 0; d < 3; ++d) w[d] = pack_steps(step_of(lo[d], c, d), -step_of(hi[d], c, d));
+    for (int d = 0; d < 3; ++d) w[d] = pack_steps(step_lo(lo[d], c, d), -step_hi(hi[d], c, d));
 }
 
 // Edge-edge pairs, one wave per cell: its lanes take the edge queries

@@ -59,3 +59,23 @@ def test_touching_boxes_and_mixed_objects(gp, strips, length, unit, origin, dhat
     assert len(ref) > 0 and len(c) == len(ref)
     assert set(map(tuple, c.tolist())) == set(map(tuple, ref.tolist()))
     ctx.close()
+
+
+@pytest.mark.parametrize("first", [True, False])
+def test_a_box_of_nan_is_apart_from_nothing(gp, first):
+    # a comparison with NaN never says that boxes are apart, and NaN falls into
+    # the grid's first cell, where this triangle lies too
+    nan = np.full((2, 3), np.nan)
+    x = np.concatenate([[[0.0, 0.0, 0.0], [1.0, 0.0, 0.1], [0.0, 1.0, 0.2]], nan])
+    vobj = np.array([0, 0, 0, 1, 1])
+    tris = np.array([[0, 1, 2]])
+    edges = np.array([[0, 1], [1, 2], [0, 2]])
+    edges = np.concatenate([[[3, 4]], edges] if first else [edges, [[3, 4]]])
+    dev = torch.device("cuda", 0)
+    ctx = gp.Context()
+    c = gp.candidates(ctx, torch.tensor(x, device=dev), *(torch.tensor(a, dtype=torch.int32, device=dev)
+                                                         for a in (vobj, tris, edges)), 1e-3).cpu().numpy()
+    want = [(-4, 0, 1, 2), (-5, 0, 1, 2)]
+    want += [(3, 4, a, b) if first else (a, b, 3, 4) for a, b in [(0, 1), (1, 2), (0, 2)]]
+    assert len(c) == len(want) and set(map(tuple, c.tolist())) == set(want)
+    ctx.close()
