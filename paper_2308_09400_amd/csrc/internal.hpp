@@ -249,6 +249,7 @@ struct PcgScalars {  // device-resident scalars of the PCG loop
     int iters, done, breakdown, maxit;
     int delta;  // stopping test: 0 r.r <= rtol2 b.b, 1 r.z <= rtol2 r0.z0
     int conv;   // the stopping test held
+    int stop;       // what the merged update found, for the p update
     double rzb[2];  // r.z by the parity of the iteration that reads it
 };
 

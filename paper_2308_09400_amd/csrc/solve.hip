@@ -506,26 +506,33 @@ __device__ __forceinline__ double wg_total(const double* __restrict__ part, int6
     return a;
 }
 
-// alpha, x += alpha p, r -= alpha q, z = M^-1 r, partials (r.z, r.r).  The
-// scalars that other workgroups read are not written here, save done at a
-// breakdown, which they all find by themselves.
+// alpha, x += alpha p, r -= alpha q, z = M^-1 r, partials (r.z, r.r).  A launch
+// never writes a scalar that its workgroups read, since nothing orders the
+// store of one against the loads of another's wavefronts, and a workgroup that
+// lost some of its wavefronts would sum LDS that they never wrote: this one
+// reads done and leaves stop, the p update reads stop and leaves done.
 __global__ void __launch_bounds__(kBlock) k_pcg_alpha_update(int32_t V, double* __restrict__ x, double* __restrict__ r,
                                                              double* __restrict__ z, const double* __restrict__ p,
                                                              const double* __restrict__ q,
                                                              const double* __restrict__ minv,
                                                              const double* __restrict__ pqpart, int64_t npq,
                                                              double* __restrict__ part, PcgScalars* sc, int cur) {
-    if (sc->done) return;
-    __shared__ double lds[kBlock / 64];
-    const double pq = wg_total(pqpart, npq, lds);
-    if (!(pq > 0.0)) {
-        if (blockIdx.x == 0 && threadIdx.x == 0) {
-            sc->pq = pq;
-            sc->breakdown = 1;
-            sc->done = 1;
-        }
+    const bool first = blockIdx.x == 0 && threadIdx.x == 0;
+    if (sc->done) {
+        if (first) sc->stop = 1;
         return;
     }
+    __shared__ double lds[kBlock / 64];
+    const double pq = wg_total(pqpart, npq, lds);  // the same in every workgroup
+    const bool bad = !(pq > 0.0);
+    if (first) {
+        sc->stop = bad;
+        if (bad) {
+            sc->pq = pq;
+            sc->breakdown = 1;
+        }
+    }
+    if (bad) return;
     const double al = sc->rzb[cur] / pq;
     const int64_t i = (int64_t)blockIdx.x * kBlock + threadIdx.x;
     double rz = 0, rr = 0;
@@ -557,14 +564,16 @@ __device__ __forceinline__ void pcg_step(PcgScalars* sc, double RZ, double RR, d
     sc->done = sc->conv || sc->iters >= sc->maxit;
 }
 
-// beta, p = z + beta p and its FP32 copy; nb: workgroups of the update.  A
-// workgroup that finds done already set by the first one leaves its part of p
-// as it is: nothing reads p after that.
+// beta, p = z + beta p and its FP32 copy; nb: workgroups of the update.  After
+// a breakdown only done is left to set.
 __global__ void __launch_bounds__(kBlock) k_pcg_beta_pupdate(int64_t n, const double* __restrict__ z,
                                                              double* __restrict__ p, float* __restrict__ p32,
                                                              const double* __restrict__ part, int64_t nb,
                                                              PcgScalars* sc, int cur) {
-    if (sc->done) return;
+    if (sc->stop) {
+        if (blockIdx.x == 0 && threadIdx.x == 0) sc->done = 1;
+        return;
+    }
     __shared__ double lds[kBlock / 64];
     const double RZ = wg_total(part, nb, lds), RR = wg_total(part + nb, nb, lds);
     const double be = RZ / sc->rzb[cur];
