@@ -345,19 +345,19 @@ __global__ void __launch_bounds__(kBlock) k_cells_fill(const double* __restrict_
 // place is the number of entries of the cell below it (the ids of a cell
 // are distinct), counted against the others handed over by lane reads;
 // raw (which starts at the first cell's entry) -> ent; ncell = cells of both
-// primitive tables
-__global__ void __launch_bounds__(kBlock) k_cell_sort(int64_t ncell, const int64_t* __restrict__ off,
+// primitive tables, c0 = the launch's first
+__global__ void __launch_bounds__(kBlock) k_cell_sort(int64_t c0, int64_t ncell, const int64_t* __restrict__ off,
                                                       const int32_t* __restrict__ raw,
                                                       int32_t* __restrict__ ent) {
     const int lane = threadIdx.x & 63;
     const int64_t c =
-        (int64_t)blockIdx.x * (kBlock / 64) + __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
+        c0 + (int64_t)blockIdx.x * (kBlock / 64) + __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
     if (c >= ncell) return;
     const int64_t b = off[c], n = off[c + 1] - b;
     raw -= off[0];
-    for (int64_t c0 = 0; c0 < n; c0 += 64) {
-        const bool mine_ok = c0 + lane < n;
-        const int32_t mine = mine_ok ? raw[b + c0 + lane] : 0;
+    for (int64_t m0 = 0; m0 < n; m0 += 64) {
+        const bool mine_ok = m0 + lane < n;
+        const int32_t mine = mine_ok ? raw[b + m0 + lane] : 0;
         int rank = 0;
         for (int64_t c1 = 0; c1 < n; c1 += 64) {
             const int32_t other = c1 + lane < n ? raw[b + c1 + lane] : 0;
@@ -476,7 +476,7 @@ __global__ void __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(6))
                                                        const int32_t* __restrict__ vobj,
                                                        const PrimRec* __restrict__ erec,
                                                        const int32_t* __restrict__ edges, Grid g, double dhat,
-                                                       int64_t ncell, const int64_t* __restrict__ qtoff,
+                                                       int64_t c0, int64_t ncell, const int64_t* __restrict__ qtoff,
                                                        const int32_t* __restrict__ qent,
                                                        const int64_t* __restrict__ qeoff,
                                                        const int64_t* __restrict__ coff,
@@ -487,7 +487,7 @@ __global__ void __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(6))
                                                        int64_t* __restrict__ evis, int4* __restrict__ out) {
     const int lane = threadIdx.x & 63;
     const int64_t cell =
-        xcd_block() * (kBlock / 64) + __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
+        c0 + xcd_block() * (kBlock / 64) + __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
     if (cell >= ncell) return;
     const int64_t qa = qtoff[cell], qz = qtoff[cell + 1];
     const int64_t ta = coff[cell], tz = coff[cell + 1];
@@ -645,14 +645,14 @@ __global__ void __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(6))
 template <bool EMIT>
 __global__ void __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(7)))
 k_cell_pairs_pt(const double* __restrict__ X, const int32_t* __restrict__ vobj, const PrimRec* __restrict__ trec,
-                const int32_t* __restrict__ tris, Grid g, double dhat, int64_t ncell, const int64_t* __restrict__ qtoff,
+                const int32_t* __restrict__ tris, Grid g, double dhat, int64_t c0, int64_t ncell, const int64_t* __restrict__ qtoff,
                 const int32_t* __restrict__ qent, const int64_t* __restrict__ qeoff,
                 const int64_t* __restrict__ coff, const int32_t* __restrict__ cent, int32_t* __restrict__ cnt,
                 const int64_t* __restrict__ eoff, const int64_t* __restrict__ boff,
                 unsigned long long* __restrict__ bal, int64_t* __restrict__ evis, int4* __restrict__ out) {
     const int lane = threadIdx.x & 63;
     const int64_t cell =
-        (int64_t)blockIdx.x * (kBlock / 64) + __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
+        c0 + (int64_t)blockIdx.x * (kBlock / 64) + __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
     if (cell >= ncell) return;
     const int64_t qa = qtoff[cell], qz = qtoff[cell + 1];
     const int64_t ta = coff[cell], tz = coff[cell + 1];
@@ -764,6 +764,21 @@ __global__ void __launch_bounds__(kBlock) k_cell_slots(int64_t ncell, const int6
     n[c] = c < ncell ? ((nt + 63) >> 6) * nq : ((nq + 63) >> 6) * nt;
 }
 
+// The passes with one wavefront per cell run in slices of kCellSlice cells: a
+// launch takes fewer than 2^32 work-items, which is 2^26 cells, and there are
+// up to 2^28 in a grid and twice as many in the two primitive tables.
+// launch(first cell, workgroups) for every slice of n cells.
+constexpr int64_t kCellSlice = int64_t(1) << 25;
+template <typename L>
+hipError_t cell_slices(int64_t n, L launch) {
+    for (int64_t c0 = 0; c0 < n; c0 += kCellSlice) {
+        const int64_t m = n - c0 < kCellSlice ? n - c0 : kCellSlice;
+        launch(c0, (unsigned)((m + kBlock / 64 - 1) / (kBlock / 64)));
+        const hipError_t e = hipGetLastError();
+        if (e != hipSuccess) return e;
+    }
+    return hipSuccess;
+}
 
 Grid to_grid(const CandGrid& cg) {
     Grid g;
@@ -817,9 +832,9 @@ hipError_t launch_cells_fill(const double* x, int32_t V, const int32_t* tris, in
                                                  g, dhat, off, fill, raw, ent);
     hipError_t e = hipGetLastError();
     if (e != hipSuccess) return e;
-    k_cell_sort<<<(unsigned)((2 * ncell + kBlock / 64 - 1) / (kBlock / 64)), kBlock, 0, s>>>(
-        2 * ncell, off + 2 * ncell, raw, ent);
-    return hipGetLastError();
+    return cell_slices(2 * ncell, [&](int64_t c0, unsigned nwg) {
+        k_cell_sort<<<nwg, kBlock, 0, s>>>(c0, 2 * ncell, off + 2 * ncell, raw, ent);
+    });
 }
 
 hipError_t launch_cell_slots(const CandGrid& cg, const int64_t* off, int64_t* n, hipStream_t s) {
@@ -835,26 +850,15 @@ hipError_t launch_cell_pairs(int kind, bool emit, const double* x, const int32_t
                              int64_t* evis, int32_t* out, hipStream_t s) {
     const Grid g = to_grid(cg);
     const int64_t ncell = (int64_t)g.n[0] * g.n[1] * g.n[2];
-    const unsigned nb = (unsigned)((ncell + kBlock / 64 - 1) / (kBlock / 64));
     int4* o = reinterpret_cast<int4*>(out);
     const PrimRec* pr = static_cast<const PrimRec*>(rec);
     unsigned long long* b = reinterpret_cast<unsigned long long*>(bal);
-    if (kind == 0) {
-        if (emit)
-            k_cell_pairs_pt<true><<<nb, kBlock, 0, s>>>(x, vobj, pr, prims, g, dhat, ncell, qtoff, qent, qeoff, coff, cent,
-                                                        cnt, eoff, boff, b, evis, o);
-        else
-            k_cell_pairs_pt<false><<<nb, kBlock, 0, s>>>(x, vobj, pr, prims, g, dhat, ncell, qtoff, qent, qeoff, coff, cent,
-                                                         cnt, eoff, boff, b, evis, o);
-    } else {
-        if (emit)
-            k_cell_pairs_ee<true><<<nb, kBlock, 0, s>>>(x, vobj, pr, prims, g, dhat, ncell, qtoff, qent, qeoff, coff, cent,
-                                                        cnt, eoff, boff, b, evis, o);
-        else
-            k_cell_pairs_ee<false><<<nb, kBlock, 0, s>>>(x, vobj, pr, prims, g, dhat, ncell, qtoff, qent, qeoff, coff,
-                                                         cent, cnt, eoff, boff, b, evis, o);
-    }
-    return hipGetLastError();
+    const auto kernel = kind == 0 ? (emit ? k_cell_pairs_pt<true> : k_cell_pairs_pt<false>)
+                                  : (emit ? k_cell_pairs_ee<true> : k_cell_pairs_ee<false>);
+    return cell_slices(ncell, [&](int64_t c0, unsigned nwg) {
+        kernel<<<nwg, kBlock, 0, s>>>(x, vobj, pr, prims, g, dhat, c0, ncell, qtoff, qent, qeoff, coff, cent, cnt, eoff,
+                                      boff, b, evis, o);
+    });
 }
 
 }  // namespace gipc
