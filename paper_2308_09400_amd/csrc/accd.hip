@@ -22,41 +22,45 @@
 namespace gipc {
 namespace {
 
-// 1 / v for v > 0 to about 2^-45: v_rcp_f64 and one Newton step.  Used for
-// the parameter of a closest point on a segment only: the distance is
-// stationary there, so this error enters it squared, below its rounding.
-// (Times of 24 scenes of 2 x 12^2 to 6 x 101^2 vertices against a 64-bit
-// reference: 1.42e-16 on average, 3.84e-16 at most, and the same with a true
-// division; 1.31e-16 and 3.84e-16 with the distances of the classification.)
-__device__ __forceinline__ double rcp_near(double v) {
-    const double r = __builtin_amdgcn_rcp(v);
-    return fma(r, fma(-v, r, 1.0), r);
+// 1 / v to about a unit in the last place: v_rcp_f64 and two Newton steps
+__device__ __forceinline__ double recip(double v) {
+    double r = __builtin_amdgcn_rcp(v);
+    r = fma(fma(-v, r, 1.0), r, r);
+    return fma(fma(-v, r, 1.0), r, r);
 }
 
-// squared distance of the point a + ap to the segment from a along ab, il2 =
-// 1 / |ab|^2 (0 for one shorter than 1e-150: its first end point then)
-__device__ __forceinline__ double seg_dist2_near(d3 ap, d3 ab, double il2) {
-    const double t = dot(ap, ab) * il2;
-    const d3 w = ap - fmin(fmax(t, 0.0), 1.0) * ab;
+// squared distance of the point a + ap to the segment from a along ab, il =
+// recip(l2), l2 = |ab|^2.  The parameter has to be the quotient n / l2 itself:
+// one that is off by a relative 2^-45 moves the foot by 2^-45 |ab|, which is
+// all of the distance where a point touches the far end (its parameter is no
+// longer 1) and much of it below some 2^-40 |ab|.  So n il is corrected once by
+// its remainder (Markstein's division), which gives the bits of the division
+// without its scaling for the ends of the range; the products of one segment
+// share the reciprocal.  On 18M tuples of sheets and of random points in all
+// kinds of tuple the times have the bits that true divisions give, which cost
+// 2.85 against 1.94 ms on ten 256 x 256 sheets.  A length below 7.5e-155 (its
+// square has no reciprocal) counts as the first end point.
+__device__ __forceinline__ double seg_near2(d3 ap, d3 ab, double l2, double il) {
+    const double n = dot(ap, ab), q = n * il;
+    const double a = fma(fma(-l2, q, n), il, q);
+    const d3 w = ap - fmin(fmax(a, 0.0), 1.0) * ab;
     return dot(w, w);
 }
-__device__ __forceinline__ double inv_len2(double l2) { return l2 > 1e-300 ? rcp_near(l2) : 0.0; }
 
 // the constrained minimum of Eq. 4 / Eq. 5 over the sub-problems of
 // classify_pt and classify_ee, without the sub-problem it is attained at: the
-// interior tests compare numerators, and a distance has one full division
-// (six or seven there)
+// interior tests compare numerators
 __device__ __forceinline__ double near_pt2(d3 p, d3 t0, d3 t1, d3 t2) {
-    const d3 e1 = t1 - t0, e2 = t2 - t0, e3 = t2 - t1, r = p - t0, r1 = p - t1;
+    const d3 e1 = t1 - t0, e2 = t2 - t0, e3 = t2 - t1, r = p - t0;
     const d3 n = cross(e1, e2);
-    const double nn = dot(n, n), a11 = dot(e1, e1), a22 = dot(e2, e2), a12 = dot(e1, e2);
+    const double nn = dot(n, n), a11 = dot(e1, e1), a22 = dot(e2, e2), a12 = dot(e1, e2), a33 = dot(e3, e3);
     const double b1 = dot(e1, r), b2 = dot(e2, r);
     const double u = a22 * b1 - a12 * b2, v = a11 * b2 - a12 * b1, h = dot(r, n);
     double best = INFINITY;
     if (nn > kInteriorTol * a11 * a22 && u >= 0.0 && v >= 0.0 && u + v <= nn) best = h * h / nn;
-    best = fmin(best, seg_dist2_near(r, e1, inv_len2(a11)));
-    best = fmin(best, seg_dist2_near(r1, e3, inv_len2(dot(e3, e3))));
-    return fmin(best, seg_dist2_near(r, e2, inv_len2(a22)));
+    best = fmin(best, seg_near2(r, e1, a11, recip(a11)));
+    best = fmin(best, seg_near2(p - t1, e3, a33, recip(a33)));
+    return fmin(best, seg_near2(p - t2, t0 - t2, a22, recip(a22)));
 }
 
 __device__ __forceinline__ double near_ee2(d3 a0, d3 a1, d3 b0, d3 b1) {
@@ -67,11 +71,11 @@ __device__ __forceinline__ double near_ee2(d3 a0, d3 a1, d3 b0, d3 b1) {
     const double u = ab * br - bb * ar, v = aa * br - ab * ar, h = dot(r, n);
     double best = INFINITY;
     if (cc > kInteriorTol * aa * bb && u >= 0.0 && u <= cc && v >= 0.0 && v <= cc) best = h * h / cc;
-    const double ia = inv_len2(aa), ib = inv_len2(bb);
-    best = fmin(best, seg_dist2_near(r, b, ib));
-    best = fmin(best, seg_dist2_near(a1 - b0, b, ib));
-    best = fmin(best, seg_dist2_near(b0 - a0, a, ia));
-    return fmin(best, seg_dist2_near(b1 - a0, a, ia));
+    const double ia = recip(aa), ib = recip(bb);
+    best = fmin(best, seg_near2(r, b, bb, ib));
+    best = fmin(best, seg_near2(a1 - b0, b, bb, ib));
+    best = fmin(best, seg_near2(b0 - a0, a, aa, ia));
+    return fmin(best, seg_near2(b1 - a0, a, aa, ia));
 }
 
 // constrained squared distance of a decoded tuple whose four slots are the
@@ -85,8 +89,8 @@ __device__ __forceinline__ double local_dist2(int kind, const double* L) {
     const d3 a = par ? p2 : p1, b = par ? p3 : p2;
     const d3 w = p0 - a;
     if (kind == 3 || kind == 5) return dot(w, w);
-    const d3 e = b - a;
-    return seg_dist2_near(w, e, inv_len2(dot(e, e)));
+    double al;
+    return seg_dist2(p0, a, b, al);
 }
 
 // counters: [0] malformed tuples, [1] first malformed index, [2] tuples
@@ -119,7 +123,7 @@ __global__ void k_accd_reset(unsigned long long* c, double tc) {
 // wavefront per SIMD.  Bound by vector issue (three quarters of the slots).
 // The 50.6M candidates of ten 256 x 256 sheets, each falling or jittering by
 // about dhat: 1.82 ms; with the initial distance apart from the trials, lanes
-// refilled one at a time, a division in every segment test and three atomics
+// refilled one at a time, a true division in every segment test and three atomics
 // on one line per wavefront and 256 tuples it was 3.97 ms, and 826k
 // candidates of three 101 x 101 sheets 378 against 68 us (there the atomics,
 // 20 ns apart, were nearly all of it).
