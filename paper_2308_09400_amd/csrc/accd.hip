@@ -122,7 +122,7 @@ __global__ void k_accd_reset(unsigned long long* c, double tc) {
 // The displacements stay in LDS, 24 registers fewer and so a fourth
 // wavefront per SIMD.  Bound by vector issue (three quarters of the slots).
 // The 50.6M candidates of ten 256 x 256 sheets, each falling or jittering by
-// about dhat: 1.82 ms; with the initial distance apart from the trials, lanes
+// about dhat: 1.89 ms; with the initial distance apart from the trials, lanes
 // refilled one at a time, a true division in every segment test and three atomics
 // on one line per wavefront and 256 tuples it was 3.97 ms, and 826k
 // candidates of three 101 x 101 sheets 378 against 68 us (there the atomics,
@@ -152,7 +152,7 @@ __global__ void __launch_bounds__(kBlock, 4) k_accd_queue(const int4* __restrict
     __shared__ double sdp[kBlock / 64][12][64];
     double(*dl)[64] = sdp[threadIdx.x >> 6];  // the lanes' displacements
     double x0[12];
-    double lp = 0.0, ilp = 0.0, g = 0.0, t = 0.0, tl = 0.0, tmin = tc;
+    double lp = 0.0, g = 0.0, t = 0.0, tl = 0.0, tmin = tc;
     while (true) {
         const unsigned long long idle = __ballot(!act);
         if (!exhausted && __popcll(idle) >= kAccdRefill) {
@@ -202,7 +202,7 @@ __global__ void __launch_bounds__(kBlock, 4) k_accd_queue(const int4* __restrict
                         case 4: sb = 2; ns = 2; break;
                         default: sb = 2; break;
                     }
-                    const double im = nf + ns == 4 ? 0.25 : (nf + ns == 3 ? 1.0 / 3.0 : 0.5);
+                    const double im = nf + ns == 4 ? 0.25 : 0.5;  // exact
                     double m[3] = {0.0, 0.0, 0.0};
 #pragma unroll
                     for (int k = 0; k < 4; ++k) {
@@ -211,7 +211,7 @@ __global__ void __launch_bounds__(kBlock, 4) k_accd_queue(const int4* __restrict
                         for (int d = 0; d < 3; ++d) m[d] += in ? dp[3 * k + d] : 0.0;
                     }
 #pragma unroll
-                    for (int d = 0; d < 3; ++d) m[d] *= im;
+                    for (int d = 0; d < 3; ++d) m[d] = nf + ns == 3 ? m[d] / 3.0 : m[d] * im;
 #pragma unroll
                     for (int k = 0; k < 4; ++k)
 #pragma unroll
@@ -227,7 +227,6 @@ __global__ void __launch_bounds__(kBlock, 4) k_accd_queue(const int4* __restrict
                         else if (k >= sb && k < sb + ns) l2 = fmax(l2, n2);
                     }
                     lp = sqrt(l1) + sqrt(l2);
-                    ilp = 1.0 / lp;
                 }
             }
             cb += take;
@@ -258,7 +257,7 @@ __global__ void __launch_bounds__(kBlock, 4) k_accd_queue(const int4* __restrict
                     const double d0 = sqrt(dd2);
                     g = s * d0;
                     t = 0.0;
-                    tl = (1.0 - s) * d0 * ilp;
+                    tl = (1.0 - s) * d0 / lp;
                     it = 0;
                     if (tl > tc) {
                         res = tc;
@@ -281,7 +280,7 @@ __global__ void __launch_bounds__(kBlock, 4) k_accd_queue(const int4* __restrict
                         res = tc;
                         fin = true;
                     } else {
-                        tl = 0.9 * dd * ilp;
+                        tl = 0.9 * dd / lp;
                         if (it >= max_iter) {
                             atomicAdd(&c[2], 1ull);
                             res = t;

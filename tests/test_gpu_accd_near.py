@@ -10,6 +10,11 @@
   from a rounded product over a rounded square (three roundings) and its
   product with the edge is one more, 2^-51 L in all; d^2 + (2^-51 L)^2 is
   d (1 + (2^-51 L / d)^2 / 2), and 2^-48 covers the few roundings besides.
+* The first sub-step is the quotient (1 - s) d / l_p, and the mean motion a
+  quotient by the number of vertices, to the last bit: a point at a distance
+  that is exact falls onto a point, an edge or a triangle, so all of l_p's
+  roundings are those of the same sums in numpy (the root of a rounded square
+  is the number itself).
 """
 import numpy as np
 import pytest
@@ -104,3 +109,21 @@ def test_near_an_axis_aligned_edge(gp, ctx, kind, ratio):
           flush=True)
     assert info["n_touching"] == 0 and info["n_capped"] == 0
     assert (err <= bound).all()
+
+
+@pytest.mark.parametrize("kind", ["pp", "pe", "pt"])
+def test_first_sub_step_to_the_last_bit(gp, ctx, kind):
+    rng = np.random.default_rng(17)
+    P, nv = 2000, dict(pp=2, pe=3, pt=4)[kind]
+    d, v = rng.uniform(0.5, 2.0, P), rng.uniform(0.5, 2.0, P)
+    X, D = np.zeros((P, 4, 3)), np.zeros((P, 4, 3))
+    X[:, 0, 1], D[:, 0, 1] = d, -v
+    if kind != "pp":  # the point above (0, 0, 0), a quarter along the edge, or both edges of a triangle of area 8
+        X[:, 1, 0], X[:, 2, 0] = -1.0, 3.0
+        if kind == "pt":
+            X[:, 1:3, 2], X[:, 3, 0], X[:, 3, 2] = -1.0, -1.0, 3.0
+    toi, info = _run(gp, ctx, X, D, _tuples(kind, P), tc=1e9)
+    m = -v / nv
+    lp = np.abs(-v - m) + np.abs(0.0 - m)
+    assert info["max_steps"] == 2
+    assert np.array_equal(toi, (1.0 - S) * d / lp)
