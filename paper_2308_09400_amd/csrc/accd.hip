@@ -122,7 +122,7 @@ __global__ void k_accd_reset(unsigned long long* c, double tc) {
 // The displacements stay in LDS, 24 registers fewer and so a fourth
 // wavefront per SIMD.  Bound by vector issue (three quarters of the slots).
 // The 50.6M candidates of ten 256 x 256 sheets, each falling or jittering by
-// about dhat: 1.89 ms; with the initial distance apart from the trials, lanes
+// about dhat: 1.91 ms; with the initial distance apart from the trials, lanes
 // refilled one at a time, a true division in every segment test and three atomics
 // on one line per wavefront and 256 tuples it was 3.97 ms, and 826k
 // candidates of three 101 x 101 sheets 378 against 68 us (there the atomics,
@@ -241,7 +241,7 @@ __global__ void __launch_bounds__(kBlock, 4) k_accd_queue(const int4* __restrict
             double xt[12];
 #pragma unroll
             for (int j = 0; j < 12; ++j) xt[j] = fma(ts, dl[j][lane], x0[j]);
-            if (fresh && !(lp < INFINITY)) {  // 0 * infinity: a displacement that is not finite
+            if (fresh && !(lp > 0.0 && lp < INFINITY)) {  // a displacement that is not finite times 0 (NaN: lp = 0)
 #pragma unroll
                 for (int j = 0; j < 12; ++j) xt[j] = x0[j];
             }

@@ -15,6 +15,9 @@
   that is exact falls onto a point, an edge or a triangle, so all of l_p's
   roundings are those of the same sums in numpy (the root of a rounded square
   is the number itself).
+* A displacement with a NaN has no rate of approach: tc, not counted, as for
+  no relative motion.  An infinite one has no sub-step: the search ends at
+  max_iter and is counted as capped, not as touching.
 """
 import numpy as np
 import pytest
@@ -127,3 +130,17 @@ def test_first_sub_step_to_the_last_bit(gp, ctx, kind):
     lp = np.abs(-v - m) + np.abs(0.0 - m)
     assert info["max_steps"] == 2
     assert np.array_equal(toi, (1.0 - S) * d / lp)
+
+
+@pytest.mark.parametrize("kind", sorted(ENDS))
+def test_displacement_not_finite(gp, ctx, kind):
+    rng = np.random.default_rng(23)
+    used = sorted(ENDS[kind][0] + ENDS[kind][1])
+    P = 12 * len(used)
+    for value, capped in ((np.nan, 0), (np.inf, P), (-np.inf, P)):
+        X, D = rng.normal(size=(P, 4, 3)), rng.normal(size=(P, 4, 3))
+        D[np.arange(P), np.resize(used, P), np.arange(P) // len(used) % 3] = value
+        toi, info = _run(gp, ctx, X, D, _tuples(kind, P), tc=0.75)
+        assert info["n_touching"] == 0 and info["n_capped"] == capped
+        if np.isnan(value):
+            assert (toi == 0.75).all() and info["step"] == 0.75
