@@ -25,15 +25,12 @@ enum TupleStatus { TS_OK = 0, TS_BAD = 1, TS_SPAN = 2, TS_DEGEN = 3 };
 // classified at X: ft is its
 // sub-type if it is closer than its scene's dhat (else FT_NONE), vo its
 // staged stencil, dprim whether a primitive is degenerate (an edge of zero
-// length, a triangle of zero area) while the distance is still positive; s
-// and d2 are the closest sub-problem and its squared distance, active or not.
+// length, a triangle of zero area) while the distance is still positive.
 __device__ inline int classify_tuple(const int4 t, int32_t V, const double* __restrict__ X,
                                      const double* __restrict__ XR, const DevParams& pm, int& ft, int4& vo,
-                                     bool& dprim, Staged& s, double& d2) {
+                                     bool& dprim) {
     ft = FT_NONE;
     vo = make_int4(-1, -1, -1, -1);
-    d2 = 0.0;
-    s = Staged{FT_NONE, {-1, -1, -1, -1}};
     dprim = false;
     int v[4], nv;
     const int kind = decode_tuple(t, V, v, nv);
@@ -43,7 +40,9 @@ __device__ inline int classify_tuple(const int4 t, int32_t V, const double* __re
         for (int k = 1; k < nv; ++k)
             if (pm.vscene[v[k]] != s0) return TS_SPAN;
     }
+    double d2;
     bool degen = false;
+    Staged s;
     if (kind == 0) s = classify_ee(X, XR, v[0], v[1], v[2], v[3], pm, d2, degen);
     else if (kind == 1) s = classify_pt(X, v[0], v[1], v[2], v[3], d2, degen);
     else if (kind == 2) s = classify_pe(X, v[0], v[1], v[2], d2, degen);
@@ -77,9 +76,7 @@ __global__ void __launch_bounds__(kBlock) k_stage_classify(const int4* __restric
     if (p < P) {
         int4 vo;
         bool dprim;
-        Staged sub;
-        double d2;
-        const int st = classify_tuple(tuples[p], V, X, XR, pm, ft, vo, dprim, sub, d2);
+        const int st = classify_tuple(tuples[p], V, X, XR, pm, ft, vo, dprim);
         if (st == TS_BAD) flag_index(&counters[0], &counters[1], p);
         else if (st == TS_SPAN) flag_index(&counters[20], &counters[21], p);
         else if (st == TS_DEGEN) flag_index(&counters[2], &counters[3], p);
@@ -132,9 +129,7 @@ __global__ void __launch_bounds__(kBlock) k_stage_check(const int4* __restrict__
         int ft;
         int4 vo;
         bool dprim;
-        Staged sub;
-        double d2;
-        const int st = classify_tuple(tuples[p], V, X, XR, pm, ft, vo, dprim, sub, d2);
+        const int st = classify_tuple(tuples[p], V, X, XR, pm, ft, vo, dprim);
         if (st == TS_BAD || st == TS_SPAN) {
             which = 4;
         } else {
@@ -148,18 +143,9 @@ __global__ void __launch_bounds__(kBlock) k_stage_check(const int4* __restrict__
                 // uses, also puts the pair at or beyond dhat
                 const int4 b = vid_b[p];
                 const int bv[4] = {b.x, b.y, b.z, b.w};
-                double dhat, kappa;
-                scene_params(pm, bv[0], dhat, kappa);
-                const bool same = sub.ft == fb && sub.v[0] == bv[0] && sub.v[1] == bv[1] && sub.v[2] == bv[2] &&
-                                  sub.v[3] == bv[3];
-                which = 1;
-                // the same sub-problem at a distance clearly beyond dhat: its staged
-                // formula is this distance up to rounding, no evaluation needed
-                if (!(same && d2 > (1.0 + 1e-9) * (dhat * dhat))) {
-                    PairFactors o;
-                    eval_typed(fb, bv, X, XR, pm, o);
-                    if (o.E != 0.0 || o.a2 != 0.0 || o.P22 != 0.0) which = 2;
-                }
+                PairFactors o;
+                eval_typed(fb, bv, X, XR, pm, o);
+                which = (o.E != 0.0 || o.a2 != 0.0 || o.P22 != 0.0) ? 2 : 1;
             } else if (fb != FT_NONE) {
                 const int4 b = vid_b[p];
                 if (fb != ft || b.x != vo.x || b.y != vo.y || b.z != vo.z || b.w != vo.w) which = 2;
