@@ -202,17 +202,11 @@ __device__ __forceinline__ int decode_tuple(const int4 t, int32_t V, int v[4], i
     }
     v[0] = v[1] = v[2] = v[3] = -1;
     nv = 0;
-    if (t.x >= 0) {
-        if (t.z >= 0 && t.w >= 0) {
-            kind = 0; nv = 4;
-            v[0] = t.x; v[1] = t.y >= 0 ? t.y : ~t.y; v[2] = t.z; v[3] = t.w;
-        }
-    } else if (t.y >= 0) {
+    if (t.x < 0 && t.y >= 0) {
         v[0] = ~t.x; v[1] = t.y;
-        if (t.z >= 0 && t.w >= 0) { kind = 1; nv = 4; v[2] = t.z; v[3] = t.w; }
-        else if (t.z >= 0 && t.w == -1) { kind = 2; nv = 3; v[2] = t.z; }
+        if (t.z >= 0 && t.w == -1) { kind = 2; nv = 3; v[2] = t.z; }
         else if (t.z == -1 && t.w == -1) { kind = 3; nv = 2; }
-    } else if (t.w < 0) {
+    } else if (t.x < 0 && t.w < 0) {
         v[0] = ~t.x; v[1] = ~t.y; v[3] = ~t.w; nv = 4;
         if (t.z >= 0) { kind = 4; v[2] = t.z; }
         else { kind = 5; v[2] = ~t.z; }
