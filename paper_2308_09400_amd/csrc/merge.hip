@@ -62,9 +62,9 @@ __device__ __forceinline__ uint64_t home(const Key& k, unsigned long long f, dou
     return ((uint64_t)((double)(uint32_t)k.a * scale) + ((f >> kRepBits) & 15ull)) & mask;
 }
 
-// Probes stop after kMaxProbe slots: a pair whose key finds neither its
-// slot nor an empty one that close to home stays unmerged (exact, only
-// slower); both passes walk the same sequence, so they agree.
+// Probes stop after kMaxProbe slots: a group whose key finds neither its
+// slot nor an empty one that close to home stands for itself (exact, only
+// slower).
 constexpr int kMaxProbe = 4096;
 
 // pairs [k0, k1) are PE then PP from pp0 on.  slot[k - k0] = the key's slot,

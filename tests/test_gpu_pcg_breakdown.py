@@ -4,11 +4,12 @@ last good iterate.
 
 The right-hand side of a chain sits in its first row, so the search direction
 of iteration k reaches row k; the block of row 5 is -I / 1000 there, and p.Ap
-is first negative in the sixth iteration, after five good ones.  The iterations before do the same operations in the same order however many
-are asked for, so x equals the five iterations' x bit for bit, in every entry
+is first negative in the sixth iteration, after five good ones.  The
+iterations before do the same operations in the same order however many are
+asked for, so x equals the five iterations' x bit for bit, in every entry
 point: the counted ones, which report the breakdown, and the enqueue-only
-call, which cannot.  (The paper's termination stops after the five:
-r.z is negative by then.)
+call, which cannot.  (The paper's termination stops after the five: r.z is
+negative by then.)
 """
 import numpy as np
 import pytest
