@@ -43,7 +43,7 @@
 // every scalar (alpha, beta, residual norms, the stopping test) lives in
 // device memory, so an iteration is a few kernel launches without host
 // round trips (product, p.q partials, alpha, update with the r.z and r.r
-// partials, beta, p update: six, four up to 65536 rows and two up to 4096,
+// partials, beta, p update: six, four up to 98304 rows and two up to 1536,
 // see kMergeParts); the host polls the "done" flag every 16
 // iterations (once when rtol = 0).  Every other iteration walks the matrix
 // backwards, so that it starts with the blocks read last, some of which the
@@ -484,15 +484,19 @@ __global__ void __launch_bounds__(kBlock) k_pupdate(int64_t n, const double* __r
 // every workgroup of the update forms alpha, and every one of the p update
 // beta, from the partials itself (a few KB from L2): two launches fewer.  Up
 // to kVecRows rows one workgroup does everything between two products: four
-// launches fewer, about 4.5 us each where launches are what a solve waits
-// for.  A whole Newton step of two 16 x 16 sheets (512 rows, 16 iterations)
-// 1.22 -> 0.93 ms, of three 101 x 101 sheets (30603 rows, 16 iterations) with
-// 0.31 ms of it from elsewhere 1.88 -> 1.46 ms.  One workgroup walks 4096 rows
-// in about the time of the three launches it saves; above 65536 rows the
-// partials that every workgroup would read again outweigh a launch.
-constexpr int kMergeParts = 256;
+// launches fewer (three fewer without a matrix, whose product leaves the
+// partials of p.q itself).  Where the lines lie, 32 iterations in us with one
+// workgroup / merged / six launches:
+//   matrix       512 rows 442 / 574 / 731, 1458 rows 538 / 588, 1800 rows
+//                596 / 579, 4050 rows 836 / 583 / 747; 65522 rows 1120 merged
+//                and 1215, 100352 1484 and 1574, 262144 3921 and 3918, 524288
+//                8549 and 8316
+//   matrix-free  512 rows 622 / 670 / 771, 1152 rows 676 / 667, 4050 rows 1000
+//                / 679 / 801; 65522 rows 1432 merged and 1518, 100352 2033 and
+//                2057, 131072 2605 and 2559
+constexpr int kMergeParts = 384;
 constexpr int kVecThreads = 1024;
-constexpr int kVecRows = 4096;
+constexpr int kVecRows = 1536, kVecRowsMf = 1024;
 
 // sum of part[0..n), in every thread of the workgroup (fixed order)
 __device__ __forceinline__ double wg_total(const double* __restrict__ part, int64_t n, double* lds) {
@@ -594,7 +598,7 @@ __global__ void __launch_bounds__(kVecThreads) k_pcg_vec(int32_t V, double* __re
                                                          PcgScalars* sc, int cur) {
     if (sc->done) return;
     __shared__ double lds[kVecThreads / 64], tot[3];
-    constexpr int M = kVecRows / kVecThreads;
+    constexpr int M = (kVecRows + kVecThreads - 1) / kVecThreads;
     double d = 0.0;
     for (int64_t i = threadIdx.x; i < V; i += kVecThreads) d += dot(ldv(p, i), ldv(q, i));
     d = block_sum_n<kVecThreads>(d, lds);
@@ -811,7 +815,7 @@ static hipError_t pcg_exec(const gipc_bsr& A, const double* b, double* x, double
 
     // partials of p.q apart from those of r.z and r.r (over b.b, which is read once)
     double* pqpart = part + 2 * pcg_num_parts(A, mf);
-    const bool tiny = V <= kVecRows, merged = nbv <= kMergeParts;
+    const bool tiny = V <= (mf ? kVecRowsMf : kVecRows), merged = nbv <= kMergeParts;
 
     k_pcg_reset<<<1, 64, 0, s>>>(sc);
     // r = b - A x0 (for FP32 matrices through an FP32 copy of x0)

@@ -25,7 +25,7 @@ K = 5
 
 
 @pytest.mark.parametrize("dtype", ["f64", "f32"])
-@pytest.mark.parametrize("V", [4096, 4097, 65536, 65537])
+@pytest.mark.parametrize("V", [1536, 1537, 4096, 4097, 65536, 65537, 98304, 98305])
 def test_x_at_a_late_breakdown(gp, V, dtype):  # noqa: F811
     dt = gp.F64 if dtype == "f64" else gp.F32
     rows, cols, vals = _chain(V)
