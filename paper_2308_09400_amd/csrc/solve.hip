@@ -21,8 +21,9 @@
 // non-temporal column loads (264 us) and a contiguous eighth of the
 // workgroups per XCD (259 against 257 us in that run).  Short runs of 16
 // workgroups per XCD share the gathered x lines without touching eight far
-// places of the matrix at once: 265 against 272 us (runs of 256: 268), a solve
-// of 20 iterations 6.80 against 6.90 ms.  For FP32 blocks the row kernel
+// places of the matrix at once: 257 against 267 us product after product, 326
+// against 328 with 1 GB written in between (runs of 256: 268 against 272 in
+// another run).  For FP32 blocks the row kernel
 // stays (161 us against 163 us), and a descriptor without the map uses it too.
 //
 // SpMV by rows (k_spmv): G = 32 lanes per block row (two rows per
@@ -33,8 +34,14 @@
 // Rows of the contact matrices hold about 27 blocks, so most lanes issue all
 // their loads at once.  Measured on the ten-sheet matrix, FP64: 4 / 8 / 16 /
 // 32 / 64 lanes = 815 / 373 / 311 / 296 / 383 us; FP32: 8 / 16 / 32 lanes =
-// 228 / 178 / 163 us.  Runs of 256 workgroups per XCD: seven 201 x 201 sheets
-// in FP32 50 against 58 us (runs of 16: 52).  At 8 lanes, non-temporal value loads (573 us) and
+// 228 / 178 / 163 us.  Runs of 64 workgroups per XCD, in FP32, product after
+// product and with 1 GB written in between: ten 256 x 256 sheets 157 / 199
+// against 168 / 205 us without runs, seven 201 x 201 63.4 / 102 against 65.7 /
+// 102, five 200 x 200 35.8 / 80 against 42.8 / 80 (runs of 16 much the same;
+// of 256 warm the same, but seven 201 x 201 take 105 us cold).  Inside the
+// PCG, where the matrix is warm or too large to be, runs of 256: 32 iterations
+// on five 200 x 200 sheets 2020 us, 2052 with 64, 2205 without; on seven
+// 201 x 201 3468, 3501 and 3461.  At 8 lanes, non-temporal value loads (573 us) and
 // XCD-contiguous row chunks (405 us) were slower; at 32 lanes, two to four
 // rows per lane group (315-340 us) were too.
 //
@@ -47,8 +54,9 @@
 // see kMergeParts); the host polls the "done" flag every 16
 // iterations (once when rtol = 0).  Every other iteration walks the matrix
 // backwards, so that it starts with the blocks read last, some of which the
-// 256 MB cache still holds: 6.84 against 6.94 ms for 20 iterations on ten
-// 256 x 256 sheets (1.25 GB of blocks).  The p.q partials are a pass of their
+// 256 MB cache still holds: 32 iterations on ten 256 x 256 sheets (1.25 GB of
+// blocks) 10.57 against 10.71 ms, each within 0.01 when timed in turn; on 0.1
+// to 0.5 GB no difference.  The p.q partials are a pass of their
 // own over p and q: formed in the product's epilogue (a block reduction
 // at the end of every product workgroup) they cost 355 against 327 us per
 // FP64 iteration on the ten-sheet matrix, and 254 against 223 us in FP32.
@@ -58,12 +66,13 @@ namespace gipc {
 namespace {
 
 constexpr int kG = 32;  // lanes per block row
+constexpr int kRowRun = 64;  // workgroups an XCD takes in a row
 
 template <typename T>
 __global__ void __launch_bounds__(kBlock) k_spmv(int32_t nrows, const int32_t* __restrict__ rp,
                                                  const int32_t* __restrict__ ci, const T* __restrict__ val,
                                                  int64_t nnzb, const T* __restrict__ x, T* __restrict__ y) {
-    const int64_t row = (xcd_block() * kBlock + threadIdx.x) / kG;
+    const int64_t row = ((int64_t)xcd_run<kRowRun>(blockIdx.x, gridDim.x) * kBlock + threadIdx.x) / kG;
     const int lg = threadIdx.x % kG;
     T a0 = 0, a1 = 0, a2 = 0;
     if (row < nrows) {
