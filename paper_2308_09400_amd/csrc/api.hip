@@ -501,16 +501,19 @@ gipc_status gipc_pairs_check(gipc_ctx* ctx, const gipc_mesh* mesh, const gipc_pa
     int64_t init[kCheckCopies][kCheckStride] = {}, hc[kCheckCopies][kCheckStride];
     for (auto& c : init) c[5] = INT64_MAX;
     CK(ensure(ctx->chk, sizeof(init)), "alloc check counters");
-    CK(hipMemcpyAsync(ctx->chk.p, init, sizeof(init), hipMemcpyHostToDevice, s), "clear check counters");
+    // the copies that the workgroups of this list use
+    const size_t copies = (size_t)std::min<int64_t>(kCheckCopies, (pairs->P + kBlock - 1) / kBlock);
+    const size_t bytes = copies * sizeof(init[0]);
+    CK(hipMemcpyAsync(ctx->chk.p, init, bytes, hipMemcpyHostToDevice, s), "clear check counters");
     CK(launch_stage_check(pairs->tuples, pairs->P, mesh->V, mesh->x, xr, pm, as<uint8_t>(ctx->cand_ft),
                           as<int4>(ctx->cand_vid), as<int64_t>(ctx->chk), s),
        "check");
-    CK(hipMemcpyAsync(hc, ctx->chk.p, sizeof(hc), hipMemcpyDeviceToHost, s), "copy check counters");
+    CK(hipMemcpyAsync(hc, ctx->chk.p, bytes, hipMemcpyDeviceToHost, s), "copy check counters");
     CK(hipStreamSynchronize(s), "stream synchronize");
     int64_t h[6] = {0, 0, 0, 0, 0, INT64_MAX};
-    for (const auto& c : hc) {
-        for (int i = 0; i < 5; ++i) h[i] += c[i];
-        h[5] = std::min(h[5], c[5]);
+    for (size_t k = 0; k < copies; ++k) {
+        for (int i = 0; i < 5; ++i) h[i] += hc[k][i];
+        h[5] = std::min(h[5], hc[k][5]);
     }
     if (h[4] > 0) return fail(ctx, GIPC_ERR_INDEX, "%lld malformed tuple(s)", (long long)h[4]);
     gipc_check c{h[0], h[1], h[2], h[3], (h[0] + h[2] > 0) ? h[5] : -1};
