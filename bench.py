@@ -69,7 +69,7 @@ MEASURED_TRAFFIC = {
     "source": "profiles/sheets10_path.md (rocprofv3 FETCH_SIZE x 2.0 + WRITE_SIZE x 1.0 per dispatch, "
               "calibrated on the library's 2 GiB copy in the same run)",
     "file": "paper_2308_09400_amd/csrc/solve.hip",
-    "sha256": "690161e36e9009018877ef60b73a54984efbbb1d2236607306164743ac2a52bd",
+    "sha256": "d7f2c88bb423dd3f742397b2f85209b41977d7ff12ee976effce9a3de76dda77",
 }
 
 

@@ -123,10 +123,10 @@ __global__ void k_accd_reset(unsigned long long* c, double tc) {
 // wavefront per SIMD.  Bound by vector issue (three quarters of the slots).
 // The 50.6M candidates of ten 256 x 256 sheets, each falling or jittering by
 // about dhat: 1.91 ms; with the initial distance apart from the trials, lanes
-// refilled one at a time, a true division in every segment test and three atomics
-// on one line per wavefront and 256 tuples it was 3.97 ms, and 826k
-// candidates of three 101 x 101 sheets 378 against 68 us (there the atomics,
-// 20 ns apart, were nearly all of it).
+// refilled one at a time, a true division in every segment test and three
+// atomics on one line per wavefront and 256 tuples it was 3.97 ms, and 826k
+// candidates of three 101 x 101 sheets 386 against 86 us a call (there the
+// atomics, 20 ns apart, were nearly all of it).
 // The grid is at most the workgroups the chip holds at once; each wavefront
 // starts with a chunk of its own and takes further ones from the queue until
 // it is empty; every search ends within max_iter steps, so every wavefront
