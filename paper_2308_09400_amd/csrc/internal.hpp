@@ -341,7 +341,8 @@ hipError_t launch_stage_scatter(const uint8_t* ft, const int4* vid, int64_t P, c
 // the build's classification (ft_b, vid_b) against the one at x; counters
 // (device int64 [kCheckCopies][kCheckStride], each copy's first six zeroed,
 // [5] = INT64_MAX): entered, left, changed, degenerate, malformed, first
-// changed tuple; the result is the sum (the smallest [5]) over the copies
+// changed tuple; the result is the sum (the smallest [5]) over the copies in
+// use, one per workgroup of kBlock tuples up to kCheckCopies
 constexpr int kCheckCopies = 64, kCheckStride = 16;
 hipError_t launch_stage_check(const int32_t* tuples, int64_t P, int32_t V, const double* x, const double* xr,
                               const DevParams& pm, const uint8_t* ft_b, const int4* vid_b, int64_t* counters,
